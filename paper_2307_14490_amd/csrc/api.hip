@@ -739,14 +739,28 @@ bool walk_config_ok(const huge_walk_config* c) {
     return true;
 }
 
+struct WalkLayout {
+    size_t offsets, counts, sums, nodes, total;
+};
+
+WalkLayout walk_layout(int64_t num_seeds) {
+    const size_t n = (size_t)(num_seeds > 0 ? num_seeds : 1);
+    WalkLayout L;
+    L.offsets = 0;
+    L.counts = L.offsets + align_up(sizeof(uint64_t) * n);
+    L.sums = L.counts + align_up(sizeof(uint32_t) * n);
+    L.nodes = L.sums + align_up(sizeof(uint64_t) * (size_t)kWalkRanges);
+    L.total = L.nodes + align_up((size_t)walk_node_bytes((int64_t)n));
+    return L;
+}
+
 }  // namespace
 
 extern "C" {
 
 size_t huge_walk_workspace_bytes(const huge_walk_config* cfg, int64_t num_seeds) {
     if (!walk_config_ok(cfg) || num_seeds < 0) return 0;
-    const size_t n = (size_t)(num_seeds > 0 ? num_seeds : 1);
-    return align_up(sizeof(uint64_t) * n) + align_up(sizeof(uint32_t) * n);
+    return walk_layout(num_seeds).total;
 }
 
 huge_status huge_sample_walks(const huge_walk_config* cfg, const int64_t* d_offsets,
@@ -763,10 +777,15 @@ huge_status huge_sample_walks(const huge_walk_config* cfg, const int64_t* d_offs
     if (capacity > 0 && (!d_src || !d_dst || !d_cc)) return HUGE_ERR_INVALID_ARG;
     if ((uintptr_t)d_workspace % kAlign != 0) return HUGE_ERR_INVALID_ARG;
     if (ws_bytes < huge_walk_workspace_bytes(cfg, num_seeds)) return HUGE_ERR_WORKSPACE;
-    const size_t n = (size_t)(num_seeds > 0 ? num_seeds : 1);
     uint8_t* ws = static_cast<uint8_t*>(d_workspace);
-    uint64_t* offsets = reinterpret_cast<uint64_t*>(ws);
-    uint32_t* counts = reinterpret_cast<uint32_t*>(ws + align_up(sizeof(uint64_t) * n));
+    const WalkLayout L = walk_layout(num_seeds);
+    WalkBuffers B;
+    B.offsets = reinterpret_cast<uint64_t*>(ws + L.offsets);
+    B.counts = reinterpret_cast<uint32_t*>(ws + L.counts);
+    B.sums = reinterpret_cast<uint64_t*>(ws + L.sums);
+    B.nodes = reinterpret_cast<int32_t*>(ws + L.nodes);
+    B.node_cap = walk_node_bytes(num_seeds) / (int64_t)sizeof(int32_t);
+    const WalkOut O{d_count, capacity, d_src, d_dst, d_cc, d_hist, d_status};
     WalkArgs A;
     A.off = d_offsets;
     A.nbr = d_neighbors;
@@ -779,8 +798,8 @@ huge_status huge_sample_walks(const huge_walk_config* cfg, const int64_t* d_offs
     A.seed = cfg->seed;
     A.first_seed = first_seed;
     A.num_seeds = num_seeds;
-    HIP_TRY(launch_walks(A, counts, offsets, d_count, capacity, d_src, d_dst, d_cc, d_hist,
-                         d_status, static_cast<hipStream_t>(stream)));
+    const int32_t pairs = (int32_t)(cfg->walks_per_node * walk_pairs_per_walk(cfg));
+    HIP_TRY(launch_walks(A, pairs, B, O, static_cast<hipStream_t>(stream)));
     return HUGE_OK;
 }
 

@@ -69,11 +69,23 @@ constexpr int kSamplePos = 512;        // positives per sampler workgroup
 constexpr int kNegBlock = 8;           // negatives whose rows are in flight together
 constexpr int kMaxNeg = 64;
 constexpr int kMaxDim = 1024;
-// Random-walk sampler: one workgroup holds a seed's walks and pairs in LDS.
+// Random-walk sampler: one wave sorts a seed's pairs.
 constexpr int kWalkMaxWalks = 1024;    // walks per seed
 constexpr int kWalkMaxNodes = 8192;    // walks x (steps + 1)
 constexpr int kWalkMaxPairs = 4096;    // co-occurrence pairs of one seed
 constexpr int kWalkMaxSteps = 64;
+constexpr int64_t kWalkRanges = 1024;  // ranges of the scan of the triples' counts, at most
+// Workspace for the nodes of the walks: so much per seed, at least one seed's
+// and at most the last number; seeds beyond it are taken in chunks.  The
+// size depends on the number of seeds alone.
+constexpr int64_t kWalkNodeBytesPerSeed = 2048;
+constexpr int64_t kWalkNodeBytesMin = 4 * kWalkMaxNodes;
+constexpr int64_t kWalkNodeBytesMax = (int64_t)256 << 20;
+inline int64_t walk_node_bytes(int64_t num_seeds) {
+    if (num_seeds >= kWalkNodeBytesMax / kWalkNodeBytesPerSeed) return kWalkNodeBytesMax;
+    const int64_t b = num_seeds * kWalkNodeBytesPerSeed;
+    return b > kWalkNodeBytesMin ? b : kWalkNodeBytesMin;
+}
 constexpr int kWalkMaxWindow = 32;
 
 // Status bits of a step (Control::step_bad) and the sticky error code.
@@ -272,6 +284,25 @@ struct WalkArgs {
     int64_t num_seeds;
 };
 
+// Workspace of the sampler.
+struct WalkBuffers {
+    uint64_t* offsets;  // [num_seeds] first triple of each seed
+    uint32_t* counts;   // [num_seeds] triples of each seed
+    uint64_t* sums;     // [kWalkRanges]
+    int32_t* nodes;     // [node_cap] the nodes of a chunk's walks
+    int64_t node_cap;
+};
+
+struct WalkOut {
+    int64_t* count;
+    int64_t capacity;
+    int32_t* src;
+    int32_t* dst;
+    int32_t* cc;
+    int32_t* hist;  // or null
+    int32_t* status;
+};
+
 // ---------------------------------------------------------------------------
 // Launchers (each defined next to its kernels).  All return hipError_t of the
 // launch.
@@ -345,9 +376,9 @@ struct FinishArgs {
 hipError_t launch_finish(const TableArgs& t, Control* ctl, const FinishArgs& f, hipEvent_t stop,
                          hipStream_t s);
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
-hipError_t launch_walks(const WalkArgs& A, uint32_t* counts, uint64_t* offsets, int64_t* total,
-                        int64_t capacity, int32_t* src, int32_t* dst, int32_t* cc, int32_t* hist,
-                        int32_t* status, hipStream_t s);
+// pairs: the co-occurrence pairs of one seed, at most
+hipError_t launch_walks(const WalkArgs& A, int32_t pairs, const WalkBuffers& B, const WalkOut& O,
+                        hipStream_t s);
 // Per-positive weights from distance histograms (k_tables.hip)
 constexpr int kMaxHistWindow = 32;
 hipError_t launch_cocount_weights(const int32_t* hist, int64_t n, int window, const float* wd,

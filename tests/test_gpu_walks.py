@@ -122,3 +122,62 @@ def test_walk_triples_train_like_the_oracle():
     assert loss == pytest.approx(ref, rel=1e-5)
     assert_close(tr.S.cpu().numpy(), S, "S")
     assert_close(tr.T.cpu().numpy(), T, "T")
+
+
+# The group kernel's variants: pairs per seed at and around powers of two
+# (1 .. 64 keys per lane), with the nodes of window pairs in the small sort
+# and in the full one.
+EDGES = [
+    (1, 1, 1, True), (21, 3, 3, True), (16, 4, 4, True), (13, 5, 5, True), (43, 6, 3, True),
+    (64, 8, 5, True), (101, 7, 7, True), (1024, 4, 4, True),
+    (1, 1, 1, False), (1, 17, 2, False), (2, 9, 2, False), (1, 64, 32, False),
+    (16, 20, 6, False), (2048 // 64, 64, 1, False), (5, 64, 3, False), (15, 20, 8, False),
+    (1024, 2, 1, False),
+]
+
+
+@pytest.mark.parametrize("walks,steps,window,seed_only", EDGES)
+def test_walk_group_variants_match_the_oracle(walks, steps, window, seed_only):
+    say(f"walk group walks={walks} steps={steps} window={window} seed_only={seed_only}")
+    n = 150
+    off, nbr = _graph("random_with_sinks", n, seed=walks + steps)
+    ref = orc.sample_walks(off, nbr, n, walks, steps, window, seed_only, seed=5, first_seed=3,
+                           num_seeds=101)
+    got = P.sample_walks(dev(off, torch), dev(nbr, torch), n, walks, steps, window, seed_only,
+                         seed=5, first_seed=3, num_seeds=101)
+    for name, g, r in zip(("src", "dst", "cc", "hist"), got, ref):
+        assert np.array_equal(g.cpu().numpy(), r), name
+
+
+@pytest.mark.parametrize("n", [2 ** 27 - 1, 2 ** 27 + 3])
+def test_walks_on_ids_at_the_width_of_a_direct_key(n):
+    """Ids up to 27 bits fit a pair key beside the distance; larger ones are
+    taken by their places in the seed's sorted nodes.  Only the last 1000
+    nodes have neighbours."""
+    m, deg = 1000, 5
+    off = np.zeros(n + 1, np.int64)
+    off[n - m:] = np.arange(m + 1) * deg
+    nbr = np.random.default_rng(1).integers(n - m, n, m * deg).astype(np.int32)
+    first, count = n - 300, 300
+    say(f"walks n={n}")
+    ref = orc.sample_walks(off, nbr, n, 30, 6, 5, True, seed=2, first_seed=first,
+                           num_seeds=count)
+    got = P.sample_walks(dev(off, torch), dev(nbr, torch), n, 30, 6, 5, True, seed=2,
+                         first_seed=first, num_seeds=count)
+    for name, g, r in zip(("src", "dst", "cc", "hist"), got, ref):
+        assert np.array_equal(g.cpu().numpy(), r), name
+
+
+def test_triple_counts_are_scanned_over_many_ranges():
+    """5,000 seeds of a cycle: every seed has the same number of triples, so
+    the places of all of them are known."""
+    n, steps = 5000, 4
+    off, nbr = _graph("cycle", n)
+    src, dst, cc, hist = P.sample_walks(dev(off, torch), dev(nbr, torch), n, 2, steps, steps,
+                                        True, seed=1)
+    assert src.numel() == n * steps
+    want = np.repeat(np.arange(n), steps)
+    assert np.array_equal(src.cpu().numpy(), want)
+    ring = (np.arange(n)[:, None] + np.arange(1, steps + 1)) % n
+    assert np.array_equal(dst.cpu().numpy(), np.sort(ring, axis=1).reshape(-1))
+    assert (cc == 2).all() and (hist.sum(1) == 2).all()
