@@ -185,7 +185,16 @@ Layout make_layout(const huge_config* c) {
     L.lossp = take(sizeof(double) * (size_t)L.loss_blocks);
     if (sorted) {
         L.part = take(sizeof(double) * (size_t)caps.parts * (size_t)D);
-        L.dup = take(sizeof(float) * (size_t)(M * D));
+        // occurrences by slot, kept source rows and source gradients, in a region of at least D floats per occurrence (the size
+        // huge_workspace_bytes reports for a sorted handle holds that much)
+        const size_t rows = align_up(sizeof(float) * (size_t)(nb * D));
+        const size_t occ = align_up(sizeof(uint32_t) * (size_t)M);
+        const size_t need = kSlots * occ + 2 * rows;
+        const size_t slots = sizeof(float) * (size_t)(M * D);
+        size_t at = take(need > slots ? need : slots);
+        for (int s = 0; s < kSlots; ++s, at += occ) L.slot[s].occ = at;
+        L.srow = at;
+        L.sgrad = L.srow + rows;
     } else {
         L.gsrc = take(sizeof(float) * (size_t)(nb * D));
         L.coef = take(sizeof(float) * (size_t)(nb * (1 + K)));
@@ -423,7 +432,8 @@ huge_status stage_prepare(huge_handle* h, const int32_t* src, const int32_t* dst
         const ListCaps caps{L.cap_short, L.cap_piece, L.cap_comb, L.cap_part};
         HIP_TRY(launch_group(ctl, at<uint32_t>(h, SL.keys1), at<uint32_t>(h, SL.vals1), m,
                              h->cfg.num_nodes, hist, at<uint32_t>(h, SL.bstart),
-                             at<int32_t>(h, SL.info), at<uint4>(h, SL.shorts),
+                             at<int32_t>(h, SL.info), at<uint32_t>(h, SL.occ),
+                             at<uint4>(h, SL.shorts),
                              at<uint4>(h, SL.pieces), at<uint4>(h, SL.combs),
                              at<uint32_t>(h, SL.ccount), at<uint4>(h, SL.bcount), caps,
                              at<uint32_t>(h, SL.wstats), 1 << bits, h->key_bits,
@@ -482,17 +492,21 @@ huge_status apply_next(huge_handle* h, float lr, double* loss_out, hipStream_t s
             ev_start = h->prof_ev[(size_t)b.prof * kProfEvents + 6];
             ev_stop = h->prof_ev[(size_t)b.prof * kProfEvents + 7];
         }
+        const RepeatArgs rep{h->ws + L.srow, at<float>(h, L.sgrad)};
         HIP_TRY(launch_fused_step(t, ctl, a, at<int32_t>(h, SL.keys0) + 2, stride,
-                                  at<int32_t>(h, SL.info), at<float>(h, L.dup), lossp, &blocks,
-                                  ev_start, ev_stop, s));
+                                  at<int32_t>(h, SL.info), rep, lossp, &blocks, ev_start,
+                                  ev_stop, s));
         FinishArgs f;
         // an empty batch is not grouped: no record is read (f.m = 0)
         f.m = m;
+        f.info = at<int32_t>(h, SL.info);
+        f.occ = at<uint32_t>(h, SL.occ);
+        div_magic(stride, &f.div_mul, &f.div_shift);
         f.shorts = at<uint4>(h, SL.shorts);
         f.pieces = at<uint4>(h, SL.pieces);
         f.combs = at<uint4>(h, SL.combs);
         f.ccount = at<uint32_t>(h, SL.ccount);
-        f.dup = at<float>(h, L.dup);
+        f.rep = rep;
         f.part = at<double>(h, L.part);
         f.caps = ListCaps{L.cap_short, L.cap_piece, L.cap_comb, L.cap_part};
         f.lr = lr;

@@ -132,11 +132,13 @@ struct SlotLayout {
     size_t keys0 = 0;    // u32 [M] keys in occurrence order
     size_t keys1 = 0;    // u32 [M] keys grouped by their lowest digit
     size_t vals1 = 0;    // u32 [M] their occurrence indices
-    size_t info = 0;     // i32 [M]: -1, or the duplicate-buffer slot of an occurrence of a
-                         // repeated row (-1 between batches: the fused step resets it)
+    size_t info = 0;     // i32 [M]: -1, or the duplicate slot of an occurrence of a repeated
+                         // row; the fused step leaves its coefficient there (-1 between
+                         // batches: the finish kernel resets it)
     size_t tcount = 0;   // u32 [sort_tiles * kMaxBins] occurrences per tile and digit
     size_t tprefix = 0;  // u32 [sort_tiles * kMaxBins] the same summed over earlier tiles
     size_t bstart = 0;   // u32 [kMaxBins] first position of each bucket
+    size_t occ = 0;      // u32 [M] by duplicate slot: the occurrence
     // repeated-row records: short runs and pieces in one list each (a range
     // of the grouping appends at positions reserved from Control::nshort,
     // ::npiece); bucket b (first position s0, n items) writes its combine
@@ -163,7 +165,10 @@ struct Layout {
     size_t lossp = 0;      // double [loss_blocks]
     // sorted scatter
     size_t part = 0;     // f64 [cap_part * D] partial sums of the pieces of long runs
-    size_t dup = 0;      // f32 [M * D] per-occurrence contributions of repeated rows
+    size_t srow = 0;     // [max_batch * D] source rows (of the tables' type) of the positives
+                         // with a repeated context row
+    size_t sgrad = 0;    // f32 [max_batch * D] source gradients of those with a repeated
+                         // source row
     // atomic scatter
     size_t gsrc = 0;     // f32 [max_batch * D] source-row gradients
     size_t coef = 0;     // f32 [max_batch * (1 + K)]
@@ -345,25 +350,34 @@ hipError_t launch_radix_pass(Control* ctl, const uint32_t* keys_in, uint32_t* ke
 // whether a kernel was launched (an empty batch launches none).
 hipError_t launch_group(Control* ctl, const uint32_t* keys, const uint32_t* vals, int64_t m,
                         int64_t N, const uint32_t* hist, const uint32_t* bstart, int32_t* info,
-                        uint4* shorts, uint4* pieces, uint4* combs, uint32_t* ccount,
+                        uint32_t* occ, uint4* shorts, uint4* pieces, uint4* combs, uint32_t* ccount,
                         uint4* bcount, ListCaps caps, uint32_t* wstats, int bins, int key_bits,
                         hipEvent_t stop, bool* launched, hipStream_t s);
 // Negative k of positive i: neg[i * neg_stride + k].
+// Occurrences of repeated rows: what the fused step leaves and the finish
+// kernel sums.
+struct RepeatArgs {
+    void* srow;    // [positive] source rows, of the tables' element type
+    float* sgrad;  // [positive] source gradients
+};
 // start, stop (if not null): recorded at the kernel's start and completion.
 hipError_t launch_fused_step(const TableArgs& t, Control* ctl, const StepArgs& a,
-                             const int32_t* neg, uint32_t neg_stride, int32_t* info, float* dup,
-                             double* lossp, int64_t* blocks_out, hipEvent_t start,
+                             const int32_t* neg, uint32_t neg_stride, int32_t* info,
+                             const RepeatArgs& rep, double* lossp, int64_t* blocks_out, hipEvent_t start,
                              hipEvent_t stop, hipStream_t s);
 // After the fused step: the repeated rows (short runs, pieces, and rows
 // whose pieces are combined by the last piece to finish) and, with a loss
 // output, the loss sum (the fused step's partials in a fixed order).
 struct FinishArgs {
     int64_t m;               // occurrences of the batch (0: no records)
+    int32_t* info;           // the coefficients of repeated context occurrences
+    const uint32_t* occ;     // [m] by duplicate slot: the occurrence (below m)
+    uint32_t div_mul, div_shift;  // o / (2 + K) = umulhi(o, div_mul) >> div_shift, o < 2^31
     const uint4* shorts;     // its short-run records (Control::nshort of them)
     const uint4* pieces;     // its pieces (Control::npiece)
     const uint4* combs;
     uint32_t* ccount;
-    const float* dup;
+    RepeatArgs rep;
     double* part;
     ListCaps caps;
     float lr;
@@ -371,6 +385,16 @@ struct FinishArgs {
     int64_t loss_blocks;   // how many
     double* loss_out;      // or null: no loss
 };
+// Multiplier and shift that divide any x < 2^31 by d in [2, 2^31):
+// x / d = umulhi(x, mul) >> shift.  With 2^s >= d > 2^(s-1) and
+// mul = ceil(2^(31 + s) / d) < 2^32, mul d exceeds 2^(31 + s) by less than
+// d <= 2^s, which adds less than 1 / d to x / d.
+inline void div_magic(uint32_t d, uint32_t* mul, uint32_t* shift) {
+    uint32_t s = 1;
+    while (((uint64_t)1 << s) < d) ++s;
+    *mul = (uint32_t)((((uint64_t)1 << (31 + s)) + d - 1) / d);
+    *shift = s - 1;
+}
 // stop (if not null) is recorded by the kernel's own completion, not by a
 // separate queue packet.
 hipError_t launch_finish(const TableArgs& t, Control* ctl, const FinishArgs& f, hipEvent_t stop,

@@ -17,7 +17,7 @@
 //      gives every repeated row a contiguous range of duplicate-buffer slots
 //      (inside the bucket's own range of positions), writes the slot of each
 //      of its occurrences, in occurrence order, to info[o], and lists the
-//      repeated rows for the finish kernel.
+//      repeated rows, and by slot their occurrences, for the finish kernel.
 // All of them run beside the previous batch's fused step: 256-thread
 // workgroups whose waves hold few registers (one item per thread at a time,
 // loads issued in small groups) and work mostly in LDS.
@@ -370,7 +370,7 @@ hipError_t launch_radix_pass(Control* ctl, const uint32_t* keys_in, uint32_t* ke
 //           own region) for a run longer than kPiece;
 //   place:  the repeated items, taken in occurrence order (chunk by chunk,
 //           compacted, then ranked by one wave 64 at a time), receive their
-//           row's next slot: info[o] = slot.
+//           row's next slot: info[o] = slot, occ[slot] = o.
 // At the end the bucket's record counts go to bcount[b].  No step waits for
 // another workgroup; the only device-scope atomics reserve a range's places
 // in the batch's record lists.  Where a row's range lands
@@ -402,8 +402,8 @@ template <bool BM>
 __global__ __launch_bounds__(kBlock) HUGE_BESIDE_72 void k_group(
     Control* __restrict__ ctl, const uint32_t* __restrict__ keys,
     const uint32_t* __restrict__ vals, int64_t m, int64_t N, const uint32_t* __restrict__ hist,
-    const uint32_t* __restrict__ bstart, int32_t* __restrict__ info, uint4* __restrict__ shorts,
-    uint4* __restrict__ pieces, uint4* __restrict__ combs, uint32_t* __restrict__ ccount,
+    const uint32_t* __restrict__ bstart, int32_t* __restrict__ info,
+    uint32_t* __restrict__ occ, uint4* __restrict__ shorts, uint4* __restrict__ pieces, uint4* __restrict__ combs, uint32_t* __restrict__ ccount,
     uint4* __restrict__ bcount, ListCaps caps, uint32_t* __restrict__ wstats, int bins, int shift,
     int sub_bits) {
     constexpr int kBitWords = (1 << kBitmapBits) / 32;           // words of one bitmap
@@ -807,10 +807,13 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE_72 void k_group(
                         const uint32_t pos = s_rep[kk++];
                         const uint32_t e = c0 + (uint32_t)(tid * kGroupItems + r);
                         const uint32_t o = vals_cached ? s_cval[e] : vals[s0 + e];
-                        if ((int64_t)pos >= s0 && (int64_t)pos < s0 + (int64_t)n && (int64_t)o < m)
+                        if ((int64_t)pos >= s0 && (int64_t)pos < s0 + (int64_t)n &&
+                            (int64_t)o < m) {
                             info[o] = (int32_t)pos;
-                        else
+                            occ[pos] = o;
+                        } else {
                             HUGE_FAIL(kSiteGroupPlace);
+                        }
                     }
                 }
                 __syncthreads();  // s_rep is reused by the next chunk
@@ -843,7 +846,7 @@ finished:
 
 hipError_t launch_group(Control* ctl, const uint32_t* keys, const uint32_t* vals, int64_t m,
                         int64_t N, const uint32_t* hist, const uint32_t* bstart, int32_t* info,
-                        uint4* shorts, uint4* pieces, uint4* combs, uint32_t* ccount,
+                        uint32_t* occ, uint4* shorts, uint4* pieces, uint4* combs, uint32_t* ccount,
                         uint4* bcount, ListCaps caps, uint32_t* wstats, int bins, int key_bits,
                         hipEvent_t stop, bool* launched, hipStream_t s) {
     *launched = false;
@@ -866,12 +869,12 @@ hipError_t launch_group(Control* ctl, const uint32_t* keys, const uint32_t* vals
     if (bm) {
         hipExtLaunchKernelGGL(k_group<true>, dim3((unsigned)bins), dim3(kBlock),
                               group_lds_words<true>() * sizeof(uint32_t), s, nullptr, stop, 0,
-                              ctl, keys, vals, m, N, hist, bstart, info, shorts, pieces, combs,
+                              ctl, keys, vals, m, N, hist, bstart, info, occ, shorts, pieces, combs,
                               ccount, bcount, caps, wstats, bins, shift, sub_bits);
     } else {
         hipExtLaunchKernelGGL(k_group<false>, dim3((unsigned)bins), dim3(kBlock),
                               group_lds_words<false>() * sizeof(uint32_t), s, nullptr, stop, 0,
-                              ctl, keys, vals, m, N, hist, bstart, info, shorts, pieces, combs,
+                              ctl, keys, vals, m, N, hist, bstart, info, occ, shorts, pieces, combs,
                               ccount, bcount, caps, wstats, bins, shift, sub_bits);
     }
     const hipError_t e = hipGetLastError();

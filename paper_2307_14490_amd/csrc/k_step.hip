@@ -4,9 +4,9 @@
 //
 // Rows that occur once in the batch are rewritten in place by the thread
 // group that read them -- no other group reads them.  A row that occurs
-// several times is left untouched here: each occurrence stores its
-// contribution in the slot the grouping gave it (a row's slots are
-// consecutive, in occurrence order), and the finish kernel sums them in that
+// several times is left untouched here: the finish kernel forms the
+// contributions of its occurrences (listed by the grouping, in occurrence
+// order) from the positives' kept rows and coefficients, sums them in that
 // order and updates the row once, so every read sees pre-step values.
 #include "common.hpp"
 #include "device.hpp"
@@ -40,16 +40,24 @@ __device__ __forceinline__ void block_loss(float loss, double* __restrict__ out)
 // FULL: K == NB, the negatives are one block of compile-time size.
 // Negative k of positive i is neg[i * neg_stride + k] (the sort keys in
 // occurrence order, whose slots 2.. are the negatives' row ids).  info[o] is
-// -1 for a row occurring once, else the occurrence's duplicate-buffer slot;
-// the kernel sets every entry it finds >= 0 back to -1 once it has read it,
-// so that the array is all -1 again for the next batch in this slot (the
-// grouping writes only the repeated occurrences).
+// -1 for a row occurring once, else the occurrence's duplicate slot.
+// A contribution to a repeated context row is h S[u], one to a repeated source
+// row the source gradient.  A positive with any repeated context row keeps its
+// source row once in srow[positive], one with a repeated source row its
+// gradient in sgrad[positive]; the coefficient of a repeated context
+// occurrence o replaces its slot in info[o].  The finish kernel reads it there
+// and sets the entry (a repeated source occurrence's too) back to -1, so that
+// the array is all -1 again for the next batch of this grouping slot.  Writing
+// each contribution itself, a row per repeated occurrence, moved those rows
+// through HBM twice.  131,072 positives, K = 31, 1e7 nodes (1.4M repeated
+// occurrences): fused 900 -> 780 us, finish 356 -> 305; 100,003 positives of a
+// power-law graph, K = 20, D = 256: 800 -> 490 and 565 -> 468.
 template <int G, int NB, bool FULL, typename IO, typename DIO>
 __global__ __launch_bounds__(kBlock) void k_fused_step(TableArgs t, Control* __restrict__ ctl,
                                                        StepArgs a, const int32_t* __restrict__ neg,
                                                        uint32_t neg_stride,
                                                        int32_t* __restrict__ info,
-                                                       float* __restrict__ dup,
+                                                       RepeatArgs rep,
                                                        double* __restrict__ lossp) {
     using E = typename IO::Elem;
     using Reg = typename IO::Reg;
@@ -78,18 +86,12 @@ __global__ __launch_bounds__(kBlock) void k_fused_step(TableArgs t, Control* __r
     const int lane = threadIdx.x % G;
     const int64_t i = (int64_t)blockIdx.x * PPB + grp;
     const int K = FULL ? NB : t.K;
-    if (ctl->step_bad) {  // a no-op step: only the slots the grouping may have set
-        if (i < a.n && lane == 0) {
-            const uint32_t o = (uint32_t)i * (uint32_t)(2 + K);
-            for (int q = 0; q < 2 + K; ++q)
-                if (info[o + q] >= 0) info[o + q] = -1;
-        }
-        return;
-    }
+    const uint32_t step_bad = ctl->step_bad;  // looked at once the index loads are issued
     const int32_t D = t.D;
     const float lr = a.lr;
     E* __restrict__ S = static_cast<E*>(t.S);
     E* __restrict__ T = static_cast<E*>(t.T);
+    E* __restrict__ srow = static_cast<E*>(rep.srow);
     float loss = 0.f;
 
     // Every index of the positive is loaded before any of them is used, so
@@ -120,13 +122,15 @@ __global__ __launch_bounds__(kBlock) void k_fused_step(TableArgs t, Control* __r
                 ik[j] = info[o + 2 + j];
             }
         }
-        if (lane == 0) {
-            if (info_s >= 0) info[o] = -1;
-            if (info_d >= 0) info[o + 1] = -1;
-#pragma unroll
-            for (int j = 0; j < NB; ++j)
-                if (j < cnt && ik[j] >= 0) info[o + 2 + j] = -1;
+    }
+    if (step_bad) {  // a no-op step: only the slots the grouping may have set
+        if (active && lane == 0) {
+            for (int q = 0; q < 2 + K; ++q)
+                if (info[o + q] >= 0) info[o + q] = -1;
         }
+        return;
+    }
+    if (active) {
         if (u < 0 || (int64_t)u >= t.N || v < 0 || (int64_t)v >= t.N) {
             if (lane == 0) raise_internal(ctl, kSiteStepIds);
             active = false;
@@ -157,11 +161,6 @@ __global__ __launch_bounds__(kBlock) void k_fused_step(TableArgs t, Control* __r
 #pragma unroll
                 for (int q = 0; q < C; ++q) nv[q] = axpy4(-(lr * g), s[q], IO::chunk(t0, q));
                 IO::store(T, v, D, lane, nv);
-            } else {
-                float4 cv[C];
-#pragma unroll
-                for (int q = 0; q < C; ++q) cv[q] = scale4(g, s[q]);
-                DIO::store(dup, info_d, D, lane, cv);
             }
         };
         if constexpr (!kLanePos) {
@@ -173,6 +172,11 @@ __global__ __launch_bounds__(kBlock) void k_fused_step(TableArgs t, Control* __r
         }
 
         // negatives, NB rows in flight at a time
+        int32_t slot = info_d;  // >= 0: a context row so far is repeated
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+            if (j < cnt) slot = slot > ik[j] ? slot : ik[j];
+        bool kept = false;  // the source row is in srow
         int kb = 0;
         while (true) {
             float y[NB];
@@ -229,12 +233,34 @@ __global__ __launch_bounds__(kBlock) void k_fused_step(TableArgs t, Control* __r
                         for (int q = 0; q < C; ++q)
                             nv[q] = axpy4(-(lr * h[j]), s[q], IO::chunk(tk[j], q));
                         IO::store(T, mk[j], D, lane, nv);
-                    } else {
-                        float4 cv[C];
-#pragma unroll
-                        for (int q = 0; q < C; ++q) cv[q] = scale4(h[j], s[q]);
-                        DIO::store(dup, ik[j], D, lane, cv);
                     }
+                }
+            }
+            if (slot >= 0) {
+                // exact: the row as it was read; streamed: a plain store cost the
+                // pipelined step 1.2% (the finish kernel is the next to read it)
+                if (!kept) IO::store_stream(srow, i32, D, lane, s);
+                kept = true;
+                // the coefficients of the block's repeated rows (and the
+                // destination's): lane q stores that of context row kb + q
+                if constexpr (G > NB) {
+                    float w = g;
+                    int32_t own = kb == 0 ? info_d : -1;
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) {
+                        if (lane == j + 1) {
+                            w = h[j];
+                            own = j < cnt ? ik[j] : -1;
+                        }
+                    }
+                    if (lane <= NB && own >= 0)
+                        info[o + 1 + (uint32_t)(kb + lane)] = __float_as_int(w);
+                } else if (lane == 0) {
+                    if (kb == 0 && info_d >= 0) info[o + 1] = __float_as_int(g);
+#pragma unroll
+                    for (int j = 0; j < NB; ++j)
+                        if (j < cnt && ik[j] >= 0)
+                            info[o + 2 + (uint32_t)(kb + j)] = __float_as_int(h[j]);
                 }
             }
             kb += NB;
@@ -247,14 +273,14 @@ __global__ __launch_bounds__(kBlock) void k_fused_step(TableArgs t, Control* __r
                     ik[j] = info[o + 2 + (uint32_t)(kb + j)];
                 }
             }
-            if (lane == 0) {
+            slot = -1;
 #pragma unroll
-                for (int j = 0; j < NB; ++j)
-                    if (j < cnt && ik[j] >= 0) info[o + 2 + (uint32_t)(kb + j)] = -1;
+            for (int j = 0; j < NB; ++j) {
+                if (j < cnt) {
+                    slot = slot > ik[j] ? slot : ik[j];
+                    IO::load_packed(tk[j], T, mk[j], D, lane);
+                }
             }
-#pragma unroll
-            for (int j = 0; j < NB; ++j)
-                if (j < cnt) IO::load_packed(tk[j], T, mk[j], D, lane);
         }
 
         // source row
@@ -264,7 +290,7 @@ __global__ __launch_bounds__(kBlock) void k_fused_step(TableArgs t, Control* __r
             for (int q = 0; q < C; ++q) nv[q] = axpy4(-lr, dS[q], s[q]);
             IO::store(S, u, D, lane, nv);
         } else {
-            DIO::store(dup, info_s, D, lane, dS);
+            DIO::store(rep.sgrad, i32, D, lane, dS);
         }
         // with lane coefficients every lane holds its own loss terms
         if (kLaneCoefs || lane == 0) loss = c * lsum;
@@ -283,8 +309,8 @@ static int64_t fused_step_blocks(const TableArgs& t, int64_t n) {
 }
 
 hipError_t launch_fused_step(const TableArgs& t, Control* ctl, const StepArgs& a,
-                             const int32_t* neg, uint32_t neg_stride, int32_t* info, float* dup,
-                             double* lossp, int64_t* blocks_out, hipEvent_t start,
+                             const int32_t* neg, uint32_t neg_stride, int32_t* info,
+                             const RepeatArgs& rep, double* lossp, int64_t* blocks_out, hipEvent_t start,
                              hipEvent_t stop, hipStream_t s) {
     const int64_t blocks = fused_step_blocks(t, a.n);
     *blocks_out = blocks;
@@ -296,7 +322,7 @@ hipError_t launch_fused_step(const TableArgs& t, Control* ctl, const StepArgs& a
                     hipExtLaunchKernelGGL(
                         (k_fused_step<G_, NB_, F_, PairIO<G_, U_, bf16_t>, PairIO<G_, U_, float>>),
                         dim3((unsigned)blocks), dim3(kBlock), 0, s, start, stop, 0, t, ctl, a,
-                        neg, neg_stride, info, dup, lossp);
+                        neg, neg_stride, info, rep, lossp);
                 });
             });
         });
@@ -308,7 +334,7 @@ hipError_t launch_fused_step(const TableArgs& t, Control* ctl, const StepArgs& a
                         hipExtLaunchKernelGGL(
                             (k_fused_step<G_, NB_, F_, RowIO<G_, C_, E_>, RowIO<G_, C_>>),
                             dim3((unsigned)blocks), dim3(kBlock), 0, s, start, stop, 0, t, ctl,
-                            a, neg, neg_stride, info, dup, lossp);
+                            a, neg, neg_stride, info, rep, lossp);
                     });
                 });
             });
@@ -409,8 +435,8 @@ hipError_t launch_probe(const TableArgs& t, Control* ctl, const int32_t* src, co
 }
 
 // ---------------------------------------------------------------------------
-// Repeated rows.  The contributions of a row, at duplicate-buffer slots
-// start .. start + len - 1, are added in that order, in double (a hub row can
+// Repeated rows.  The contributions of a row, those of the occurrences
+// occ[start .. start + len), are added in that order, in double (a hub row can
 // collect tens of thousands of terms), and the row is rounded once to its
 // element type: row = round(row - lr * sum) (for bf16 tables through fp32).
 // ---------------------------------------------------------------------------
@@ -450,32 +476,51 @@ struct PartIO {
     }
 };
 
-template <int G, int C>
-__device__ __forceinline__ void sum_rows(double4_ (&acc)[C], const float* __restrict__ rows,
-                                         int64_t start, int64_t len, int32_t D, int lane) {
-    using IO = RowIO<G, C>;
+// The first kRefBlock occurrences of a run, or the next ones.
+constexpr int kRefBlock = 4;
+
+__device__ __forceinline__ void load_occ(uint32_t (&f)[kRefBlock],
+                                         const uint32_t* __restrict__ occ, uint32_t at,
+                                         uint32_t len) {
+#pragma unroll
+    for (int j = 0; j < kRefBlock; ++j) f[j] = at + j < len ? occ[at + j] : 0u;
+}
+
+// Sum of the contributions of the occurrences occ[0 .. len) in that order, f
+// holding the first ones: occurrence o of positive i = o / (2 + K) is
+// rows[i] (grad) or the coefficient in info[o] times it, and the entry is
+// set back to -1.  Each product is rounded to
+// float, as a contribution is, then added in double.
+template <int G, int C, typename R>
+__device__ __forceinline__ void sum_occ(double4_ (&acc)[C], const FinishArgs& a,
+                                        const R* __restrict__ rows, bool grad,
+                                        uint32_t (&f)[kRefBlock],
+                                        const uint32_t* __restrict__ occ, uint32_t len,
+                                        int32_t D, int lane) {
+    using IO = RowIO<G, C, R>;
 #pragma unroll
     for (int q = 0; q < C; ++q) acc[q] = double4_{0.0, 0.0, 0.0, 0.0};
-    int64_t r = 0;
-    for (; r + 4 <= len; r += 4) {
-        float4 b0[C], b1[C], b2[C], b3[C];
-        IO::load(b0, rows, start + r, D, lane);
-        IO::load(b1, rows, start + r + 1, D, lane);
-        IO::load(b2, rows, start + r + 2, D, lane);
-        IO::load(b3, rows, start + r + 3, D, lane);
+    for (uint32_t r = 0; r < len; r += kRefBlock) {
+        float4 b[kRefBlock][C];
+        float h[kRefBlock];
 #pragma unroll
-        for (int q = 0; q < C; ++q) {
-            addd(acc[q], b0[q]);
-            addd(acc[q], b1[q]);
-            addd(acc[q], b2[q]);
-            addd(acc[q], b3[q]);
+        for (int j = 0; j < kRefBlock; ++j) {
+            const uint32_t i = __umulhi(f[j], a.div_mul) >> a.div_shift;
+            h[j] = 1.0f;
+            if (r + j < len) {
+                IO::load(b[j], rows, i, D, lane);
+                if (!grad) h[j] = __int_as_float(a.info[f[j]]);
+                if (lane == 0) a.info[f[j]] = -1;
+            }
         }
-    }
-    for (; r < len; ++r) {
-        float4 b[C];
-        IO::load(b, rows, start + r, D, lane);
+        if (r + kRefBlock < len) load_occ(f, occ, r + kRefBlock, len);
 #pragma unroll
-        for (int q = 0; q < C; ++q) addd(acc[q], b[q]);
+        for (int j = 0; j < kRefBlock; ++j) {
+            if (r + j < len) {
+#pragma unroll
+                for (int q = 0; q < C; ++q) addd(acc[q], scale4(h[j], b[j][q]));
+            }
+        }
     }
 }
 
@@ -546,43 +591,24 @@ __device__ __forceinline__ void coop_total(double4_ (&acc)[C], const double* s_p
     }
 }
 
-// Cooperative sum of `len` rows starting at row `start` of `rows` (fp32
-// contributions or fp64 partials): the PPB groups of the workgroup each sum
-// a fixed contiguous part, and group 0 receives the parts' sum in group
-// order (the result does not depend on scheduling).  Every thread of the
-// workgroup calls it; it synchronises twice.
-template <int G, int C, typename Row>
-__device__ __forceinline__ void coop_sum(double4_ (&acc)[C], const Row* __restrict__ rows,
-                                         int64_t start, uint32_t len, int32_t D, int grp,
-                                         int lane, double* s_part) {
+// Cooperative sum over `len` items -- fn(b0, cnt) leaves that of cnt of them
+// from item b0 in acc: the PPB groups of the workgroup each take a fixed
+// contiguous part, and group 0 receives the parts' sum in group order (the
+// result does not depend on scheduling).  Every thread of the workgroup calls
+// it; it synchronises twice.
+template <int G, int C, typename Fn>
+__device__ __forceinline__ void coop_sum(double4_ (&acc)[C], uint32_t len, int32_t D, int grp,
+                                         int lane, double* s_part, Fn fn) {
     constexpr int PPB = kBlock / G;
     const uint32_t part_len = (len + PPB - 1) / PPB;
     const uint32_t b0 = (uint32_t)grp * part_len;
     const uint32_t b1 = b0 + part_len < len ? b0 + part_len : len;
-    const int64_t cnt = b1 > b0 ? (int64_t)(b1 - b0) : 0;
-    if constexpr (sizeof(Row) == sizeof(float)) {
-        sum_rows<G, C>(acc, rows, start + b0, cnt, D, lane);
-    } else {
-#pragma unroll
-        for (int q = 0; q < C; ++q) acc[q] = double4_{0.0, 0.0, 0.0, 0.0};
-        for (int64_t r = 0; r < cnt; ++r) {
-            double4_ x[C];
-            PartIO<G, C>::load(x, rows, start + b0 + r, D, lane);
-#pragma unroll
-            for (int q = 0; q < C; ++q) {
-                acc[q].x += x[q].x;
-                acc[q].y += x[q].y;
-                acc[q].z += x[q].z;
-                acc[q].w += x[q].w;
-            }
-        }
-    }
+    fn(b0, b1 > b0 ? b1 - b0 : 0u);
     coop_store<G, C>(s_part, grp, lane, D, acc);
     __syncthreads();
     if (grp == 0) coop_total<G, C>(acc, s_part, lane, D);
     __syncthreads();
 }
-
 // Fixed-order sum of one double per thread over the workgroup (a tree in
 // LDS); every thread receives the sum.  Synchronises.
 __device__ __forceinline__ double block_sum_fixed(double v, double* s_red) {
@@ -605,7 +631,8 @@ __device__ __forceinline__ double block_sum_fixed(double v, double* s_red) {
 //           to pass partial sums between them, measured slower);
 //   short runs ({start, len <= kShortRun, key}): one thread group each
 //           loads the row with its contributions, sums them in occurrence
-//           order and updates the row;
+//           order and updates the row; the next record and its first
+//           occurrences are loaded before the current one's rows are used;
 //   pieces ({start, len <= kPiece, key, comb}): the whole workgroup sums
 //           them; a whole run (comb = 0) updates its row; a piece of a
 //           longer run stores its sum as partial z of its combine record
@@ -616,59 +643,52 @@ __device__ __forceinline__ double block_sum_fixed(double v, double* s_red) {
 //           updates the row once.
 // The records come in one list per kind, their counts in Control (the
 // grouping of the batch appended them).
-// Exclusive sum of one value per thread over the workgroup; *total receives
-// the sum.  Synchronises; s_tmp (kBlock / 64 words) may be reused after the
-// next barrier.
-__device__ __forceinline__ uint32_t block_excl_sum(uint32_t v, uint32_t* s_tmp, uint32_t* total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t incl = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t t = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += t;
+// A step that turned out bad while the fused step ran (a batch changed after
+// it was prepared): only the entries of info that hold coefficients or slots
+// are reset.  The records may be those of a grouping that failed, so each is
+// used only within the batch.
+__device__ __forceinline__ void reset_info(const FinishArgs& f, uint32_t ns, uint32_t np) {
+    const uint32_t step = (gridDim.x - 1u) * kBlock;
+    for (uint32_t r = (blockIdx.x - 1u) * kBlock + threadIdx.x; r < ns + np; r += step) {
+        const uint4 rec = r < ns ? f.shorts[r] : f.pieces[r - ns];
+        if (rec.y > kPiece || (int64_t)rec.x + rec.y > f.m) continue;
+        for (uint32_t j = 0; j < rec.y; ++j) {
+            const uint32_t o = f.occ[rec.x + j];
+            if ((int64_t)o < f.m) f.info[o] = -1;
+        }
     }
-    if (lane == 63) s_tmp[wave] = incl;
-    __syncthreads();
-    uint32_t add = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < kBlock / 64; ++w) {
-        const uint32_t x = s_tmp[w];
-        if (w < wave) add += x;
-        all += x;
-    }
-    *total = all;
-    return add + incl - v;
 }
-
-// The bucket of record r: the largest b < bins with prefix[b] <= r.
-__device__ __forceinline__ int record_bucket(const uint32_t* prefix, int bins, uint32_t r) {
-    int lo = 0, hi = bins - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (prefix[mid] <= r) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-
 
 template <int G, int C, typename E>
-__global__ __launch_bounds__(kBlock) void k_finish(TableArgs t, Control* __restrict__ ctl,
+__global__ __launch_bounds__(kBlock, C > 1 ? 1 : sizeof(E) == 4 ? 6 : 5) void k_finish(TableArgs t, Control* __restrict__ ctl,
                                                    FinishArgs f) {
     constexpr int PPB = kBlock / G;
     __shared__ double s_part[1024 * C];  // PPB x D doubles: D <= 4 G C
     __shared__ double s_red[kBlock];
     __shared__ uint32_t s_flag;
-    if (ctl->step_bad) {
-        if (blockIdx.x == 0 && threadIdx.x == 0 && f.loss_out != nullptr)
-            *f.loss_out = __builtin_nan("");
-        return;
-    }
     const int grp = threadIdx.x / G;
     const int lane = threadIdx.x % G;
     const int32_t D = t.D;
+    // a thread group's first record, loaded beside the control block (used
+    // only if the batch has it)
+    const uint32_t wg = blockIdx.x - 1u;
+    uint32_t r = wg * PPB + grp;
+    uint4 rec = make_uint4(0u, 0u, 0u, 0u);
+    if (blockIdx.x > 0u && f.m > 0 && r < f.caps.shorts) rec = f.shorts[r];
+    const uint32_t step_bad = ctl->step_bad;
+    uint32_t ns = ctl->nshort, np = ctl->npiece;
+    if (step_bad) {
+        if (blockIdx.x == 0) {
+            if (threadIdx.x == 0 && f.loss_out != nullptr) *f.loss_out = __builtin_nan("");
+        } else if (f.m > 0) {
+            reset_info(f, ns < f.caps.shorts ? ns : f.caps.shorts,
+                       np < f.caps.pieces ? np : f.caps.pieces);
+        }
+        return;
+    }
 
     // Workgroup 0 (dispatched first) sums the loss and nothing else: thread t
-    // adds partial pairs t, t + kBlock, ... in that order (16-byte loads, 32
+    // adds partial pairs t, t + kBlock, ... in that order (16-byte loads, 8
     // in flight), then the threads' sums meet in a fixed tree: the same
     // double on every run.
     if (blockIdx.x == 0) {
@@ -677,12 +697,12 @@ __global__ __launch_bounds__(kBlock) void k_finish(TableArgs t, Control* __restr
         const int64_t n2 = f.loss_blocks / 2;
         double acc = 0.0;
         int64_t j = threadIdx.x;
-        for (; j + 31 * kBlock < n2; j += 32 * kBlock) {
-            double2 v[32];
+        for (; j + 7 * kBlock < n2; j += 8 * kBlock) {
+            double2 v[8];
 #pragma unroll
-            for (int q = 0; q < 32; ++q) v[q] = p2[j + q * kBlock];
+            for (int q = 0; q < 8; ++q) v[q] = p2[j + q * kBlock];
 #pragma unroll
-            for (int q = 0; q < 32; ++q) {
+            for (int q = 0; q < 8; ++q) {
                 acc += v[q].x;
                 acc += v[q].y;
             }
@@ -699,43 +719,72 @@ __global__ __launch_bounds__(kBlock) void k_finish(TableArgs t, Control* __restr
     }
     // the other workgroups take the records
     if (f.m == 0) return;
-    uint32_t ns = ctl->nshort, np = ctl->npiece;
     if (ns > f.caps.shorts || np > f.caps.pieces) {  // cannot happen: the grouping checks
         if (threadIdx.x == 0) raise_internal(ctl, kSiteFinishComb);
         ns = ns < f.caps.shorts ? ns : f.caps.shorts;
         np = np < f.caps.pieces ? np : f.caps.pieces;
     }
     const uint32_t rec_groups = gridDim.x - 1u;
-    const uint32_t wg = blockIdx.x - 1u;
-    for (uint32_t r = wg * PPB + grp; r < ns; r += rec_groups * PPB) {
-        const uint4 rec = f.shorts[r];
-        // a record is used only if it lies inside this batch (the grouping
-        // writes only such records; the check keeps a broken invariant from
-        // reaching memory outside the buffers)
-        if (rec.y == 0u || rec.y > kShortRun || (int64_t)rec.x + rec.y > f.m ||
-            (int64_t)rec.z >= 2 * t.N) {
-            if (lane == 0) raise_internal(ctl, kSiteFinishComb);
-            continue;
+    const E* srow = static_cast<const E*>(f.rep.srow);
+    // the contributions of the occurrences occ[0 .. len), of which e holds the
+    // first: gradients for a source row's key, scaled source rows for a
+    // context row's
+    auto sum_run = [&](double4_ (&acc)[C], uint32_t key, uint32_t (&e)[kRefBlock],
+                       const uint32_t* occ, uint32_t len) {
+        const bool grad = (int64_t)key >= t.N;
+        if constexpr (sizeof(E) == sizeof(float)) {
+            sum_occ<G, C>(acc, f, grad ? f.rep.sgrad : srow, grad, e, occ, len, D, lane);
+        } else {
+            if (grad)
+                sum_occ<G, C>(acc, f, f.rep.sgrad, true, e, occ, len, D, lane);
+            else
+                sum_occ<G, C>(acc, f, srow, false, e, occ, len, D, lane);
         }
-        // the row's values are loaded with the contributions
-        int64_t row;
-        E* base = key_row<E>(t, rec.z, &row);
-        float4 cur[C];
-        RowIO<G, C, E>::load(cur, base, row, D, lane);
-        double4_ acc[C];
-        sum_rows<G, C>(acc, f.dup, rec.x, rec.y, D, lane);
-        sgd_row<C>(cur, acc, f.lr);
-        RowIO<G, C, E>::store(base, row, D, lane, cur);
+    };
+    // a record is used only if it lies inside this batch (the grouping writes
+    // only such records; the check keeps a broken invariant from reaching
+    // memory outside the buffers)
+    auto usable = [&](const uint4& rec, uint32_t most) {
+        return rec.y != 0u && rec.y <= most && (int64_t)rec.x + rec.y <= f.m &&
+               (int64_t)rec.z < 2 * t.N;
+    };
+    const uint32_t stride = rec_groups * PPB;
+    if (r >= ns) rec = make_uint4(0u, 0u, 0u, 0u);
+    uint32_t e[kRefBlock];
+    load_occ(e, f.occ + rec.x, 0u, usable(rec, kShortRun) ? rec.y : 0u);
+    for (; r < ns; r += stride) {
+        const uint4 nrec = ns - r > stride ? f.shorts[r + stride] : make_uint4(0u, 0u, 0u, 0u);
+        const bool ok = usable(rec, kShortRun);
+        if (!ok && lane == 0) raise_internal(ctl, kSiteFinishComb);
+        if (ok) {
+            // the row's values are loaded with the contributions
+            int64_t row;
+            E* base = key_row<E>(t, rec.z, &row);
+            float4 cur[C];
+            RowIO<G, C, E>::load(cur, base, row, D, lane);
+            double4_ acc[C];
+            sum_run(acc, rec.z, e, f.occ + rec.x, rec.y);
+            load_occ(e, f.occ + nrec.x, 0u, usable(nrec, kShortRun) ? nrec.y : 0u);
+            sgd_row<C>(cur, acc, f.lr);
+            RowIO<G, C, E>::store(base, row, D, lane, cur);
+        } else {
+            load_occ(e, f.occ + nrec.x, 0u, usable(nrec, kShortRun) ? nrec.y : 0u);
+        }
+        rec = nrec;
     }
-    for (uint32_t r = wg; r < np; r += rec_groups) {
-        const uint4 rec = f.pieces[r];  // the same for every thread
-        if (rec.y == 0u || rec.y > kPiece || (int64_t)rec.x + rec.y > f.m ||
-            (int64_t)rec.z >= 2 * t.N) {  // uniform; cannot happen
+    for (uint32_t p = wg; p < np; p += rec_groups) {
+        const uint4 rec = f.pieces[p];  // the same for every thread
+        if (!usable(rec, kPiece)) {  // uniform; cannot happen
             if (threadIdx.x == 0) raise_internal(ctl, kSiteFinishComb);
             continue;
         }
         double4_ acc[C];
-        coop_sum<G, C>(acc, f.dup, rec.x, rec.y, D, grp, lane, s_part);
+        coop_sum<G, C>(acc, rec.y, D, grp, lane, s_part, [&](uint32_t b0, uint32_t cnt) {
+            uint32_t e[kRefBlock];
+            const uint32_t* occ = f.occ + rec.x + b0;
+            load_occ(e, occ, 0u, cnt);
+            sum_run(acc, rec.z, e, occ, cnt);
+        });
         if (rec.w == 0u) {
             if (grp == 0) apply_row<G, C, E>(t, rec.z, acc, f.lr, lane);
             continue;
@@ -758,8 +807,21 @@ __global__ __launch_bounds__(kBlock) void k_finish(TableArgs t, Control* __restr
         __syncthreads();
         if (s_flag) {  // uniform: the last piece of the row
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            coop_sum<G, C>(acc, static_cast<const double*>(f.part), cb.y, cb.z, D, grp, lane,
-                           s_part);
+            coop_sum<G, C>(acc, cb.z, D, grp, lane, s_part, [&](uint32_t b0, uint32_t cnt) {
+#pragma unroll
+                for (int q = 0; q < C; ++q) acc[q] = double4_{0.0, 0.0, 0.0, 0.0};
+                for (uint32_t z = 0; z < cnt; ++z) {
+                    double4_ x[C];
+                    PartIO<G, C>::load(x, f.part, (int64_t)cb.y + b0 + z, D, lane);
+#pragma unroll
+                    for (int q = 0; q < C; ++q) {
+                        acc[q].x += x[q].x;
+                        acc[q].y += x[q].y;
+                        acc[q].z += x[q].z;
+                        acc[q].w += x[q].w;
+                    }
+                }
+            });
             if (grp == 0) apply_row<G, C, E>(t, cb.x, acc, f.lr, lane);
         }
     }

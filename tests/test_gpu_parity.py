@@ -587,3 +587,35 @@ def test_batches_of_the_wrong_type_are_refused():
     with pytest.raises(TypeError, match="counts"):
         tr.step(dst, dst, cc.double(), 0, 0.1)
     assert tr.check() == 0
+
+
+@pytest.mark.parametrize("D,K,dtype", [(32, 5, "f32"), (128, 12, "f32"), (64, 9, "bf16")])
+def test_a_batch_changed_after_its_preparation_leaves_the_next_ones_intact(D, K, dtype):
+    """Every row repeats (40 nodes).  A source id set out of range between
+    the two halves is reported; the occurrences' entries it leaves behind
+    must not reach the batches that use the same grouping slot later."""
+    N, n, lr = 40, 500, 0.02
+    rng = np.random.default_rng(D)
+    say(f"changed batch D={D} K={K} {dtype}")
+    tr = P.Trainer(N, D, K, n, seed=6, dtype=dtype)
+    d = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    src, dst = (rng.integers(0, N, n).astype(np.int32) for _ in range(2))
+    cc = rng.integers(1, 4, n).astype(np.int32)
+    ds = d(src)
+    tr.prepare(ds, d(dst), d(cc), 0)
+    torch.cuda.synchronize()
+    ds[n // 2] = N + 3
+    assert np.isnan(tr.train_prepared(lr).item())
+    assert tr.check() != 0
+    for step in range(1, 6):  # every grouping slot once more
+        src, dst = (rng.integers(0, N, n).astype(np.int32) for _ in range(2))
+        before = [t.float().cpu().numpy().copy() for t in (tr.S, tr.T)]
+        tr.step(d(src), d(dst), d(cc), step * n, lr)
+        assert tr.check() == 0
+        neg = orc.sample_negatives(6, step * n, n, K, N)
+        ref = [b.copy() for b in before]
+        orc.step_dense(ref[0], ref[1], src, dst, cc, neg, lr)
+        for got, want in zip((tr.S, tr.T), ref):
+            got = got.float().cpu().numpy().astype(np.float64)
+            tol = 1e-6 + (2.0 ** -7 if dtype == "bf16" else 1e-5) * np.abs(want)
+            assert np.all(np.abs(got - want) <= tol), step
