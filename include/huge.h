@@ -412,12 +412,13 @@ huge_status huge_eval_summary_static(const float* d_dist, int64_t n_edge, int64_
    2^-22 of it) and the products hi.hi + hi.lo + lo.hi summed in fp32 (about
    2^-21 of each term, well inside the search's fp32 distance bound); wider
    rows in fp32.  1 <= k <= 32;
-   dim <= 512.  Queries are processed in passes of up to
-   128 (dim <= 128), 64 (dim <= 256) or 32 over the table.  For dim <= 128
-   a pass is a series of threshold scans: strided samples of the row tiles,
-   each 32 times denser than the one before, then every tile; a sample's
-   k-th distance bounds the next scan's candidates per query, which are
-   sorted between scans.  Should more than 8192 rows of the last scan fall
+   dim <= 512.  Queries are processed in passes of up to 128 over the table.
+   A pass is a series of threshold scans: strided samples of the row tiles,
+   each up to 64 times denser than the one before, then every tile; a
+   sample's k-th distance bounds the next scan's candidates per query, which
+   are selected between scans.  The scans screen the pairs by fp16 products
+   within their error bound; the distances of those left are formed as said
+   above.  Should more than 8192 rows of the last scan fall
    within a query's bound (many rows at one distance), the pass is computed
    again by the per-wave lists of huge_eval_knn_lists; the answer is the
    same either way, bit for bit.  Sizes (Sec. 4's sampled recall): 100

@@ -970,7 +970,7 @@ SummaryLayout summary_layout(int64_t max_pairs) {
 }
 
 struct KnnLayout {
-    size_t qn, qn2, qid, partial, tau, cnt, gate, cand, total;
+    size_t qn, qn2, qid, partial, tau, cnt, gate, cand, qh, total;
 };
 
 KnnLayout knn_layout(int64_t num_rows, int32_t dim, int32_t k) {
@@ -989,9 +989,10 @@ KnnLayout knn_layout(int64_t num_rows, int32_t dim, int32_t k) {
         take(sizeof(uint64_t) * (size_t)knn_lists(num_rows, dim, 1) * kKnnPass * (size_t)k);
     // the threshold scans' bounds, counts, gate and candidate lists
     L.tau = take(sizeof(float) * kKnnPass);
-    L.cnt = take(sizeof(uint32_t) * kKnnPass);
+    L.cnt = take(sizeof(uint32_t) * kKnnPass * kKnnCntStride);
     L.gate = take(sizeof(int32_t));
     L.cand = take(sizeof(uint64_t) * kKnnPass * (size_t)kKnnCandCap);
+    L.qh = take(sizeof(uint16_t) * kKnnPass * (size_t)((dim + 15) / 16 * 16));
     L.total = off;
     return L;
 }
@@ -1110,6 +1111,7 @@ huge_status eval_knn(const float* d_table, int64_t num_rows, int32_t dim,
     B.cnt = reinterpret_cast<uint32_t*>(ws + L.cnt);
     B.gate = reinterpret_cast<int32_t*>(ws + L.gate);
     B.cand = reinterpret_cast<uint64_t*>(ws + L.cand);
+    B.qh = reinterpret_cast<_Float16*>(ws + L.qh);
     HIP_TRY(launch_knn(d_table, num_rows, dim, d_queries, n_queries, k, d_ids, d_dist, B,
                        lists_only, d_status, s));
     return HUGE_OK;

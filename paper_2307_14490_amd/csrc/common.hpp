@@ -55,12 +55,17 @@ constexpr int kKnnQueryFloats = 16896;  // LDS floats for the queries of a pass 
 constexpr int kKnnPass = 128;           // queries per pass over the table, at most
 constexpr int kKnnGrid = 256;           // nearest-row workgroups (one per CU)
 constexpr int kKnnMergeCap = 8192;      // keys sorted together by the merge
-// Threshold scans of the nearest-row search (dim <= 128)
+// Threshold scans of the nearest-row search
 constexpr int kKnnScanWaves = 4;        // waves of a scan workgroup (two workgroups per CU)
 constexpr int kKnnScanGrid = 512;       // scan workgroups, at most
 constexpr int kKnnCandCap = 8192;       // candidate keys kept per query and scan
 constexpr int kKnnStageTiles = 256;     // row tiles of the first (coarsest) scan, at most
 constexpr int kKnnStageGrowth = 32;     // tile stride of a scan over that of the next
+constexpr int kKnnWideWaves = 8;        // waves of a scan workgroup for dim > 128 (one per CU)
+constexpr int kKnnWideGrowth = 64;      // tile stride of such a scan over that of the next, at most
+constexpr int kKnnCntStride = 32;       // u32 between the candidate counts of two queries: a
+                                        // cache line each, since every append is an atomic (1e7 x
+                                        // 128, 100 queries: 1.41 -> 1.23 ms against adjacent counts)
 constexpr int kKnnSelectThreads = 1024; // threads of a candidate selection workgroup
 constexpr uint32_t kShortRun = 32;     // repeated rows with at most this many occurrences are
                                        // summed by one thread group
@@ -430,7 +435,8 @@ struct KnnBuffers {
     int32_t* qid;     // [kKnnPass] their rows (-1: padding)
     uint64_t* partial;  // per-wave lists of the list-merging search
     float* tau;       // [kKnnPass] distance bound of the next threshold scan
-    uint32_t* cnt;    // [kKnnPass] candidates of the current scan
+    uint32_t* cnt;    // [kKnnPass * kKnnCntStride] candidates of the current scan
+    _Float16* qh;     // wide rows: the queries' fp16 parts, as matrix operands
     uint64_t* cand;   // [kKnnPass][kKnnCandCap] their keys
     int32_t* gate;    // 1: a final scan overflowed, the list-merging search runs
 };

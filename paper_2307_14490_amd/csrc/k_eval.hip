@@ -16,6 +16,8 @@
 //                   per tile) for dim <= 128: rows and queries split into two
 //                   fp16 parts on the fp16 matrix cores; per-wave top-k lists;
 //   k_knn_tiles     the same for wider rows: fp32 matrix cores, queries in LDS;
+//   k_knn_scan      threshold scans for dim <= 128, k_knn_wide_* for wider rows;
+//   k_knn_select    the candidates of a scan, sorted: the next scan's bound;
 //   k_knn_merge     the k nearest of each query over all lists (bitonic sort);
 //   k_eval_recall   recall@k from the nearest rows and the sorted CSR lists.
 #include "common.hpp"
@@ -289,7 +291,10 @@ hipError_t launch_eval_quantiles(const uint32_t* sorted, const double* cnt, cons
 // Normalised query rows qn[j * D ..] (zero for a zero row or a padding slot)
 // and qn2[j] = |qn_j|^2 in {0, 1}; with the threshold scans, their state: no
 // candidates, the bound +inf (-inf for a padding slot: nothing passes it) and
-// the fallback gate closed.
+// the fallback gate closed.  qh (if not null) receives the queries' fp16
+// parts as matrix operands.
+constexpr float kKnnSplitScale = 1024.0f;  // 2^10: the scale of the fp16 parts
+
 __global__ __launch_bounds__(kBlock) void k_knn_queries(const float* __restrict__ T, int64_t N,
                                                         int32_t D, const int32_t* __restrict__ q,
                                                         int32_t nq, int32_t nqp,
@@ -299,6 +304,7 @@ __global__ __launch_bounds__(kBlock) void k_knn_queries(const float* __restrict_
                                                         float* __restrict__ tau,
                                                         uint32_t* __restrict__ cnt,
                                                         int32_t* __restrict__ gate,
+                                                        _Float16* __restrict__ qh,
                                                         int32_t* __restrict__ status) {
     __shared__ float s_red[kBlock];
     const int j = blockIdx.x;
@@ -324,11 +330,22 @@ __global__ __launch_bounds__(kBlock) void k_knn_queries(const float* __restrict_
     const float inv = n2 > 0.f ? 1.0f / sqrtf(n2) : 0.f;
     for (int c = threadIdx.x; c < D; c += kBlock)
         qn[(int64_t)j * D + c] = id >= 0 ? T[(int64_t)id * D + c] * inv : 0.f;
+    if (qh != nullptr) {
+        // matrix operands: element e of lane x + 32 h of chunk c of query
+        // block j / 32 is dimension 16 c + 8 h + e of query j = 32 (j / 32) + x
+        const int nc = (D + 15) / 16, x = j & 31;
+        for (int d = threadIdx.x; d < 16 * nc; d += kBlock) {
+            const float v = id >= 0 && d < D ? T[(int64_t)id * D + d] * inv : 0.f;
+            const int lane = x + 32 * ((d >> 3) & 1);
+            qh[(((size_t)(j >> 5) * nc + (d >> 4)) * 64 + lane) * 8 + (d & 7)] =
+                (_Float16)(v * kKnnSplitScale);
+        }
+    }
     if (threadIdx.x == 0) {
         qn2[j] = n2 > 0.f ? 1.f : 0.f;
         qid[j] = id;
         if (cnt) {
-            cnt[j] = 0u;
+            cnt[j * kKnnCntStride] = 0u;
             tau[j] = id >= 0 ? __builtin_inff() : -__builtin_inff();
         }
         if (gate && j == 0) *gate = 0;
@@ -337,23 +354,71 @@ __global__ __launch_bounds__(kBlock) void k_knn_queries(const float* __restrict_
 
 typedef float knn_acc16 __attribute__((ext_vector_type(16)));
 
-// One workgroup of kKnnWaves waves; wave w serves query block w % QB (32
-// queries) over tiles t = S, S + NS, ... of 32 rows, S = its list slot.  Per
-// tile: the 32 x 32 dot products of the normalised queries with the raw rows
-// by v_mfma_f32_32x32x2f32 (the K dimension runs over the dimensions in
-// chunks of 128: lane (x, h) supplies row x's dimensions c*128 + h*64 + s and
-// query x's same dimension at step s), the rows' norms from the same
-// registers, then d^2 = |q|^2 + [row != 0] - 2 dot / |row| and the key
-// (bits of d^2) << 32 | row.  Keys below the query's current k-th best are
-// staged per query (at most 32 per tile) and inserted by the query's own lane
-// into its sorted list of k.  Lists go to partial[(S * nqp + q) * k + t].
+// The exact products of the search for wide rows (dim > 128): lane (x, h)
+// holds dimensions c 128 + h 64 + 4 m .. + 3 (m < 16) of its row of the A and
+// of the B operand, from a(dim) and b(dim) (float4; past dim, zeros); chunk by
+// chunk, v_mfma_f32_32x32x2f32 per component, even m in one accumulation
+// chain, odd m in another.  The row's squared norm (its B operand) is one
+// fixed sequence of fused multiply-adds per lane, added to the other half's.
+// Every kernel of this search forms a pair's distance this way, so all give
+// the same bits.
+template <typename LoadA, typename LoadB>
+__device__ __forceinline__ void knn_exact_products(int D, int h, LoadA a, LoadB b,
+                                                   knn_acc16& acc, float& nr) {
+    constexpr int kQ4 = kKnnDimChunk / 8;  // float4 of a lane's half row
+    knn_acc16 acc1;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = acc1[r] = 0.f;
+    nr = 0.f;
+    for (int c = 0; c < D; c += kKnnDimChunk) {
+        const int d0 = c + h * (kKnnDimChunk / 2);
+        float4 bv[kQ4];
+#pragma unroll
+        for (int m = 0; m < kQ4; ++m)
+            bv[m] = d0 + 4 * m < D ? b(d0 + 4 * m) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int m = 0; m < kQ4; ++m) {
+            float t = bv[m].x * bv[m].x;
+            t = fmaf(bv[m].y, bv[m].y, t);
+            t = fmaf(bv[m].z, bv[m].z, t);
+            t = fmaf(bv[m].w, bv[m].w, t);
+            nr += t;
+            const float4 av = d0 + 4 * m < D ? a(d0 + 4 * m) : make_float4(0.f, 0.f, 0.f, 0.f);
+            knn_acc16& s = m % 2 == 0 ? acc : acc1;
+            s = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, bv[m].x, s, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, bv[m].y, s, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, bv[m].z, s, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, bv[m].w, s, 0, 0, 0);
+        }
+    }
+    acc += acc1;
+    nr += __shfl_xor(nr, 32, 64);
+}
+
+// d^2 = |q|^2 + [row != 0] - 2 <q, row> / |row|, clamped at 0 (also where it
+// is not a number).
+__device__ __forceinline__ float knn_exact_d2(float q2, float nr, float dot) {
+    const float inv = nr > 0.f ? 1.0f / sqrtf(nr) : 0.f;
+    const float nx = nr > 0.f ? 1.f : 0.f;
+    const float d2 = fmaf(-2.f * dot, inv, q2 + nx);
+    return d2 > 0.f ? d2 : 0.f;
+}
+
+// The list search for wide rows.  One workgroup of kKnnWaves waves, the
+// queries of a sub-pass (32 QB of them) in LDS; wave w serves query block
+// w % QB over tiles t = S, S + NS, ... of 32 rows, S = its list slot.  Keys
+// (bits of d^2) << 32 | row below the query's current k-th best are staged per
+// query (at most 32 per tile) and inserted by the query's own lane into its
+// sorted list of k.  Sub-pass p's lists go to
+// partial[((p NS + S) * 32 QB + q) * k + t].
 struct KnnArgs {
     const float* T;
     int64_t N;
     int32_t D;
     int32_t k;
-    int32_t nqp;   // queries in this pass, padded to 32 * QB
+    int32_t nqp;   // queries in this pass (wide rows: sub-pass), padded to 32 * QB
     int32_t QB;    // query blocks: 1, 2 or 4
+    int32_t subs;  // wide rows: sub-passes of nqp queries each
     int32_t stride;  // LDS floats per query row (D + 4)
     int64_t tiles;
     const float* qn;
@@ -379,13 +444,18 @@ __global__ __launch_bounds__(kKnnWaves * 64) void k_knn_tiles(KnnArgs A) {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int x = lane & 31, h = lane >> 5;
     const int D = A.D, k = A.k, stride = A.stride;
-    for (int i = tid; i < kKnnQueryFloats; i += kKnnWaves * 64) s_q[i] = 0.f;
-    __syncthreads();
+    const int qb = w % A.QB;
+    const int wpb = kKnnWaves / A.QB;  // waves per query block
+    const int64_t S = (int64_t)blockIdx.x * wpb + w / A.QB;
+    const int64_t NS = (int64_t)gridDim.x * wpb;
+    for (int sub = 0; sub < A.subs; ++sub) {
+    const int q0 = sub * A.nqp;  // the sub-pass's first query
+    __syncthreads();  // LDS of the previous sub-pass
     for (int64_t i = tid; i < (int64_t)A.nqp * D; i += kKnnWaves * 64)
-        s_q[(i / D) * stride + (i % D)] = A.qn[i];
+        s_q[(i / D) * stride + (i % D)] = A.qn[(int64_t)q0 * D + i];
     for (int i = tid; i < A.nqp; i += kKnnWaves * 64) {
-        s_qn2[i] = A.qn2[i];
-        s_qid[i] = A.qid[i];
+        s_qn2[i] = A.qn2[q0 + i];
+        s_qid[i] = A.qid[q0 + i];
     }
     if (lane < 32) {
         s_thr[w][lane] = kNoKey;
@@ -393,79 +463,22 @@ __global__ __launch_bounds__(kKnnWaves * 64) void k_knn_tiles(KnnArgs A) {
         s_len[w][lane] = 0u;
     }
     __syncthreads();
-
-    const int qb = w % A.QB;
-    const int wpb = kKnnWaves / A.QB;  // waves per query block
-    const int64_t S = (int64_t)blockIdx.x * wpb + w / A.QB;
-    const int64_t NS = (int64_t)gridDim.x * wpb;
-    const int nch = (D + kKnnDimChunk - 1) / kKnnDimChunk;
     const float* qrow = s_q + (qb * 32 + x) * stride;
-
-    // one dimension chunk (dim <= 128): the next tile's rows are loaded
-    // while the current tile's products run
-    constexpr int kQ4 = kKnnDimChunk / 8;  // float4 of a lane's half row
-    const int d0h = h * (kKnnDimChunk / 2);
-    auto load_rows = [&](int64_t tt, int c, float4* bv) {
-        const int64_t rr = tt * 32 + x;
-        const int d0 = c * kKnnDimChunk + d0h;
-        const float4* src = reinterpret_cast<const float4*>(A.T + rr * (int64_t)D + d0);
-        const bool ok = tt < A.tiles && rr < A.N;
-#pragma unroll
-        for (int m = 0; m < kQ4; ++m)
-            bv[m] = (ok && d0 + 4 * m < D) ? src[m] : make_float4(0.f, 0.f, 0.f, 0.f);
-    };
-    float4 nxt[kQ4];
-    if (nch == 1) load_rows(S, 0, nxt);
     for (int64_t t = S; t < A.tiles; t += NS) {
         const int64_t row = t * 32 + x;
         const bool row_ok = row < A.N;
-        // two independent accumulation chains (even and odd float4 of the
-        // lane's half row), added at the end
-        knn_acc16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
-                         0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        knn_acc16 acc1 = acc;
-        float nr = 0.f;
-        for (int c = 0; c < nch; ++c) {
-            const int d0 = c * kKnnDimChunk + d0h;
-            float4 bv[kQ4];
-            if (nch == 1) {
-#pragma unroll
-                for (int m = 0; m < kQ4; ++m) bv[m] = nxt[m];
-                load_rows(t + NS, 0, nxt);
-            } else {
-                load_rows(t, c, bv);
-            }
-#pragma unroll
-            for (int m = 0; m < kQ4; ++m) {
-                nr += bv[m].x * bv[m].x + bv[m].y * bv[m].y + bv[m].z * bv[m].z +
-                      bv[m].w * bv[m].w;
-                const int dd = d0 + 4 * m;
-                float4 av = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (dd < D) av = *reinterpret_cast<const float4*>(qrow + dd);
-                if (m % 2 == 0) {
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, bv[m].x, acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, bv[m].y, acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, bv[m].z, acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, bv[m].w, acc, 0, 0, 0);
-                } else {
-                    acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, bv[m].x, acc1, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, bv[m].y, acc1, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, bv[m].z, acc1, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, bv[m].w, acc1, 0, 0, 0);
-                }
-            }
-        }
-        acc += acc1;
-        nr += __shfl_xor(nr, 32, 64);
-        const float inv = nr > 0.f ? 1.0f / sqrtf(nr) : 0.f;
-        const float nx = nr > 0.f ? 1.f : 0.f;
+        const float* src = A.T + (row_ok ? row : 0) * (int64_t)D;
+        knn_acc16 acc;
+        float nr;
+        knn_exact_products(
+            D, h, [&](int d) { return *reinterpret_cast<const float4*>(qrow + d); },
+            [&](int d) { return *reinterpret_cast<const float4*>(src + d); }, acc, nr);
         // lane (x, h) holds query i = 8 (r / 4) + 4 h + r % 4 against row x
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int i = 8 * (r / 4) + 4 * h + (r % 4);
             const int q = qb * 32 + i;
-            float d2 = s_qn2[q] + nx - 2.f * acc[r] * inv;
-            d2 = d2 > 0.f ? d2 : 0.f;
+            const float d2 = knn_exact_d2(s_qn2[q], nr, acc[r]);
             const bool ok = row_ok && s_qid[q] >= 0 && row != (int64_t)s_qid[q];
             const uint64_t key =
                 ok ? (((uint64_t)__float_as_uint(d2) << 32) | (uint64_t)row) : kNoKey;
@@ -502,9 +515,11 @@ __global__ __launch_bounds__(kKnnWaves * 64) void k_knn_tiles(KnnArgs A) {
     }
     if (h == 0) {
         const uint32_t len = s_len[w][x];
-        uint64_t* dst = A.partial + ((size_t)S * A.nqp + qb * 32 + x) * k;
+        uint64_t* dst =
+            A.partial + (((size_t)sub * NS + S) * A.nqp + qb * 32 + x) * k;
         for (int t = 0; t < k; ++t) dst[t] = (uint32_t)t < len ? s_list[w][x][t] : kNoKey;
     }
+    }  // sub-passes
 }
 
 // The k smallest keys of query q over all NS lists: running best k plus a
@@ -516,7 +531,9 @@ __global__ __launch_bounds__(kBlock) void k_knn_merge(const uint64_t* __restrict
                                                       const int32_t* __restrict__ gate) {
     __shared__ uint64_t s_buf[kKnnMergeCap];
     if (gate && *gate == 0) return;
-    const int q = blockIdx.x;
+    // query q of the pass is query q % nqp of sub-pass q / nqp
+    const int q = blockIdx.x % nqp;
+    partial += (size_t)(blockIdx.x / nqp) * NS * nqp * k;
     const int64_t total = NS * k;
     for (int i = threadIdx.x; i < k; i += kBlock) s_buf[i] = kNoKey;
     for (int64_t base = 0; base < total; base += kKnnMergeCap - k) {
@@ -549,7 +566,7 @@ __global__ __launch_bounds__(kBlock) void k_knn_merge(const uint64_t* __restrict
     }
     for (int t = threadIdx.x; t < k; t += kBlock) {
         const uint64_t key = s_buf[t];
-        const int64_t o = (int64_t)(q_first + q) * k + t;
+        const int64_t o = (int64_t)(q_first + (int)blockIdx.x) * k + t;
         ids[o] = key == kNoKey ? -1 : (int32_t)(uint32_t)key;
         dist[o] = key == kNoKey ? __builtin_nanf("") : sqrtf(__uint_as_float((uint32_t)(key >> 32)));
     }
@@ -567,7 +584,6 @@ __global__ __launch_bounds__(kBlock) void k_knn_merge(const uint64_t* __restrict
 // lane i + 32 (c / 8), B[c][j] from element c % 8 of lane j + 32 (c / 8); the
 // accumulators are laid out as for the fp32 instruction.
 typedef _Float16 knn_h8 __attribute__((ext_vector_type(8)));
-constexpr float kKnnSplitScale = 1024.0f;                  // 2^10
 constexpr float kKnnSplitUnscale = 1.0f / (1024.0f * 1024.0f);  // 2^-20, exact
 
 // The split of 8 values scaled by sc.  Each product v is pinned as one fp32
@@ -1030,7 +1046,7 @@ __device__ __forceinline__ void knn_scan_append(const KnnScanArgs& A, int qb, in
         if (d2 <= tau && m < rows && t * 32 + m != qid) pass |= 1u << r;
     }
     if (pass == 0u) return;
-    uint32_t pos = atomicAdd(&A.cnt[q], (uint32_t)__popc(pass));
+    uint32_t pos = atomicAdd(&A.cnt[q * kKnnCntStride], (uint32_t)__popc(pass));
     uint64_t* dst = A.cand + (size_t)q * A.cap;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -1163,12 +1179,17 @@ void k_knn_scan(KnnScanArgs A) {
     }
 }
 
-// Candidate selection, one workgroup per query slot: the list's kept keys
-// (at most cap, a power of two) sorted in LDS by a bitonic network.  After a
-// sample scan the k-th key's d^2 becomes the query's bound (fewer than k keys
-// leave it); after the last scan the k smallest keys are the answer, written
-// as the list-merging search writes it, and a list that overflowed opens the
-// gate for that search.  The count is reset for the next scan.
+// Candidate selection, one workgroup per query slot: the k smallest of the
+// list's kept keys (at most cap, a power of two).  After a sample scan the
+// k-th key's d^2 becomes the query's bound (fewer than k keys leave it); after
+// the last scan the k smallest keys are the answer, written as the
+// list-merging search writes it, and a list that overflowed opens the gate for
+// that search.  The count is reset for the next scan.
+// The keys' distances are counted in kKnnSelectBins equal ranges of their bit
+// patterns between the smallest and the largest; only the keys up to the range
+// that holds the k-th are sorted (a bitonic network in LDS).  Sorting all of
+// 8192 keys took 75 us, of 1024 20; counting and sorting those left
+// 14 and 13.
 struct KnnSelectArgs {
     uint32_t* cnt;
     const uint64_t* cand;
@@ -1183,26 +1204,92 @@ struct KnnSelectArgs {
     int32_t* gate;
 };
 
+constexpr int kKnnSelectBins = 1024;
+
 __global__ __launch_bounds__(kKnnSelectThreads) void k_knn_select(KnnSelectArgs S) {
-    extern __shared__ uint64_t s_key[];
+    extern __shared__ uint64_t s_key[];  // [cap]
+    __shared__ uint32_t s_bin[kKnnSelectBins];
+    __shared__ uint32_t s_wave[kKnnSelectThreads / 64];
+    __shared__ uint32_t s_min, s_max, s_last, s_kept;
+    static_assert(kKnnSelectBins == kKnnSelectThreads, "a bin per thread");
+    static_assert(kKnnCandCap % kKnnSelectThreads == 0, "whole keys per thread");
     const int q = blockIdx.x, tid = threadIdx.x;
-    const uint32_t c = S.cnt[q];
+    const uint32_t c = S.cnt[q * kKnnCntStride];
     const uint32_t n = c < (uint32_t)S.cap ? c : (uint32_t)S.cap;
+    constexpr int kPer = kKnnCandCap / kKnnSelectThreads;
+    s_bin[tid] = 0u;
+    if (tid == 0) {
+        s_min = ~0u;
+        s_max = 0u;
+        s_last = (uint32_t)kKnnSelectBins;  // no bin: every key is kept
+        s_kept = 0u;
+    }
+    __syncthreads();
+    // the range of the distances (a missing pair's key, ~0, is none)
+    uint64_t key[kPer];
+    uint32_t lo = ~0u, hi = 0u;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+        const uint32_t i = (uint32_t)(e * kKnnSelectThreads + tid);
+        key[e] = i < n ? S.cand[(size_t)q * S.cap + i] : kNoKey;
+        if (key[e] != kNoKey) {
+            const uint32_t d = (uint32_t)(key[e] >> 32);
+            lo = d < lo ? d : lo;
+            hi = d > hi ? d : hi;
+        }
+    }
+    if (lo <= hi) {
+        atomicMin(&s_min, lo);
+        atomicMax(&s_max, hi);
+    }
+    __syncthreads();
+    const uint32_t base = s_min;
+    const uint32_t span = s_max >= base ? s_max - base : 0u;
+    // d - base <= span < 2^32: range (d - base) 2^-shift, shift such that the
+    // largest is below kKnnSelectBins
+    int shift = 0;
+    while ((span >> shift) >= (uint32_t)kKnnSelectBins) ++shift;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e)
+        if (key[e] != kNoKey) atomicAdd(&s_bin[((uint32_t)(key[e] >> 32) - base) >> shift], 1u);
+    __syncthreads();
+    {
+        const int lane = tid & 63, wave = tid >> 6;
+        const uint32_t mine = s_bin[tid];
+        uint32_t incl = mine;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t t = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += t;
+        }
+        if (lane == 63) s_wave[wave] = incl;
+        __syncthreads();
+        for (int w = 0; w < wave; ++w) incl += s_wave[w];
+        // the range that holds the k-th key
+        if (incl >= (uint32_t)S.k && incl - mine < (uint32_t)S.k) s_last = (uint32_t)tid;
+    }
+    __syncthreads();
+    const uint32_t last = s_last;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e)
+        if (key[e] != kNoKey && ((uint32_t)(key[e] >> 32) - base) >> shift <= last)
+            s_key[atomicAdd(&s_kept, 1u)] = key[e];
+    __syncthreads();
+    const uint32_t kept = s_kept;
     uint32_t P = 2u;
-    while (P < n) P <<= 1;
-    for (uint32_t i = tid; i < P; i += kKnnSelectThreads)
-        s_key[i] = i < n ? S.cand[(size_t)q * S.cap + i] : kNoKey;
+    while (P < kept || P < (uint32_t)S.k) P <<= 1;
+    for (uint32_t i = kept + tid; i < P; i += kKnnSelectThreads) s_key[i] = kNoKey;
     __syncthreads();
     for (uint32_t size = 2; size <= P; size <<= 1) {
         for (uint32_t st = size >> 1; st > 0; st >>= 1) {
             for (uint32_t i = tid; i < P / 2; i += kKnnSelectThreads) {
-                const uint32_t lo = 2 * i - (i & (st - 1));
-                const uint32_t hi = lo + st;
-                const bool up = (lo & size) == 0;
-                const uint64_t a = s_key[lo], b = s_key[hi];
+                const uint32_t lo_i = 2 * i - (i & (st - 1));
+                const uint32_t hi_i = lo_i + st;
+                const bool up = (lo_i & size) == 0;
+                const uint64_t a = s_key[lo_i], b = s_key[hi_i];
                 if ((a > b) == up) {
-                    s_key[lo] = b;
-                    s_key[hi] = a;
+                    s_key[lo_i] = b;
+                    s_key[hi_i] = a;
                 }
             }
             __syncthreads();
@@ -1211,7 +1298,7 @@ __global__ __launch_bounds__(kKnnSelectThreads) void k_knn_select(KnnSelectArgs 
     if (S.last) {
         if (q < S.m) {
             for (int t = tid; t < S.k; t += kKnnSelectThreads) {
-                const uint64_t key = (uint32_t)t < P ? s_key[t] : kNoKey;
+                const uint64_t key = s_key[t];  // k <= P
                 const int64_t o = (int64_t)(S.q_first + q) * S.k + t;
                 S.ids[o] = key == kNoKey ? -1 : (int32_t)(uint32_t)key;
                 S.dist[o] = key == kNoKey ? __builtin_nanf("")
@@ -1219,16 +1306,309 @@ __global__ __launch_bounds__(kKnnSelectThreads) void k_knn_select(KnnSelectArgs 
             }
         }
         if (tid == 0 && c > (uint32_t)S.cap) *S.gate = 1;
-    } else if (tid == 0 && n >= (uint32_t)S.k) {
+    } else if (tid == 0 && s_key[S.k - 1] != kNoKey) {
         S.tau[q] = __uint_as_float((uint32_t)(s_key[S.k - 1] >> 32));
     }
-    if (tid == 0) S.cnt[q] = 0u;
+    if (tid == 0) S.cnt[q * kKnnCntStride] = 0u;
+}
+
+// ---------------------------------------------------------------------------
+// Threshold scans of wide rows (128 < dim): the exact products cost dim / 2
+// fp32 matrix instructions of 64 cycles per 32 x 32 pairs, so they are formed
+// for few pairs only.
+//   k_knn_wide_dense    the first scan, no bound yet: every pair of at most
+//                       kKnnStageTiles tiles, exactly, each key at its place;
+//   k_knn_wide_scan     the others screen every tile of theirs with fp16
+//                       products and append the rows left to the queries'
+//                       lists;
+//   k_knn_wide_rescore  replaces those rows by their exact keys.
+// Between scans k_knn_select sorts the lists, as for narrower rows.  A scan of
+// stride s after one of stride g s keeps about k g rows per query, so
+// fewer, coarser scans cost exact products and more, finer ones launches:
+// g is at most kKnnWideGrowth.
+//
+// The screen.  A tile's rows are taken in slabs of 128 dimensions, the next
+// slab's loads in flight during the current one's products.  A row is scaled
+// by sc = 64 / |its first slab| before its fp16 rounding, since its own norm
+// is known only after the last slab; with f = sc |row| / 2^10, the product of
+// the fp16 parts is f times that of the normalised parts scaled by 2^20, up to
+//   the roundings: 2^-11 of each operand's norm, 2^10 (1 + 2^-11) units in all
+//     (a unit is f times one of a product of size 2^20); parts below 2^-14
+//     round by 2^-25 instead, under 1 unit while sc |row| >= 1;
+//   dim / 16 units for the sums here, as many for those of the exact
+//     products, 16 for f and 3 for the bound:
+// below 1150 units for dim <= 528.  A pair can pass d^2 <= tau only if its
+// product is at least f ((|q|^2 + 1 - tau) 2^19) less those (a zero row:
+// |q|^2 - tau); kKnnScreenMargin = 1536 units are left.  A row whose scaled
+// norm leaves [1, 2^14], or whose norm is tiny or not finite, is no subject of
+// the screen: it is appended to every list.  Should a list overflow, the pass
+// is computed by the list search.
+// 500,000 x 256 rows, 100 queries, k = 10: the list search alone, in two passes
+// over the table, took 1349 us, the scans take 274 us (dense 19, scan
+// 123, rescore 49, selections 14 each; the table once at the copy rate: 106).
+// ---------------------------------------------------------------------------
+struct KnnWideArgs {
+    const float* T;
+    int64_t N;
+    int32_t D;
+    int32_t cap;
+    int64_t step;   // tiles i * step, 0 <= i < count
+    int64_t count;
+    const float* qn;
+    const float* qn2;
+    const int32_t* qid;
+    const _Float16* qh;
+    const float* tau;
+    uint32_t* cnt;
+    uint64_t* cand;
+};
+
+// Wave (tile i, query block qb): the keys of their pairs at cand[q][32 i + row]
+// (no pair: kNoKey); the first tile's waves set the counts.
+template <int QB>
+__global__ __launch_bounds__(256) void k_knn_wide_dense(KnnWideArgs A) {
+    const int lane = threadIdx.x & 63;
+    const int x = lane & 31, h = lane >> 5;
+    const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t i = w / QB;
+    const int qb = (int)(w % QB);
+    if (i >= A.count) return;  // no barrier below
+    const int64_t row = i * A.step * 32 + x;
+    const bool ok = row < A.N;
+    const float* src = A.T + (ok ? row : 0) * (int64_t)A.D;
+    const float* qrow = A.qn + (int64_t)(qb * 32 + x) * A.D;
+    knn_acc16 acc;
+    float nr;
+    knn_exact_products(
+        A.D, h, [&](int d) { return *reinterpret_cast<const float4*>(qrow + d); },
+        [&](int d) { return *reinterpret_cast<const float4*>(src + d); }, acc, nr);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int q = qb * 32 + 8 * (r / 4) + 4 * h + (r % 4);
+        const float d2 = knn_exact_d2(A.qn2[q], nr, acc[r]);
+        const int32_t id = A.qid[q];
+        const bool pair = ok && id >= 0 && row != (int64_t)id;
+        A.cand[(size_t)q * A.cap + (size_t)i * 32 + x] =
+            pair ? ((uint64_t)__float_as_uint(d2) << 32) | (uint64_t)row : kNoKey;
+        if (i == 0 && x == 0) A.cnt[q * kKnnCntStride] = (uint32_t)(A.count * 32);
+    }
+}
+
+// The listed rows of query blockIdx.x, 32 per wave and round: their exact keys
+// in their places.  The A operand holds the query in every row, so each lane
+// finds its row's product in accumulator 0.
+__global__ __launch_bounds__(256) void k_knn_wide_rescore(KnnWideArgs A) {
+    extern __shared__ __align__(16) float s_query[];  // [dim]
+    const int lane = threadIdx.x & 63;
+    const int x = lane & 31, h = lane >> 5;
+    const int q = blockIdx.x;
+    const uint32_t c = A.cnt[q * kKnnCntStride];
+    const uint32_t n = c < (uint32_t)A.cap ? c : (uint32_t)A.cap;
+    if (32u * 4u * blockIdx.y >= n) return;  // uniform
+    for (int d = threadIdx.x; d < A.D; d += 256) s_query[d] = A.qn[(int64_t)q * A.D + d];
+    __syncthreads();
+    const float q2 = A.qn2[q];
+    const int32_t id = A.qid[q];
+    uint64_t* list = A.cand + (size_t)q * A.cap;
+    const uint32_t first = 32u * (blockIdx.y * 4u + (threadIdx.x >> 6));
+    for (uint32_t j0 = first; j0 < n; j0 += 128u * gridDim.y) {
+        const uint32_t j = j0 + (uint32_t)x;
+        const bool ok = j < n;
+        const int64_t row = ok ? (int64_t)(uint32_t)list[j] : 0;
+        const float* src = A.T + row * (int64_t)A.D;
+        knn_acc16 acc;
+        float nr;
+        knn_exact_products(
+            A.D, h, [&](int d) { return *reinterpret_cast<const float4*>(s_query + d); },
+            [&](int d) { return *reinterpret_cast<const float4*>(src + d); }, acc, nr);
+        const float d2 = knn_exact_d2(q2, nr, acc[0]);
+        if (ok && h == 0)
+            list[j] = id >= 0 && row != (int64_t)id
+                          ? ((uint64_t)__float_as_uint(d2) << 32) | (uint64_t)row
+                          : kNoKey;
+    }
+}
+
+// LDS: the queries' operands, [QB][chunks][64 lanes], then the bounds
+// ((|q|^2 + 1 - tau) 2^19 less the margin), 32 per query block.
+template <int QB>
+__global__ __launch_bounds__(kKnnWideWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_knn_wide_scan(KnnWideArgs A) {
+    constexpr int kCh = kKnnDimChunk / 16;  // chunks of a slab
+    extern __shared__ __align__(16) uint8_t s_wide[];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int x = lane & 31, h = lane >> 5;
+    const int D = A.D, nc = (D + 15) / 16;
+    const int slabs = (nc + kCh - 1) / kCh;
+    knn_h8* const s_q = reinterpret_cast<knn_h8*>(s_wide);
+    float* const s_thr = reinterpret_cast<float*>(s_wide + sizeof(knn_h8) * 64 * QB * nc);
+    for (int j = tid; j < QB * nc * 64; j += kKnnWideWaves * 64)
+        s_q[j] = reinterpret_cast<const knn_h8*>(A.qh)[j];
+    for (int q = tid; q < 32 * QB; q += kKnnWideWaves * 64) {
+        const float q1 = A.qn2[q] > 0.f ? 1.f : 0.f;
+        s_thr[q] = A.qid[q] >= 0
+                       ? ((q1 + 1.f) - A.tau[q]) * kKnnAccPerD2 - 3.f - kKnnScreenMargin
+                       : __builtin_inff();
+    }
+    __syncthreads();
+
+    const int64_t W = (int64_t)gridDim.x * kKnnWideWaves;
+    const int d0 = 8 * h;
+    // slab sl of row x of tile i * step; past the scan or the table, row 0
+    auto load_slab = [&](int64_t i, int sl, float4 (&dst)[2 * kCh]) {
+        const int64_t row = i * A.step * 32 + x;
+        const bool ok = i < A.count && row < A.N;
+        const float* src = A.T + (ok ? row : 0) * (int64_t)D;
+#pragma unroll
+        for (int c = 0; c < kCh; ++c) {
+            const int d = sl * kKnnDimChunk + 16 * c + d0;
+            dst[2 * c] = d + 4 <= D ? *reinterpret_cast<const float4*>(src + d)
+                                    : make_float4(0.f, 0.f, 0.f, 0.f);
+            dst[2 * c + 1] = d + 8 <= D ? *reinterpret_cast<const float4*>(src + d + 4)
+                                        : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    };
+    knn_acc16 acc[QB];
+    float nr = 0.f, sc = 0.f;
+    auto take_slab = [&](int64_t i, int sl, const float4 (&bv)[2 * kCh]) {
+        float p = (knn_sq4(bv) + knn_sq4(bv + 4)) + (knn_sq4(bv + 8) + knn_sq4(bv + 12));
+        p += __shfl_xor(p, 32, 64);
+        if (sl == 0) {
+            nr = p;
+            sc = p > 0.f ? 64.f / sqrtf(p) : 0.f;
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[qb][r] = 0.f;
+        } else {
+            nr += p;
+        }
+#pragma unroll
+        for (int c = 0; c < kCh; ++c) {
+            const int ch = sl * kCh + c;
+            if (ch < nc) {
+                const knn_h8 bh = knn_hi8(bv[2 * c], bv[2 * c + 1], sc);
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb)
+                    acc[qb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                        s_q[(qb * nc + ch) * 64 + lane], bh, acc[qb], 0, 0, 0);
+            }
+        }
+        if (sl + 1 < slabs) return;
+        // the tile is done: lane (x, h) holds row x against the queries
+        // 8 (r / 4) + 4 h + r % 4 of every block
+        const int64_t row = i * A.step * 32 + x;
+        const float norm = sc * sqrtf(nr);
+        const bool zero = nr == 0.f;
+        const bool fits = nr >= 1e-30f && nr <= 1e38f && norm >= 1.f && norm <= 16384.f;
+        const bool there = row < A.N;
+        const float f = zero ? 1.f : norm * (1.f / 1024.f);
+        const float off = zero ? -kKnnAccPerD2 : 0.f;
+        const bool force = there && !zero && !fits;
+        uint32_t mask[QB];
+        bool any = false;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            mask[qb] = 0u;
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                const float4 th = *reinterpret_cast<const float4*>(s_thr + qb * 32 + 8 * r4 + 4 * h);
+                const float t4[4] = {th.x, th.y, th.z, th.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    // not below the bound (nor a number at all)
+                    const bool left = !(acc[qb][4 * r4 + e] < fmaf(t4[e], f, off));
+                    mask[qb] |= (left || force) && there ? 1u << (4 * r4 + e) : 0u;
+                }
+            }
+            any |= mask[qb] != 0u;
+        }
+        if (__ballot(any) == 0ull) return;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            for (uint32_t m = mask[qb]; m != 0u; m &= m - 1u) {
+                const int r = __builtin_ctz(m);
+                const int q = qb * 32 + 8 * (r / 4) + 4 * h + (r % 4);
+                if (A.qid[q] < 0) continue;  // a padding slot
+                const uint32_t pos = atomicAdd(&A.cnt[q * kKnnCntStride], 1u);
+                if (pos < (uint32_t)A.cap) A.cand[(size_t)q * A.cap + pos] = (uint64_t)row;
+            }
+        }
+    };
+    // slabs one after the other, in two register buffers
+    float4 ba[2 * kCh], bb[2 * kCh];
+    int64_t i = (int64_t)blockIdx.x * kKnnWideWaves + w;
+    int sl = 0;
+    if (i >= A.count) return;
+    load_slab(i, 0, ba);
+    while (true) {
+        int64_t ni = i;
+        int ns = sl + 1;
+        if (ns == slabs) {
+            ns = 0;
+            ni += W;
+        }
+        load_slab(ni, ns, bb);
+        take_slab(i, sl, ba);
+        i = ni;
+        sl = ns;
+        if (i >= A.count) break;
+        ns = sl + 1;
+        if (ns == slabs) {
+            ns = 0;
+            ni += W;
+        }
+        load_slab(ni, ns, ba);
+        take_slab(i, sl, bb);
+        i = ni;
+        sl = ns;
+        if (i >= A.count) break;
+    }
+}
+
+template <int QB>
+static hipError_t launch_knn_wide_scan(const KnnWideArgs& A, hipStream_t s) {
+    const size_t lds = sizeof(knn_h8) * 64 * QB * (size_t)((A.D + 15) / 16) +
+                       sizeof(float) * 32 * QB;
+    const hipError_t e = hipFuncSetAttribute(
+        reinterpret_cast<const void*>(&k_knn_wide_scan<QB>),
+        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    int64_t grid = (A.count + kKnnWideWaves - 1) / kKnnWideWaves;
+    grid = grid < kKnnGrid ? grid : kKnnGrid;
+    hipLaunchKernelGGL(k_knn_wide_scan<QB>, dim3((unsigned)grid), dim3(kKnnWideWaves * 64), lds,
+                       s, A);
+    return hipGetLastError();
 }
 
 int knn_pass_queries(int D) {
     int qp = kKnnQueryFloats / (D + 4);
     qp = qp > kKnnPass ? kKnnPass : qp;
     return (qp / 32) * 32;
+}
+
+// Query blocks of a sub-pass of the list search for wide rows: as many (1 or 2)
+// as its LDS holds and as the pass needs.
+static int knn_wide_blocks(int D, int blocks) {
+    return blocks >= 2 && knn_pass_queries(D) >= 64 ? 2 : 1;
+}
+
+// Tile strides of the scans of wide rows, coarsest first: the first visits at
+// most kKnnStageTiles tiles (whose keys fit the lists), each next one is finer
+// by one factor of at most kKnnWideGrowth, the last visits every tile.
+// Returns the number of scans.
+int knn_wide_steps(int64_t tiles, int64_t* steps) {
+    int n = 1;
+    for (int64_t reach = kKnnStageTiles; reach < tiles; reach *= kKnnWideGrowth) ++n;
+    int64_t g = 1;  // the smallest factor that reaches every tile in n scans
+    for (;; ++g) {
+        int64_t reach = kKnnStageTiles;
+        for (int j = 1; j < n && reach < tiles; ++j) reach *= g;
+        if (reach >= tiles) break;
+    }
+    int64_t s = 1;
+    for (int j = n - 1; j >= 0; --j, s *= g) steps[j] = s;
+    return n;
 }
 
 // Lists of one pass: (workgroups) x (waves per query block).
@@ -1268,19 +1648,71 @@ int knn_scan_steps(int64_t tiles, int64_t* steps) {
 hipError_t launch_knn(const float* T, int64_t N, int32_t D, const int32_t* q, int32_t nq,
                       int32_t k, int32_t* ids, float* dist, const KnnBuffers& B,
                       bool lists_only, int32_t* status, hipStream_t s) {
-    const int qp = knn_pass_queries(D);
-    if (qp < 32 || k < 1 || k > kKnnMaxK || N < 1) return hipErrorInvalidValue;
-    const bool scans = D <= kKnnDimChunk && !lists_only;
+    if (knn_pass_queries(D) < 32 || k < 1 || k > kKnnMaxK || N < 1) return hipErrorInvalidValue;
+    const bool wide = D > kKnnDimChunk;
+    const bool scans = !lists_only;
     const int64_t tiles = (N + 31) / 32;
-    for (int32_t q0 = 0; q0 < nq; q0 += qp) {
-        const int32_t m = nq - q0 < qp ? nq - q0 : qp;
+    for (int32_t q0 = 0; q0 < nq; q0 += kKnnPass) {
+        const int32_t m = nq - q0 < kKnnPass ? nq - q0 : kKnnPass;
         int QB = (m + 31) / 32;
         if (QB == 3) QB = 4;
         const int32_t nqp = 32 * QB;
         hipLaunchKernelGGL(k_knn_queries, dim3((unsigned)nqp), dim3(kBlock), 0, s, T, N, D,
                            q + q0, m, nqp, B.qn, B.qn2, B.qid, scans ? B.tau : nullptr,
-                           scans ? B.cnt : nullptr, scans ? B.gate : nullptr, status);
-        if (scans) {
+                           scans ? B.cnt : nullptr, scans ? B.gate : nullptr,
+                           scans && wide ? B.qh : nullptr, status);
+        KnnSelectArgs SS;
+        SS.cnt = B.cnt;
+        SS.cand = B.cand;
+        SS.cap = kKnnCandCap;
+        SS.k = k;
+        SS.m = m;
+        SS.q_first = q0;
+        SS.tau = B.tau;
+        SS.ids = ids;
+        SS.dist = dist;
+        SS.gate = B.gate;
+        int64_t steps[16];
+        if (scans && wide) {
+            KnnWideArgs WA;
+            WA.T = T;
+            WA.N = N;
+            WA.D = D;
+            WA.cap = kKnnCandCap;
+            WA.qn = B.qn;
+            WA.qn2 = B.qn2;
+            WA.qid = B.qid;
+            WA.qh = B.qh;
+            WA.tau = B.tau;
+            WA.cnt = B.cnt;
+            WA.cand = B.cand;
+            const int ns = knn_wide_steps(tiles, steps);
+            for (int j = 0; j < ns; ++j) {
+                WA.step = steps[j];
+                WA.count = (tiles + steps[j] - 1) / steps[j];
+                if (j == 0) {
+                    const dim3 grid((unsigned)((WA.count * QB + 3) / 4));
+                    if (QB == 4)
+                        hipLaunchKernelGGL(k_knn_wide_dense<4>, grid, dim3(256), 0, s, WA);
+                    else if (QB == 2)
+                        hipLaunchKernelGGL(k_knn_wide_dense<2>, grid, dim3(256), 0, s, WA);
+                    else
+                        hipLaunchKernelGGL(k_knn_wide_dense<1>, grid, dim3(256), 0, s, WA);
+                } else {
+                    const hipError_t e = QB == 4   ? launch_knn_wide_scan<4>(WA, s)
+                                         : QB == 2 ? launch_knn_wide_scan<2>(WA, s)
+                                                   : launch_knn_wide_scan<1>(WA, s);
+                    if (e != hipSuccess) return e;
+                    // k g rows per query and those within the screen's margin: a
+                    // round or two of 32 rows for each of 32 waves
+                    hipLaunchKernelGGL(k_knn_wide_rescore, dim3((unsigned)nqp, 8), dim3(256),
+                                       sizeof(float) * (size_t)D, s, WA);
+                }
+                SS.last = j == ns - 1;
+                hipLaunchKernelGGL(k_knn_select, dim3((unsigned)nqp), dim3(kKnnSelectThreads),
+                                   sizeof(uint64_t) * kKnnCandCap, s, SS);
+            }
+        } else if (scans) {
             KnnScanArgs SA;
             SA.T = T;
             SA.N = N;
@@ -1292,18 +1724,6 @@ hipError_t launch_knn(const float* T, int64_t N, int32_t D, const int32_t* q, in
             SA.tau = B.tau;
             SA.cnt = B.cnt;
             SA.cand = B.cand;
-            KnnSelectArgs SS;
-            SS.cnt = B.cnt;
-            SS.cand = B.cand;
-            SS.cap = kKnnCandCap;
-            SS.k = k;
-            SS.m = m;
-            SS.q_first = q0;
-            SS.tau = B.tau;
-            SS.ids = ids;
-            SS.dist = dist;
-            SS.gate = B.gate;
-            int64_t steps[16];
             const int ns = knn_scan_steps(tiles, steps);
             for (int j = 0; j < ns; ++j) {
                 SA.step = steps[j];
@@ -1319,16 +1739,16 @@ hipError_t launch_knn(const float* T, int64_t N, int32_t D, const int32_t* q, in
                                    sizeof(uint64_t) * kKnnCandCap, s, SS);
             }
         }
-        // the list-merging search: for wider rows always, else only where a
-        // final candidate list overflowed (the gate; otherwise its kernels
-        // return at once)
+        // the list-merging search: asked for, or where a final candidate list
+        // overflowed (the gate; otherwise its kernels return at once)
         KnnArgs A;
         A.T = T;
         A.N = N;
         A.D = D;
         A.k = k;
-        A.nqp = nqp;
-        A.QB = QB;
+        A.QB = wide ? knn_wide_blocks(D, QB) : QB;
+        A.nqp = 32 * A.QB;
+        A.subs = nqp / A.nqp;
         A.stride = D + 4;
         A.tiles = tiles;
         A.qn = B.qn;
@@ -1336,8 +1756,8 @@ hipError_t launch_knn(const float* T, int64_t N, int32_t D, const int32_t* q, in
         A.qid = B.qid;
         A.partial = B.partial;
         A.gate = scans ? B.gate : nullptr;
-        const int64_t NS = knn_lists(N, D, QB);
-        if (D <= kKnnDimChunk) {
+        const int64_t NS = knn_lists(N, D, A.QB);
+        if (!wide) {
             const int64_t grid = NS / (kKnnWavesR / QB);
             if (QB == 4)
                 hipLaunchKernelGGL(k_knn_tiles_h4, dim3((unsigned)grid), dim3(kKnnWavesR * 64), 0,
@@ -1346,11 +1766,11 @@ hipError_t launch_knn(const float* T, int64_t N, int32_t D, const int32_t* q, in
                 hipLaunchKernelGGL(k_knn_tiles_h, dim3((unsigned)grid), dim3(kKnnWavesR * 64), 0,
                                    s, A);
         } else {
-            const int64_t grid = NS / (kKnnWaves / QB);
+            const int64_t grid = NS / (kKnnWaves / A.QB);
             hipLaunchKernelGGL(k_knn_tiles, dim3((unsigned)grid), dim3(kKnnWaves * 64), 0, s, A);
         }
-        hipLaunchKernelGGL(k_knn_merge, dim3((unsigned)m), dim3(kBlock), 0, s, B.partial, NS, nqp,
-                           k, q0, ids, dist, A.gate);
+        hipLaunchKernelGGL(k_knn_merge, dim3((unsigned)m), dim3(kBlock), 0, s, B.partial, NS,
+                           A.nqp, k, q0, ids, dist, A.gate);
     }
     return hipGetLastError();
 }

@@ -309,6 +309,60 @@ def test_knn_threshold_scans_at_a_million_rows():
     check_knn(Td.cpu().numpy(), queries[:4], k, ids[:4], dist[:4])
 
 
+@pytest.mark.parametrize("N,D,nq,k,note", [
+    (8192, 132, 90, 10, "one dense scan of 256 tiles; 96 queries in three list sub-passes"),
+    (8193, 140, 33, 3, "one tile more: a second scan, two query blocks"),
+    (30011, 260, 128, 32, "the widest rows with two query blocks per list sub-pass"),
+    (20000, 264, 5, 10, "one block, a ragged last slab"),
+    (9000, 524, 128, 7, "the widest rows taken"),
+    (530000, 160, 40, 10, "three scans"),
+])
+def test_knn_wide_scans_match_the_list_search(N, D, nq, k, note):
+    """Threshold scans of rows wider than 128 against the list search, bit for
+    bit, with rows that the fp16 screen cannot judge: zero, not finite, huge,
+    tiny, and with next to nothing in their first 128 dimensions."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + D)
+    T = torch.randn((N, D), generator=g, device="cuda")
+    T[N // 2:] += 2.0 * torch.randn(D, generator=g, device="cuda")  # a cluster
+    T[3] = 0.0
+    T[4] = T[5] * 2.0
+    T[7, :128] = 0.0
+    T[8, :128] *= 1e-7
+    T[9] *= 1e-18
+    T[10] *= 1e18
+    T[11, 0] = float("inf")
+    T[12, 130] = float("nan")
+    T[N - 2] = T[N - 1]
+    q = torch.randint(0, N, (nq,), generator=g, device="cuda", dtype=torch.int32)
+    q[:5] = torch.tensor([3, 4, 7, 8, N - 1], dtype=torch.int32, device="cuda")
+    say(f"knn wide N={N} D={D} nq={nq} k={k} ({note})")
+    ev = P.Evaluator(N, D, 8, k=k)
+    ids, dist = ev.knn(T, q, k)
+    ids_l, dist_l = ev.knn(T, q, k, lists=True)
+    assert torch.equal(ids, ids_l)
+    assert torch.equal(dist.view(torch.int32), dist_l.view(torch.int32))
+    fine = np.setdiff1d(q[5:].cpu().numpy(), [9, 10, 11, 12])[:3].astype(np.int32)
+    T[9:13] = torch.randn((4, D), generator=g, device="cuda")  # rows of double's own range
+    i2, d2 = ev.knn(T, dev(fine, torch), k)
+    if fine.size and N <= 40000:
+        check_knn(T.cpu().numpy(), fine, k, i2.cpu().numpy(), d2.cpu().numpy())
+
+
+def test_knn_wide_falls_back_to_the_list_search_when_a_candidate_list_overflows():
+    N, D, k = 30000, 192, 10
+    T = torch.from_numpy(np.random.default_rng(8).normal(size=(N, D)).astype(np.float32)).cuda()
+    T[12000:] = T[5]
+    q = torch.tensor([5, 100, 7000], dtype=torch.int32, device="cuda")
+    say(f"knn wide overflow N={N} D={D}")
+    ev = P.Evaluator(N, D, 8, k=k)
+    ids, dist = ev.knn(T, q, k)
+    ids_l, dist_l = ev.knn(T, q, k, lists=True)
+    assert ids[0].tolist() == list(range(12000, 12000 + k))
+    assert torch.equal(ids, ids_l)
+    assert torch.equal(dist.view(torch.int32), dist_l.view(torch.int32))
+
+
 def test_knn_reports_bad_query_ids():
     T = torch.randn((100, 16), device="cuda")
     ev = P.Evaluator(100, 16, 8, k=4)
