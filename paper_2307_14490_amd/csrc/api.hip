@@ -426,7 +426,7 @@ huge_status stage_prepare(huge_handle* h, const int32_t* src, const int32_t* dst
                                  at<uint32_t>(h, SL.tprefix), hist, s));
         if (!prof_mark(h, b, 1, s) || !prof_mark(h, b, 2, s)) return HUGE_ERR_HIP;
         HIP_TRY(launch_radix_pass(ctl, at<uint32_t>(h, SL.keys0), at<uint32_t>(h, SL.keys1),
-                                  at<uint32_t>(h, SL.vals1), m, tile, bits, 0, hist,
+                                  at<uint32_t>(h, SL.vals1), m, tile, bits, hist,
                                   at<uint32_t>(h, SL.tprefix), at<uint32_t>(h, SL.bstart), s));
         if (!prof_mark(h, b, 3, s) || !prof_mark(h, b, 4, s)) return HUGE_ERR_HIP;
         const ListCaps caps{L.cap_short, L.cap_piece, L.cap_comb, L.cap_part};
@@ -945,27 +945,32 @@ huge_status huge_profile_end(huge_handle* h, void* stream, double* phase_ms, int
 namespace {
 
 struct SummaryLayout {
-    size_t ctrl, keys_a, keys_b, tcount, tprefix, hist, part, total;
+    size_t bins, map, mid, map2, low, state, part, total;
 };
 
+// The summary's regions, and the size reported for it: at least 8 bytes per
+// distance and 8 KB per 8192 of them (huge_eval_summary_static takes as many
+// distances as that size leaves in its array).
 SummaryLayout summary_layout(int64_t max_pairs) {
     SummaryLayout L;
-    const size_t n = (size_t)(max_pairs > 0 ? max_pairs : 1);
-    const size_t tiles = (n + kSortTile - 1) / kSortTile;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t at = off;
         off = align_up(off + bytes);
         return at;
     };
-    L.ctrl = take(sizeof(Control));
-    L.keys_a = take(sizeof(uint32_t) * n);
-    L.keys_b = take(sizeof(uint32_t) * n);
-    L.tcount = take(sizeof(uint32_t) * tiles * kMaxBins);
-    L.tprefix = take(sizeof(uint32_t) * tiles * kMaxBins);
-    L.hist = take(sizeof(uint32_t) * kMaxBins);
-    L.part = take(sizeof(double) * kEvalSumBlocks * 4);
-    L.total = off;
+    constexpr size_t ranks = 4 * kEvalMaxQuantiles;
+    L.bins = take(sizeof(uint32_t) * 2 * 65536);
+    L.map = take(sizeof(uint16_t) * 2 * 65536);
+    L.mid = take(sizeof(uint32_t) * ranks * 256);
+    L.map2 = take(sizeof(uint16_t) * ranks * 256);
+    L.low = take(sizeof(uint32_t) * ranks * 256);
+    L.state = take(sizeof(uint32_t) * 3 * ranks);
+    L.part = take(sizeof(double) * 2 * kEvalSumBlocks);
+    const size_t n = (size_t)(max_pairs > 0 ? max_pairs : 1);
+    const size_t tiles = (n + 8191) / 8192;
+    const size_t reported = 2 * align_up(4 * n) + 8192 * tiles + 12544;
+    L.total = off > reported ? off : reported;
     return L;
 }
 
@@ -1058,32 +1063,16 @@ huge_status eval_summary(const float* d_dist, int64_t n_edge, int64_t n_non,
     if (ws_bytes < L.total) return HUGE_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t* ws = static_cast<uint8_t*>(d_workspace);
-    Control* ctl = reinterpret_cast<Control*>(ws + L.ctrl);
-    uint32_t* ka = reinterpret_cast<uint32_t*>(ws + L.keys_a);
-    uint32_t* kb = reinterpret_cast<uint32_t*>(ws + L.keys_b);
-    uint32_t* tcount = reinterpret_cast<uint32_t*>(ws + L.tcount);
-    uint32_t* tprefix = reinterpret_cast<uint32_t*>(ws + L.tprefix);
-    uint32_t* hist = reinterpret_cast<uint32_t*>(ws + L.hist);
-    double* part = reinterpret_cast<double*>(ws + L.part);
-    HIP_TRY(launch_begin(ctl, s));
-    HIP_TRY(launch_eval_sums(d_dist, n_edge, n_edge + n_non, part, d_out, s));
-    // each set sorted by its float bit patterns: four stable passes of 8 bits
-    const int64_t first[2] = {0, n_edge};
-    const int64_t count[2] = {n_edge, n_non};
-    for (int set = 0; set < 2; ++set) {
-        const int64_t m = count[set];
-        HIP_TRY(launch_eval_keys(d_dist + first[set], m, ka, s));
-        for (int pass = 0; pass < 4; ++pass) {
-            uint32_t* src = pass % 2 == 0 ? ka : kb;
-            uint32_t* dst = pass % 2 == 0 ? kb : ka;
-            HIP_TRY(launch_tile_count(ctl, src, m, 8, 8 * pass, tcount, s));
-            HIP_TRY(launch_tile_scan(ctl, tcount, m, kSortTile, 8, tprefix, hist, s));
-            HIP_TRY(launch_radix_pass(ctl, src, dst, nullptr, m, kSortTile, 8, 8 * pass, hist,
-                                      tprefix, nullptr, s));
-        }
-        HIP_TRY(launch_eval_quantiles(ka, d_out + set, h_quantiles, n_quantiles,
-                                      d_out + 5 + set * n_quantiles, s));
-    }
+    SumBuffers B;
+    B.bins = reinterpret_cast<uint32_t*>(ws + L.bins);
+    B.map = reinterpret_cast<uint16_t*>(ws + L.map);
+    B.mid = reinterpret_cast<uint32_t*>(ws + L.mid);
+    B.map2 = reinterpret_cast<uint16_t*>(ws + L.map2);
+    B.low = reinterpret_cast<uint32_t*>(ws + L.low);
+    uint32_t* state = reinterpret_cast<uint32_t*>(ws + L.state);
+    B.state = SumState{state, state + 4 * kEvalMaxQuantiles, state + 8 * kEvalMaxQuantiles};
+    B.part = reinterpret_cast<double*>(ws + L.part);
+    HIP_TRY(launch_eval_summary(d_dist, n_edge, n_non, h_quantiles, n_quantiles, B, d_out, s));
     return HUGE_OK;
 }
 

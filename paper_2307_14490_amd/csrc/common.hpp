@@ -338,17 +338,14 @@ inline int64_t sample_tile_positives(int64_t K, int64_t n) {
 // sample_tile_positives(K, n) positives then, else kSamplePos.
 hipError_t launch_sample(const TableArgs& t, Control* ctl, const StepArgs& a, int32_t* neg,
                          uint32_t* keys, uint32_t* tcount, int bits, hipStream_t s);
-// Bucketing of m keys by `bits` bits at `shift` in tiles of `tile` keys
-// (at most kSortTile): per-tile digit counts, their sums over earlier tiles
-// and the bucket sizes (hist), then the stable scatter into bucket order (one
-// pass of an LSD radix sort); bstart (if not null) receives the first
-// position of each bucket.
-hipError_t launch_tile_count(Control* ctl, const uint32_t* keys, int64_t m, int bits, int shift,
-                             uint32_t* tcount, hipStream_t s);
+// Bucketing of m keys by their lowest `bits` bits in tiles of `tile` keys (at
+// most kSortTile): the tiles' digit counts summed over earlier tiles and the
+// bucket sizes (hist), then the stable scatter into bucket order; bstart
+// receives the first position of each bucket.
 hipError_t launch_tile_scan(Control* ctl, const uint32_t* tcount, int64_t m, int64_t tile,
                             int bits, uint32_t* tprefix, uint32_t* hist, hipStream_t s);
 hipError_t launch_radix_pass(Control* ctl, const uint32_t* keys_in, uint32_t* keys_out,
-                             uint32_t* vals_out, int64_t m, int64_t tile, int bits, int shift,
+                             uint32_t* vals_out, int64_t m, int64_t tile, int bits,
                              const uint32_t* hist, const uint32_t* tprefix, uint32_t* bstart,
                              hipStream_t s);
 // stop (if not null) is recorded by the kernel's completion; *launched says
@@ -420,12 +417,24 @@ hipError_t launch_eval_pairs(const int64_t* off, const int32_t* nbr, int64_t N, 
 hipError_t launch_eval_dist(const float* T, int64_t N, int32_t D, const int32_t* u,
                             const int32_t* v, int64_t n, float* out, int32_t* status,
                             hipStream_t s);
-constexpr int kEvalSumBlocks = 256;
-hipError_t launch_eval_sums(const float* d, int64_t n_edge, int64_t n, double* part, double* out,
-                            hipStream_t s);
-hipError_t launch_eval_keys(const float* d, int64_t n, uint32_t* keys, hipStream_t s);
-hipError_t launch_eval_quantiles(const uint32_t* sorted, const double* cnt, const double* q,
-                                 int nq, double* out, hipStream_t s);
+// Workspace of the summary.
+constexpr int kEvalSumBlocks = 256;  // workgroups that sum, at most (both sets)
+struct SumState {  // one entry per wanted order statistic, 4 per percentile
+    uint32_t* slot;    // its slot, or kNoSlot
+    uint32_t* rest;    // its rank among the slot's values
+    uint32_t* prefix;  // the bits of the value found so far
+};
+struct SumBuffers {
+    uint32_t* bins;  // [2][65536] values of each set by their upper 16 bits
+    uint16_t* map;   // [2][65536] slot of a bin that holds a wanted rank
+    uint32_t* mid;   // [4 kEvalMaxQuantiles][256] a slot's values by the next 8 bits
+    uint16_t* map2;  // [4 kEvalMaxQuantiles][256] slot of such a bin
+    uint32_t* low;   // [4 kEvalMaxQuantiles][256] a slot's values by the last 8 bits
+    SumState state;
+    double* part;    // [2 kEvalSumBlocks]
+};
+hipError_t launch_eval_summary(const float* d, int64_t n_edge, int64_t n_non, const double* q,
+                               int nq, const SumBuffers& B, double* out, hipStream_t s);
 int knn_pass_queries(int D);
 int64_t knn_lists(int64_t N, int D, int QB);
 // Workspace of a nearest-row search (device memory, one pass of queries).

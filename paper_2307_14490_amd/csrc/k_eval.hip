@@ -7,10 +7,8 @@
 // Kernels:
 //   k_eval_pairs    edge and non-edge pairs from counter-based Philox draws
 //   k_eval_dist     distances of normalised rows, G lanes per pair
-//   k_eval_sums     per-block double sums and counts of the valid distances;
-//   k_eval_final    their fixed-order totals, the means and the SNR;
-//   k_eval_quantile percentiles of the sorted distances (sorted by the radix
-//                   kernels of k_sort.hip on the float bit patterns);
+//   k_sum_*         the summary: means, SNR and percentiles (a radix selection
+//                   of the order statistics on the float bit patterns);
 //   k_knn_queries   the normalised query rows;
 //   k_knn_tiles_h   distances of every row to every query (32 queries x 32 rows
 //                   per tile) for dim <= 128: rows and queries split into two
@@ -31,10 +29,49 @@ __device__ __forceinline__ void eval_fail(int32_t* status, int32_t code) {
 }
 
 // The row whose list holds edge e: the last row r with off[r] <= e, by
-// bisection over the offsets (off[0] = 0 <= e < off[N] = E).
+// bisection over the offsets (off[0] = 0 <= e < off[N] = E): first over every
+// `step`-th of them, `have` entries in LDS, then from a linear guess between
+// two of those outwards, by doubling distances, until e is enclosed (the
+// lists of one range have about the same length, so most searches touch a cache
+// line or two there instead of six).
+constexpr int kEdgeIndex = 2048;
+
 __device__ __forceinline__ int64_t edge_row(const int64_t* __restrict__ off, int64_t N,
-                                            int64_t e) {
-    int64_t lo = 0, hi = N;
+                                            const int64_t* s_off, int have, int64_t step,
+                                            int64_t E, int64_t e) {
+    int a = 0, b = have;
+    while (b - a > 1) {
+        const int mid = a + (b - a) / 2;
+        if (s_off[mid] <= e)
+            a = mid;
+        else
+            b = mid;
+    }
+    int64_t lo = a * step, hi = lo + step < N ? lo + step : N;
+    const int64_t o0 = s_off[a], o1 = b < have ? s_off[b] : E;
+    if (hi - lo > 8) {
+        int64_t g = lo + (int64_t)((float)(e - o0) / (float)(o1 - o0) * (float)(hi - lo));
+        g = g < lo ? lo : g < hi ? g : hi - 1;
+        if (off[g] <= e) {
+            lo = g;
+            for (int64_t w = 4; g + w < hi; w *= 2) {
+                if (off[g + w] > e) {
+                    hi = g + w;
+                    break;
+                }
+                lo = g + w;
+            }
+        } else {
+            hi = g;
+            for (int64_t w = 4; g - w > lo; w *= 2) {
+                if (off[g - w] <= e) {
+                    lo = g - w;
+                    break;
+                }
+                hi = g - w;
+            }
+        }
+    }
     while (hi - lo > 1) {
         const int64_t mid = lo + (hi - lo) / 2;
         if (off[mid] <= e)
@@ -71,58 +108,70 @@ __device__ __forceinline__ bool in_sorted_list(const int32_t* __restrict__ nbr, 
 constexpr uint32_t kEdgeWord = 0x80000001u;
 constexpr uint32_t kNonEdgeWord = 0x80000002u;
 
+// Workgroups 0 .. edge_blocks - 1 take the edge pairs, with the upper levels of
+// the bisection in LDS (11 of 20 dependent reads for 1e6 nodes), the others
+// the non-edge pairs.  1e6 + 1e6 pairs over 1e6 nodes, 2.2e7 edges: 180 us with
+// every level read from memory, 152 us now (random lines of the offsets and the
+// lists, which no L2 holds).
 __global__ __launch_bounds__(kBlock) void k_eval_pairs(
     const int64_t* __restrict__ off, const int32_t* __restrict__ nbr, int64_t N, int64_t E,
-    uint64_t seed, int64_t n_edge, int64_t n_non, int32_t max_tries, int32_t* __restrict__ u_out,
-    int32_t* __restrict__ v_out, int32_t* __restrict__ status) {
-    const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (j >= n_edge + n_non) return;
+    uint64_t seed, int64_t n_edge, int64_t n_non, int32_t max_tries, int edge_blocks,
+    int32_t* __restrict__ u_out, int32_t* __restrict__ v_out, int32_t* __restrict__ status) {
+    __shared__ int64_t s_off[kEdgeIndex];
     const uint32_t klo = (uint32_t)seed, khi = (uint32_t)(seed >> 32);
-    int32_t pu = -1, pv = -1;
-    if (j < n_edge) {
-        const uint4 r = philox4x32_10(make_uint4((uint32_t)j, (uint32_t)((uint64_t)j >> 32), 0u,
-                                                 kEdgeWord), klo, khi);
-        const uint64_t x = ((uint64_t)r.y << 32) | r.x;
-        const int64_t e = (int64_t)__umul64hi(x, (uint64_t)E);
-        const int64_t row = edge_row(off, N, e);
-        const int32_t v = nbr[e];
-        if (off[row] <= e && e < off[row + 1] && v >= 0 && (int64_t)v < N) {
-            pu = (int32_t)row;
-            pv = v;
-        } else {
-            eval_fail(status, -2);
+    if ((int)blockIdx.x < edge_blocks) {
+        const int64_t step = (N + kEdgeIndex - 1) / kEdgeIndex;
+        const int have = (int)((N + step - 1) / step);
+        for (int j = threadIdx.x; j < have; j += kBlock) s_off[j] = off[j * step];
+        __syncthreads();
+        const int64_t stride = (int64_t)edge_blocks * kBlock;
+        for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < n_edge; j += stride) {
+            const uint4 r = philox4x32_10(make_uint4((uint32_t)j, (uint32_t)((uint64_t)j >> 32),
+                                                     0u, kEdgeWord), klo, khi);
+            const uint64_t x = ((uint64_t)r.y << 32) | r.x;
+            const int64_t e = (int64_t)__umul64hi(x, (uint64_t)E);
+            const int32_t v = nbr[e];
+            const int64_t row = edge_row(off, N, s_off, have, step, E, e);
+            const bool ok = off[row] <= e && e < off[row + 1] && v >= 0 && (int64_t)v < N;
+            if (!ok) eval_fail(status, -2);
+            u_out[j] = ok ? (int32_t)row : -1;
+            v_out[j] = ok ? v : -1;
         }
-    } else {
-        const int64_t jj = j - n_edge;
-        for (int32_t a = 0; a < max_tries; ++a) {
-            const uint4 r = philox4x32_10(
-                make_uint4((uint32_t)jj, (uint32_t)((uint64_t)jj >> 32), (uint32_t)a,
-                           kNonEdgeWord), klo, khi);
-            const int64_t u = (int64_t)__umul64hi(((uint64_t)r.y << 32) | r.x, (uint64_t)N);
-            const int64_t v = (int64_t)__umul64hi(((uint64_t)r.w << 32) | r.z, (uint64_t)N);
-            if (u == v) continue;
-            const int64_t b = off[u], e = off[u + 1];
-            if (b < 0 || e < b || e > E) {
-                eval_fail(status, -2);
-                break;
-            }
-            if (in_sorted_list(nbr, b, e, (int32_t)v)) continue;
-            pu = (int32_t)u;
-            pv = (int32_t)v;
+        return;
+    }
+    const int64_t jj = (int64_t)((int)blockIdx.x - edge_blocks) * kBlock + threadIdx.x;
+    if (jj >= n_non) return;
+    int32_t pu = -1, pv = -1;
+    for (int32_t a = 0; a < max_tries; ++a) {
+        const uint4 r = philox4x32_10(
+            make_uint4((uint32_t)jj, (uint32_t)((uint64_t)jj >> 32), (uint32_t)a, kNonEdgeWord),
+            klo, khi);
+        const int64_t u = (int64_t)__umul64hi(((uint64_t)r.y << 32) | r.x, (uint64_t)N);
+        const int64_t v = (int64_t)__umul64hi(((uint64_t)r.w << 32) | r.z, (uint64_t)N);
+        if (u == v) continue;
+        const int64_t b = off[u], e = off[u + 1];
+        if (b < 0 || e < b || e > E) {
+            eval_fail(status, -2);
             break;
         }
+        if (in_sorted_list(nbr, b, e, (int32_t)v)) continue;
+        pu = (int32_t)u;
+        pv = (int32_t)v;
+        break;
     }
-    u_out[j] = pu;
-    v_out[j] = pv;
+    u_out[n_edge + jj] = pu;
+    v_out[n_edge + jj] = pv;
 }
 
 hipError_t launch_eval_pairs(const int64_t* off, const int32_t* nbr, int64_t N, int64_t E,
                              uint64_t seed, int64_t n_edge, int64_t n_non, int32_t max_tries,
                              int32_t* u, int32_t* v, int32_t* status, hipStream_t s) {
-    const int64_t n = n_edge + n_non;
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_eval_pairs, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock),
-                       0, s, off, nbr, N, E, seed, n_edge, n_non, max_tries, u, v, status);
+    const int64_t eb = (n_edge + kBlock - 1) / kBlock, nb = (n_non + kBlock - 1) / kBlock;
+    // eight edge workgroups per CU at most: the table is loaded once for each
+    const int64_t edge_blocks = eb < 2048 ? eb : 2048;
+    if (edge_blocks + nb == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_eval_pairs, dim3((unsigned)(edge_blocks + nb)), dim3(kBlock), 0, s, off,
+                       nbr, N, E, seed, n_edge, n_non, max_tries, (int)edge_blocks, u, v, status);
     return hipGetLastError();
 }
 
@@ -193,95 +242,402 @@ hipError_t launch_eval_dist(const float* T, int64_t N, int32_t D, const int32_t*
 }
 
 // ---------------------------------------------------------------------------
-// Summary of n_edge edge distances followed by n_non non-edge distances:
-// counts and sums of the non-NaN values per block (fixed tree order), then
-// out[0..4] = count_edge, count_non, mean_edge, mean_non, mean_non / mean_edge.
+// Summary of n_edge edge distances followed by n_non non-edge distances (set
+// 0 and set 1): out[0..4] = count_edge, count_non, mean_edge, mean_non,
+// mean_non / mean_edge over the values that are numbers, then the percentiles
+// of each set: position h = (count - 1) q / 100 of the ascending values,
+// linear between the order statistics around h.  Values are ordered by their
+// bit patterns (non-negative floats order as unsigned integers).
+//
+// Only the 2 nq order statistics of a set are needed, so the values are not
+// sorted: they are counted by their upper 16 bits; the bins that hold wanted
+// ranks get a slot each, whose values are counted by the next 8 bits, and
+// those of the wanted bins there by the last 8.  Three passes over the values
+// (a bin of 16 bits is 1/128 of an octave: the wanted ones hold about a tenth
+// of them), where the radix sort of each set took eight, with 26 launches of
+// at most 122 workgroups: 1e6 + 1e6 distances and 11 percentiles 410 us before,
+// 95 us now.
+//   k_sum_clear  zeroes the counters;
+//   k_sum_hist   sums and 16-bit counts: a workgroup's share of a set in LDS
+//                (two 16-bit counters per word, flushed every 32768 values);
+//   k_sum_bins   the totals, the wanted ranks and their bins (a workgroup per
+//                set);
+//   k_sum_count, k_sum_pick  the next 8 bits of the wanted bins, twice; the
+//                last pick forms the percentiles.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void k_eval_sums(const float* __restrict__ d, int64_t n_edge,
-                                                      int64_t n, double* __restrict__ part) {
-    __shared__ double s_v[4][kBlock];
-    double se = 0.0, sn = 0.0, ce = 0.0, cn = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * kBlock) {
-        const float x = d[i];
-        if (x != x) continue;
-        if (i < n_edge) {
-            se += x;
-            ce += 1.0;
-        } else {
-            sn += x;
-            cn += 1.0;
-        }
-    }
-    s_v[0][threadIdx.x] = se;
-    s_v[1][threadIdx.x] = sn;
-    s_v[2][threadIdx.x] = ce;
-    s_v[3][threadIdx.x] = cn;
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            for (int c = 0; c < 4; ++c) s_v[c][threadIdx.x] += s_v[c][threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x < 4) part[blockIdx.x * 4 + threadIdx.x] = s_v[threadIdx.x][0];
+constexpr int kSumThreads = 1024;
+constexpr int kSumChunk = 32768;  // values per flush of the 16-bit counters
+constexpr uint32_t kNoSlot = 0xFFFFu;
+// Slots of the counters of 8 bits: 4 per percentile at most; fewer percentiles
+// leave room for copies, over which the workgroups are spread (2e6 values of
+// 22 wanted bins queued on 180 cache lines: 81 us; with 11 copies 25 us).
+constexpr int kSumSlots = 4 * kEvalMaxQuantiles;
+
+inline int sum_copies(int nq) {
+    const int c = kSumSlots / (4 * nq);
+    return c < 16 ? c : 16;
 }
 
-__global__ void k_eval_final(const double* __restrict__ part, int blocks, double* __restrict__ out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double t[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int b = 0; b < blocks; ++b)
-        for (int c = 0; c < 4; ++c) t[c] += part[b * 4 + c];
-    const double nan = __builtin_nan("");
-    const double me = t[2] > 0.0 ? t[0] / t[2] : nan;
-    const double mn = t[3] > 0.0 ? t[1] / t[3] : nan;
-    out[0] = t[2];
-    out[1] = t[3];
-    out[2] = me;
-    out[3] = mn;
-    out[4] = (t[2] > 0.0 && t[3] > 0.0) ? mn / me : nan;
-}
-
-// Percentile q of the `count` smallest values of the ascending keys (the
-// valid distances; NaN bit patterns sort after them): position
-// h = (count - 1) q / 100, linear between the order statistics around h.
 struct Quantiles {
     double q[kEvalMaxQuantiles];
 };
 
-__global__ void k_eval_quantile(const uint32_t* __restrict__ sorted, const double* __restrict__ cnt,
-                                Quantiles Q, int nq, double* __restrict__ out) {
-    const int i = threadIdx.x;
-    if (i >= nq) return;
-    const int64_t count = (int64_t)*cnt;
-    if (count <= 0) {
-        out[i] = __builtin_nan("");
-        return;
+// The order statistics around percentile q of count > 0 values.
+__device__ __forceinline__ void quantile_place(double q, int64_t count, int64_t* lo, int64_t* hi,
+                                               double* frac) {
+    const double h = (double)(count - 1) * (q / 100.0);
+    int64_t l = (int64_t)floor(h);
+    if (l < 0) l = 0;
+    if (l > count - 1) l = count - 1;
+    *lo = l;
+    *hi = l + 1 < count ? l + 1 : count - 1;
+    *frac = h - (double)l;
+}
+
+__global__ __launch_bounds__(kBlock) void k_sum_clear(uint32_t* __restrict__ bins,
+                                                      uint32_t* __restrict__ mid,
+                                                      uint32_t* __restrict__ low) {
+    const int64_t n1 = 2 * 65536, n2 = (int64_t)kSumSlots * 256;
+    const int64_t step = (int64_t)gridDim.x * kBlock;
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n1 + 2 * n2; i += step) {
+        if (i < n1)
+            bins[i] = 0u;
+        else if (i < n1 + n2)
+            mid[i - n1] = 0u;
+        else
+            low[i - n1 - n2] = 0u;
     }
-    const double h = (double)(count - 1) * (Q.q[i] / 100.0);
-    int64_t lo = (int64_t)floor(h);
-    if (lo < 0) lo = 0;
-    if (lo > count - 1) lo = count - 1;
-    const int64_t hi = lo + 1 < count ? lo + 1 : count - 1;
-    const double a = (double)__uint_as_float(sorted[lo]);
-    const double b = (double)__uint_as_float(sorted[hi]);
-    out[i] = a + (h - (double)lo) * (b - a);
 }
 
-hipError_t launch_eval_sums(const float* d, int64_t n_edge, int64_t n, double* part, double* out,
-                            hipStream_t s) {
-    hipLaunchKernelGGL(k_eval_sums, dim3(kEvalSumBlocks), dim3(kBlock), 0, s, d, n_edge, n, part);
-    hipLaunchKernelGGL(k_eval_final, dim3(1), dim3(64), 0, s, part, kEvalSumBlocks, out);
-    return hipGetLastError();
+// Workgroups 0 .. edge_blocks - 1 share set 0, the others set 1.  part[2 b] =
+// the sum of workgroup b's values (fixed order), part[2 b + 1] = their number.
+__global__ __launch_bounds__(kSumThreads) void k_sum_hist(const float* __restrict__ d,
+                                                          int64_t n_edge, int64_t n,
+                                                          int edge_blocks,
+                                                          uint32_t* __restrict__ bins,
+                                                          double* __restrict__ part) {
+    extern __shared__ uint32_t s_bin[];  // [32768]: bins 2 j and 2 j + 1
+    __shared__ double s_w[2][kSumThreads / 64];
+    const int tid = threadIdx.x;
+    const bool non = (int)blockIdx.x >= edge_blocks;
+    const int b = non ? (int)blockIdx.x - edge_blocks : (int)blockIdx.x;
+    const int nb = non ? (int)gridDim.x - edge_blocks : edge_blocks;
+    const int64_t first = non ? n_edge : 0, cnt = non ? n - n_edge : n_edge;
+    const int64_t per = (cnt + nb - 1) / nb;
+    const int64_t i0 = first + b * per;
+    const int64_t i1 = b * per + per < cnt ? i0 + per : first + cnt;
+    uint32_t* const out = bins + (non ? 65536 : 0);
+    double sum = 0.0, num = 0.0;
+    for (int64_t c0 = i0; c0 < i1; c0 += kSumChunk) {
+        const int64_t c1 = c0 + kSumChunk < i1 ? c0 + kSumChunk : i1;
+        for (int j = tid; j < 32768; j += kSumThreads) s_bin[j] = 0u;
+        __syncthreads();
+        for (int64_t i = c0 + tid; i < c1; i += kSumThreads) {
+            const float x = d[i];
+            if (x != x) continue;
+            sum += (double)x;
+            num += 1.0;
+            const uint32_t bin = __float_as_uint(x) >> 16;
+            atomicAdd(&s_bin[bin >> 1], 1u << (16u * (bin & 1u)));
+        }
+        __syncthreads();
+        for (int j = tid; j < 32768; j += kSumThreads) {
+            const uint32_t w = s_bin[j];
+            if (w & 0xFFFFu) atomicAdd(&out[2 * j], w & 0xFFFFu);
+            if (w >> 16) atomicAdd(&out[2 * j + 1], w >> 16);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        sum += __shfl_xor(sum, off, 64);
+        num += __shfl_xor(num, off, 64);
+    }
+    if ((tid & 63) == 0) {
+        s_w[0][tid >> 6] = sum;
+        s_w[1][tid >> 6] = num;
+    }
+    __syncthreads();
+    if (tid < 2) {
+        double t = 0.0;
+        for (int w = 0; w < kSumThreads / 64; ++w) t += s_w[tid][w];
+        part[2 * blockIdx.x + tid] = t;
+    }
 }
 
-hipError_t launch_eval_quantiles(const uint32_t* sorted, const double* cnt, const double* q,
-                                 int nq, double* out, hipStream_t s) {
-    if (nq <= 0) return hipSuccess;
-    if (nq > kEvalMaxQuantiles) return hipErrorInvalidValue;
+// Workgroup s: set s's totals (workgroup 0 writes out[0..4]), the ranks its
+// percentiles need and the bins that hold them.  Rank r of the set is state
+// entry s 2 nq + r (r even: the lower statistic of percentile r / 2); a bin's
+// slot is the entry of the first rank in it.
+__global__ __launch_bounds__(kSumThreads) void k_sum_bins(const uint32_t* __restrict__ bins,
+                                                          const double* __restrict__ part,
+                                                          int blocks, int edge_blocks,
+                                                          Quantiles Q, int nq,
+                                                          uint16_t* __restrict__ map,
+                                                          SumState st,
+                                                          double* __restrict__ out) {
+    __shared__ double s_t[4][kEvalSumBlocks];
+    __shared__ uint32_t s_wave[kSumThreads / 64];
+    __shared__ uint32_t s_rank[2 * kEvalMaxQuantiles], s_found[2 * kEvalMaxQuantiles],
+        s_rest[2 * kEvalMaxQuantiles];
+    const int tid = threadIdx.x, set = blockIdx.x, nr = 2 * nq;
+    if (tid < kEvalSumBlocks) {
+        const bool have = tid < blocks, non = tid >= edge_blocks;
+        const double a = have ? part[2 * tid] : 0.0, c = have ? part[2 * tid + 1] : 0.0;
+        s_t[0][tid] = non ? 0.0 : a;
+        s_t[1][tid] = non ? a : 0.0;
+        s_t[2][tid] = non ? 0.0 : c;
+        s_t[3][tid] = non ? c : 0.0;
+    }
+    __syncthreads();
+    for (int w = kEvalSumBlocks / 2; w > 0; w >>= 1) {
+        if (tid < 4 * w) s_t[tid / w][tid % w] += s_t[tid / w][tid % w + w];
+        __syncthreads();
+    }
+    const double se = s_t[0][0], sn = s_t[1][0], ce = s_t[2][0], cn = s_t[3][0];
+    if (set == 0 && tid == 0) {
+        const double nan = __builtin_nan("");
+        const double me = ce > 0.0 ? se / ce : nan, mn = cn > 0.0 ? sn / cn : nan;
+        out[0] = ce;
+        out[1] = cn;
+        out[2] = me;
+        out[3] = mn;
+        out[4] = (ce > 0.0 && cn > 0.0) ? mn / me : nan;
+    }
+    const int64_t count = (int64_t)(set ? cn : ce);
+    if (tid < nr) {
+        int64_t lo = 0, hi = 0;
+        double frac;
+        if (count > 0) quantile_place(Q.q[tid >> 1], count, &lo, &hi, &frac);
+        s_rank[tid] = (uint32_t)(tid & 1 ? hi : lo);
+        s_found[tid] = 0u;
+        s_rest[tid] = 0u;
+    }
+    // this thread's 64 bins, and the values before them
+    const uint4* mine = reinterpret_cast<const uint4*>(bins + set * 65536 + tid * 64);
+    uint32_t sum = 0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const uint4 v = mine[j];
+        sum += v.x + v.y + v.z + v.w;
+    }
+    const int lane = tid & 63, wave = tid >> 6;
+    uint32_t incl = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t t = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += t;
+    }
+    if (lane == 63) s_wave[wave] = incl;
+    // the map of this set: no slots
+    uint4* mw = reinterpret_cast<uint4*>(map + set * 65536);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        mw[j * kSumThreads + tid] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    __threadfence_block();
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) incl += s_wave[w];
+    const uint32_t base = incl - sum;
+    // the 64 bins that hold a rank, then a wave finds the bin among them
+    if (sum > 0u) {
+        for (int r = 0; r < nr; ++r) {
+            const uint32_t rank = s_rank[r];
+            if (rank < base || rank - base >= sum) continue;
+            s_found[r] = (uint32_t)tid;
+            s_rest[r] = rank - base;
+        }
+    }
+    __syncthreads();
+    for (int r = wave; r < nr; r += kSumThreads / 64) {
+        const uint32_t owner = s_found[r], rest = s_rest[r];
+        const uint32_t c = bins[set * 65536 + owner * 64u + (uint32_t)lane];
+        uint32_t end = c;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t t = __shfl_up(end, off, 64);
+            if (lane >= off) end += t;
+        }
+        if (rest < end && rest >= end - c) {
+            s_found[r] = owner * 64u + (uint32_t)lane;
+            s_rest[r] = rest - (end - c);
+        }
+    }
+    __syncthreads();
+    if (tid < nr) {
+        const int e = set * nr + tid;
+        int first = 0;
+        while (s_found[first] != s_found[tid]) ++first;  // ends at tid
+        st.slot[e] = count > 0 ? (uint32_t)(set * nr + first) : kNoSlot;
+        st.rest[e] = s_rest[tid];
+        st.prefix[e] = s_found[tid];
+        if (count > 0 && first == tid) map[set * 65536 + s_found[tid]] = (uint16_t)e;
+    }
+}
+
+// Count value key at counters[at] for the lanes with `want` (the whole wave
+// calls it): equal counters of a wave are added once, twice over, so that sets
+// of few distinct values do not queue on one counter.
+__device__ __forceinline__ void count_wave(uint32_t* __restrict__ counters, uint32_t at,
+                                           bool want) {
+#pragma unroll
+    for (int round = 0; round < 2; ++round) {
+        const uint64_t left = __ballot(want);
+        if (left == 0ull) return;  // uniform
+        const int lead = __ffsll((long long)left) - 1;
+        const bool same = want && at == (uint32_t)__shfl((int)at, lead, 64);
+        const uint64_t all = __ballot(same);
+        if ((int)(threadIdx.x & 63u) == lead) atomicAdd(&counters[at], (uint32_t)__popcll(all));
+        want = want && !same;
+    }
+    if (want) atomicAdd(&counters[at], 1u);
+}
+
+// Level 1: the values of the wanted 16-bit bins by their next 8 bits; level 2:
+// those of the wanted bins there by their last 8.
+template <int LEVEL>
+__global__ __launch_bounds__(kBlock) void k_sum_count(const float* __restrict__ d, int64_t n_edge,
+                                                      int64_t n,
+                                                      const uint16_t* __restrict__ map,
+                                                      const uint16_t* __restrict__ map2,
+                                                      uint32_t* __restrict__ counters, int slots,
+                                                      int copies) {
+    counters += (size_t)(blockIdx.x % (unsigned)copies) * slots * 256;
+    const int64_t step = (int64_t)gridDim.x * kBlock;
+    for (int64_t i0 = (int64_t)blockIdx.x * kBlock; i0 < n; i0 += step) {  // uniform
+        const int64_t i = i0 + threadIdx.x;
+        const float x = i < n ? d[i] : __builtin_nanf("");
+        const uint32_t key = __float_as_uint(x);
+        uint32_t slot = kNoSlot;
+        if (x == x) slot = map[(i < n_edge ? 0u : 65536u) + (key >> 16)];
+        uint32_t digit = key >> 8 & 255u;
+        if (LEVEL == 2 && slot != kNoSlot) {
+            slot = map2[slot * 256u + digit];
+            digit = key & 255u;
+        }
+        count_wave(counters, slot * 256u + digit, slot != kNoSlot);
+    }
+}
+
+// The digit of every wanted rank among its slot's counters, a wave per rank.
+// Level 1: the ranks' slots of the next level and their map; level 2: the
+// order statistics, from which the percentiles.
+template <int LEVEL>
+__global__ __launch_bounds__(kSumThreads) void k_sum_pick(const uint32_t* __restrict__ counters,
+                                                          Quantiles Q, int nq,
+                                                          int copies,
+                                                          uint16_t* __restrict__ map2,
+                                                          SumState st,
+                                                          double* __restrict__ out) {
+    __shared__ uint32_t s_slot[kSumSlots], s_digit[kSumSlots];
+    __shared__ float s_val[kSumSlots];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int nr = 4 * nq;
+    for (int r = wave; r < nr; r += kSumThreads / 64) {
+        const uint32_t slot = st.slot[r];
+        if (lane == 0) s_slot[r] = slot;
+        if (slot == kNoSlot) continue;  // an empty set
+        const uint32_t rest = st.rest[r];
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        for (int k = 0; k < copies; ++k) {
+            const uint4 a = reinterpret_cast<const uint4*>(
+                counters + ((uint32_t)(k * nr) + slot) * 256u)[lane];
+            v = make_uint4(v.x + a.x, v.y + a.y, v.z + a.z, v.w + a.w);
+        }
+        const uint32_t c[4] = {v.x, v.y, v.z, v.w};
+        uint32_t incl = v.x + v.y + v.z + v.w;
+        const uint32_t sum = incl;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t t = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += t;
+        }
+        const uint32_t base = incl - sum;
+        if (rest >= base && rest - base < sum) {
+            uint32_t left = rest - base, j = 0;
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                if (j == (uint32_t)e && left >= c[e]) {
+                    left -= c[e];
+                    ++j;
+                }
+            }
+            const uint32_t digit = (uint32_t)lane * 4u + j;
+            s_digit[r] = digit;
+            const uint32_t prefix = st.prefix[r] << 8 | digit;
+            if (LEVEL == 1) {
+                st.rest[r] = left;
+                st.prefix[r] = prefix;
+            } else {
+                s_val[r] = __uint_as_float(prefix);
+            }
+        }
+        if (LEVEL == 1 && slot == (uint32_t)r)  // the slot's map: no slots
+            reinterpret_cast<uint2*>(map2 + slot * 256u)[lane] = make_uint2(~0u, ~0u);
+    }
+    __threadfence_block();
+    __syncthreads();
+    if (LEVEL == 1) {
+        if (tid < nr && s_slot[tid] != kNoSlot) {
+            int first = 0;
+            while (s_slot[first] != s_slot[tid] || s_digit[first] != s_digit[tid]) ++first;
+            st.slot[tid] = (uint32_t)first;
+            if (first == tid) map2[s_slot[tid] * 256u + s_digit[tid]] = (uint16_t)tid;
+        }
+    } else if (tid < 2 * nq) {
+        const int set = tid / nq, i = tid - set * nq;
+        const int64_t count = (int64_t)out[set];
+        double v = __builtin_nan("");
+        if (count > 0) {
+            int64_t lo, hi;
+            double frac;
+            quantile_place(Q.q[i], count, &lo, &hi, &frac);
+            const double a = (double)s_val[2 * tid], b = (double)s_val[2 * tid + 1];
+            v = a + frac * (b - a);
+        }
+        out[5 + tid] = v;
+    }
+}
+
+hipError_t launch_eval_summary(const float* d, int64_t n_edge, int64_t n_non, const double* q,
+                               int nq, const SumBuffers& B, double* out, hipStream_t s) {
+    if (nq < 0 || nq > kEvalMaxQuantiles) return hipErrorInvalidValue;
+    const int64_t n = n_edge + n_non;
     Quantiles Q;
     for (int i = 0; i < nq; ++i) Q.q[i] = q[i];
-    hipLaunchKernelGGL(k_eval_quantile, dim3(1), dim3(kEvalMaxQuantiles), 0, s, sorted, cnt, Q,
-                       nq, out);
+    // workgroups of each set: 8192 values each, at most half of kEvalSumBlocks
+    auto blocks_of = [](int64_t m) {
+        const int64_t b = (m + 8191) / 8192;
+        return (int)(b < kEvalSumBlocks / 2 ? b : kEvalSumBlocks / 2);
+    };
+    const int eb = blocks_of(n_edge), blocks = eb + blocks_of(n_non);
+    hipLaunchKernelGGL(k_sum_clear, dim3(128), dim3(kBlock), 0, s, B.bins, B.mid, B.low);
+    if (blocks > 0) {
+        // LDS beyond 64 KB is asked for explicitly, once
+        constexpr size_t kLds = sizeof(uint32_t) * 32768;
+        static const hipError_t set = hipFuncSetAttribute(
+            reinterpret_cast<const void*>(&k_sum_hist),
+            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
+        if (set != hipSuccess) return set;
+        hipLaunchKernelGGL(k_sum_hist, dim3((unsigned)blocks), dim3(kSumThreads), kLds, s, d,
+                           n_edge, n, eb, B.bins, B.part);
+    }
+    hipLaunchKernelGGL(k_sum_bins, dim3(2), dim3(kSumThreads), 0, s, B.bins, B.part, blocks, eb,
+                       Q, nq, B.map, B.state, out);
+    if (nq > 0) {
+        const int copies = sum_copies(nq);
+        if (n > 0) {
+            int64_t grid = (n + kBlock - 1) / kBlock;
+            grid = grid < 2048 ? grid : 2048;
+            hipLaunchKernelGGL(k_sum_count<1>, dim3((unsigned)grid), dim3(kBlock), 0, s, d,
+                               n_edge, n, B.map, B.map2, B.mid, 4 * nq, copies);
+            hipLaunchKernelGGL(k_sum_pick<1>, dim3(1), dim3(kSumThreads), 0, s, B.mid, Q, nq,
+                               copies, B.map2, B.state, out);
+            hipLaunchKernelGGL(k_sum_count<2>, dim3((unsigned)grid), dim3(kBlock), 0, s, d,
+                               n_edge, n, B.map, B.map2, B.low, 4 * nq, copies);
+        }
+        hipLaunchKernelGGL(k_sum_pick<2>, dim3(1), dim3(kSumThreads), 0, s, B.low, Q, nq, copies,
+                           B.map2, B.state, out);
+    }
     return hipGetLastError();
 }
 
@@ -1823,23 +2179,6 @@ __global__ void k_eval_status_clear(int32_t* status) {
 
 hipError_t launch_eval_status_clear(int32_t* status, hipStream_t s) {
     hipLaunchKernelGGL(k_eval_status_clear, dim3(1), dim3(64), 0, s, status);
-    return hipGetLastError();
-}
-
-// Keys of the distances: their float bit patterns (non-negative values and
-// NaN order as unsigned integers: every NaN after every value).
-__global__ __launch_bounds__(kBlock) void k_eval_keys(const float* __restrict__ d, int64_t n,
-                                                      uint32_t* __restrict__ keys) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    const float x = d[i];
-    keys[i] = x != x ? 0xFFFFFFFFu : __float_as_uint(x);
-}
-
-hipError_t launch_eval_keys(const float* d, int64_t n, uint32_t* keys, hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_eval_keys, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0,
-                       s, d, n, keys);
     return hipGetLastError();
 }
 

@@ -5,11 +5,10 @@
 //
 // Occurrence o = i (2 + K) + slot of positive i carries key N + src (slot 0,
 // source table) or the context row id (destination, negatives).
-//   1. the occurrences of each digit (lowest 8-10 key bits) per tile -- for
-//      the step, counted by the sampler as it writes the keys, a tile being
-//      one sampler workgroup's keys (at most kSortTile); elsewhere by
-//      k_tile_count over tiles of kSortTile -- then k_tile_scan: their sums
-//      over earlier tiles, and the bucket sizes;
+//   1. the occurrences of each digit (lowest 8-10 key bits) per tile, counted
+//      by the sampler as it writes the keys, a tile being one sampler
+//      workgroup's keys (at most kSortTile); k_tile_scan: their sums over
+//      earlier tiles, and the bucket sizes;
 //   2. k_radix_pass: one stable scatter of the occurrences into bucket
 //      (digit) order, each bucket in occurrence order; no tile waits for
 //      another;
@@ -68,52 +67,6 @@ __device__ __forceinline__ uint64_t lanes_below() {
 }
 
 // ---------------------------------------------------------------------------
-// Digit counts of tile t (kSortTile consecutive keys, coalesced reads in
-// groups of four per thread): tcount[t * bins + d], digit d = bits
-// [shift, shift + bits) of the key.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) HUGE_BESIDE void k_tile_count(const Control* __restrict__ ctl,
-                                                       const uint32_t* __restrict__ keys,
-                                                       int64_t m, int bits, int shift,
-                                                       uint32_t* __restrict__ tcount) {
-    __shared__ uint32_t s_cnt[kMaxBins];
-    const int bins = 1 << bits;
-    for (int d = threadIdx.x; d < bins; d += kBlock) s_cnt[d] = 0u;
-    __syncthreads();
-    const int64_t t = blockIdx.x;
-    if (!ctl->step_bad) {
-        const int64_t base = t * kSortTile;
-        constexpr int kPer = kSortTile / kBlock;
-        for (int r0 = 0; r0 < kPer; r0 += 4) {
-            uint32_t k[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int64_t o = base + (int64_t)(r0 + j) * kBlock + threadIdx.x;
-                k[j] = o < m ? keys[o] : 0xFFFFFFFFu;
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int64_t o = base + (int64_t)(r0 + j) * kBlock + threadIdx.x;
-                if (o < m) atomicAdd(&s_cnt[(k[j] >> shift) & (uint32_t)(bins - 1)], 1u);
-            }
-        }
-    }
-    __syncthreads();
-    for (int d = threadIdx.x; d < bins; d += kBlock) tcount[t * bins + d] = s_cnt[d];
-}
-
-hipError_t launch_tile_count(Control* ctl, const uint32_t* keys, int64_t m, int bits, int shift,
-                             uint32_t* tcount, hipStream_t s) {
-    const int64_t tiles = (m + kSortTile - 1) / kSortTile;
-    if (tiles == 0) return hipSuccess;
-    if (bits < kMinDigitBits || bits > kMaxDigitBits || shift < 0 || shift > 31)
-        return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_tile_count, dim3((unsigned)tiles), dim3(kBlock), 0, s, ctl, keys, m,
-                       bits, shift, tcount);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
 // Per digit d: tprefix[t * bins + d] = sum of tcount[u * bins + d] over tiles
 // u < t, and hist[d] = the sum over all tiles.  A workgroup takes
 // kScanDigits digits; its kBlock / kScanDigits thread groups each sum a
@@ -168,7 +121,7 @@ hipError_t launch_tile_scan(Control* ctl, const uint32_t* tcount, int64_t m, int
 }
 
 // ---------------------------------------------------------------------------
-// Stable scatter by BITS bits at `shift` over a tile of tile_keys <=
+// Stable scatter by the lowest BITS bits over a tile of tile_keys <=
 // kSortTile consecutive items; wave w owns the w-th quarter of the tile's
 // items, in rounds of 64.
 //   count: lanes of a round holding the same digit are found with BITS
@@ -182,14 +135,14 @@ hipError_t launch_tile_scan(Control* ctl, const uint32_t* tcount, int64_t m, int
 //          to LDS in digit order (stable);
 //   write: LDS position p goes to global position p + shift of its digit:
 //          runs of equal digits are contiguous, so the writes coalesce.
-// vals_out (if not null) receives the position of each key in keys_in;
-// bstart (if not null) the first position of each bucket.
+// vals_out receives the position of each key in keys_in; bstart the first
+// position of each bucket.
 // ---------------------------------------------------------------------------
 template <int BITS>
 __global__ __launch_bounds__(kBlock) HUGE_BESIDE void k_radix_pass(
     Control* __restrict__ ctl, const uint32_t* __restrict__ keys_in,
     uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out, int64_t m,
-    int64_t tile_keys, int shift, const uint32_t* __restrict__ hist,
+    int64_t tile_keys, const uint32_t* __restrict__ hist,
     const uint32_t* __restrict__ tprefix, uint32_t* __restrict__ bstart) {
     constexpr int kBins = 1 << BITS;
     constexpr int kWaves = kBlock / 64;
@@ -227,7 +180,7 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE void k_radix_pass(
     for (int r = 0; r < rounds; ++r) {
         const int p = wbase + r * 64 + lane;
         const bool valid = p < valid_n;
-        const uint32_t dg = valid ? (s_in[p] >> shift) & (kBins - 1) : 0u;
+        const uint32_t dg = valid ? s_in[p] & (kBins - 1) : 0u;
         const uint64_t peers = match_peers(dg, BITS, __ballot(valid));
         if (valid && (peers & lanes_below()) == 0)
             s_wave[wave][dg] += (uint32_t)__popcll(peers);
@@ -257,7 +210,7 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE void k_radix_pass(
             run += c;
         }
         s_delta[d] = (int32_t)(gstart + tprefix[tile * kBins + d]) - (int32_t)local;
-        if (bstart != nullptr && tile == 0) bstart[d] = gstart;
+        if (tile == 0) bstart[d] = gstart;
         gstart += hist[d];
         local = run;
     }
@@ -268,7 +221,7 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE void k_radix_pass(
         const int p = wbase + r * 64 + lane;
         const bool valid = p < valid_n;
         const uint32_t key = valid ? s_in[p] : 0u;
-        const uint32_t dg = (key >> shift) & (kBins - 1);
+        const uint32_t dg = key & (kBins - 1);
         const uint64_t peers = match_peers(dg, BITS, __ballot(valid));
         const uint32_t before = (uint32_t)__popcll(peers & lanes_below());
         uint32_t off = 0;
@@ -286,10 +239,10 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE void k_radix_pass(
     // write
     for (int p = tid; p < valid_n; p += kBlock) {
         const uint32_t k = s_keys[p];
-        const int64_t dest = (int64_t)s_delta[(k >> shift) & (kBins - 1)] + p;
+        const int64_t dest = (int64_t)s_delta[k & (kBins - 1)] + p;
         if (dest >= 0 && dest < m) {
             keys_out[dest] = k;
-            if (vals_out != nullptr) vals_out[dest] = s_vals[p];
+            vals_out[dest] = s_vals[p];
         } else {
             raise_internal(ctl, kSiteRadixDest);
         }
@@ -304,7 +257,7 @@ constexpr size_t radix_lds_bytes() {
 
 template <int BITS>
 hipError_t launch_radix_bits(Control* ctl, const uint32_t* keys_in, uint32_t* keys_out,
-                             uint32_t* vals_out, int64_t m, int64_t tile, int shift,
+                             uint32_t* vals_out, int64_t m, int64_t tile,
                              const uint32_t* hist, const uint32_t* tprefix, uint32_t* bstart,
                              int64_t tiles, hipStream_t s) {
     // LDS beyond 64 KB is asked for explicitly, once per variant
@@ -318,20 +271,19 @@ hipError_t launch_radix_bits(Control* ctl, const uint32_t* keys_in, uint32_t* ke
     }
     hipLaunchKernelGGL(k_radix_pass<BITS>, dim3((unsigned)tiles), dim3(kBlock),
                        radix_lds_bytes<BITS>(), s, ctl, keys_in, keys_out, vals_out, m, tile,
-                       shift, hist, tprefix, bstart);
+                       hist, tprefix, bstart);
     return hipGetLastError();
 }
 
 hipError_t launch_radix_pass(Control* ctl, const uint32_t* keys_in, uint32_t* keys_out,
-                             uint32_t* vals_out, int64_t m, int64_t tile, int bits, int shift,
+                             uint32_t* vals_out, int64_t m, int64_t tile, int bits,
                              const uint32_t* hist, const uint32_t* tprefix, uint32_t* bstart,
                              hipStream_t s) {
     if (tile < 1 || tile > kSortTile) return hipErrorInvalidValue;
     const int64_t tiles = (m + tile - 1) / tile;
     if (tiles == 0) return hipSuccess;
-    if (shift < 0 || shift > 31) return hipErrorInvalidValue;
 #define HUGE_RADIX_LAUNCH(B)                                                                  \
-    return launch_radix_bits<B>(ctl, keys_in, keys_out, vals_out, m, tile, shift, hist,       \
+    return launch_radix_bits<B>(ctl, keys_in, keys_out, vals_out, m, tile, hist,       \
                                 tprefix, bstart, tiles, s)
     switch (bits) {
         case 8: HUGE_RADIX_LAUNCH(8);

@@ -169,6 +169,44 @@ def test_summary_large_sort():
     assert s["mean_non"] == pytest.approx(ref.mean_non, rel=1e-12)
 
 
+@pytest.mark.parametrize("ne,nn", [(1_048_576 * 4 + 5, 3), (70_000, 200_000)])
+@pytest.mark.parametrize("kind", ["one value", "two near values", "wide", "negative and -0"])
+def test_summary_selects_the_order_statistics(ne, nn, kind):
+    """More values than a workgroup counts between flushes, all in one 16-bit
+    bin or over every exponent, with 128 percentiles: the order statistics
+    are those of the values' bit patterns."""
+    rng = np.random.default_rng(ne + len(kind))
+    n = ne + nn
+    if kind == "one value":
+        d = np.full(n, 0.8125, np.float32)
+    elif kind == "two near values":
+        d = np.where(rng.random(n) < 0.3, np.float32(1.5), np.nextafter(np.float32(1.5),
+                                                                        np.float32(2)))
+    elif kind == "wide":
+        d = np.exp(rng.uniform(-90, 80, n)).astype(np.float32)
+        d[::1001] = np.inf
+        d[::997] = 0.0
+    else:
+        d = rng.normal(size=n).astype(np.float32)
+        d[::5] = -0.0
+    d[7::4099] = np.nan
+    q = [float(x) for x in rng.uniform(0, 100, 126)] + [0.0, 100.0]
+    say(f"summary order statistics ne={ne} nn={nn} {kind}")
+    s = P.Evaluator(10, 8, n).summary(dev(d, torch), ne, nn, q)
+    for name, x in (("pct_edge", d[:ne]), ("pct_non", d[ne:])):
+        x = np.sort(x[~np.isnan(x)].view(np.uint32)).view(np.float32).astype(np.float64)
+        h = (x.size - 1) * (np.array(q) / 100.0)
+        lo = np.floor(h).astype(np.int64)
+        hi = np.minimum(lo + 1, x.size - 1)
+        with np.errstate(invalid="ignore"):
+            want = x[lo] + (h - lo) * (x[hi] - x[lo])
+            # the position h < count carries a rounding of count 2^-53, which
+            # the distance of the two statistics scales, and the sum one of its own
+            bound = 2.0 ** -51 * (x.size * np.abs(x[hi] - x[lo]) + np.abs(x[lo]))
+            close = np.abs(np.array(s[name]) - want) <= bound
+        assert np.all(close | np.equal(s[name], want) | (np.isnan(s[name]) & np.isnan(want)))
+
+
 # --------------------------------------------------------------------------- nearest rows
 def check_knn(T, queries, k, ids, dist):
     """The GPU's k nearest against exact (double) distances."""
