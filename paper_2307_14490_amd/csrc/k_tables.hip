@@ -250,27 +250,50 @@ hipError_t launch_cocount_weights(const int32_t* hist, int64_t n, int window, co
 }
 
 // ---------------------------------------------------------------------------
-// Loss: fixed-order sum of the per-workgroup partials in double.  A flagged
-// call reports NaN.
+// Loss: fixed-order sum of the per-workgroup partials in double, 16-byte loads
+// with eight in flight per thread (32,768 partials, 256 threads and one load at
+// a time: 49 us; now 6).  A flagged call reports NaN.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void k_loss_final(const Control* ctl,
-                                                       const double* __restrict__ part,
-                                                       int64_t nb, double* out) {
-    __shared__ double s[kBlock];
+constexpr int kLossThreads = 1024;
+
+__global__ __launch_bounds__(kLossThreads) void k_loss_final(const Control* ctl,
+                                                             const double* __restrict__ part,
+                                                             int64_t nb, double* out) {
+    __shared__ double s_w[kLossThreads / 64];
+    const double2* p2 = reinterpret_cast<const double2*>(part);
+    const int64_t n2 = nb / 2;
     double acc = 0.0;
-    for (int64_t j = threadIdx.x; j < nb; j += kBlock) acc += part[j];
-    s[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
-        __syncthreads();
+    int64_t j = threadIdx.x;
+    for (; j + 7 * kLossThreads < n2; j += 8 * kLossThreads) {
+        double2 v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = p2[j + q * kLossThreads];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            acc += v[q].x;
+            acc += v[q].y;
+        }
     }
-    if (threadIdx.x == 0) *out = ctl->step_bad ? __builtin_nan("") : s[0];
+    for (; j < n2; j += kLossThreads) {
+        const double2 v = p2[j];
+        acc += v.x;
+        acc += v.y;
+    }
+    if (threadIdx.x == 0 && (nb & 1)) acc += part[nb - 1];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int w = 0; w < kLossThreads / 64; ++w) t += s_w[w];
+        *out = ctl->step_bad ? __builtin_nan("") : t;
+    }
 }
 
 hipError_t launch_loss_final(Control* ctl, const double* lossp, int64_t blocks, double* out,
                              hipStream_t s) {
-    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kBlock), 0, s, ctl, lossp, blocks, out);
+    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kLossThreads), 0, s, ctl, lossp, blocks, out);
     return hipGetLastError();
 }
 

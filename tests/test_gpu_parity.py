@@ -619,3 +619,33 @@ def test_a_batch_changed_after_its_preparation_leaves_the_next_ones_intact(D, K,
             got = got.float().cpu().numpy().astype(np.float64)
             tol = 1e-6 + (2.0 ** -7 if dtype == "bf16" else 1e-5) * np.abs(want)
             assert np.all(np.abs(got - want) <= tol), step
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D,K,n", [(4, 1, 77), (8, 64, 300), (12, 9, 513), (24, 3, 1), (36, 6, 1000),
+                                   (128, 33, 259), (260, 8, 131), (512, 5, 64), (1024, 17, 33)])
+def test_eval_loss_over_row_layouts_and_negative_blocks(D, K, n, dtype):
+    """One lane of a group draws each negative (several per lane where the
+    group is narrower than a block); a positive with a bad id or count among
+    good ones is reported and gives NaN."""
+    N = 5000
+    rng = np.random.default_rng(D * 100 + K)
+    say(f"eval loss D={D} K={K} n={n} {dtype}")
+    w = rng.random(N) + 0.01 if K % 2 else None
+    tr = P.Trainer(N, D, K, n, seed=9, init_half_width=1.0, alias_weights=w, dtype=dtype)
+    src, dst = (rng.integers(0, N, n).astype(np.int32) for _ in range(2))
+    cc = rng.integers(0, 5, n).astype(np.int32)
+    args = [dev(x, torch) for x in (src, dst, cc)]
+    got = tr.eval_loss(*args, 123456789012).item()
+    thr = alias = None
+    if w is not None:
+        thr, alias = orc.build_alias(w)
+    neg = orc.sample_negatives(9, 123456789012, n, K, N, thr, alias)
+    ref = orc.loss_d(*(t.double().cpu().numpy() for t in (tr.S, tr.T)), src, dst, cc, neg)
+    assert got == pytest.approx(ref, rel=1e-5)
+    assert tr.check() == 0
+    for at, bad, status in ((0, N, -2), (2, -1, -3)):
+        args[at][n - 1] = bad
+        assert np.isnan(tr.eval_loss(*args, 5).item())
+        assert tr.check() == status
+        args[at][n - 1] = 0
