@@ -107,13 +107,33 @@ __global__ __launch_bounds__(kBlock) void k_atomic_gather(TableArgs t, Control* 
     block_loss_a(loss, lossp);
 }
 
+// A row of D floats over the G lanes of a group, lane l owning the elements
+// l, l + G, ...: an atomic instruction of the group then adds to consecutive
+// words, and the atomic unit takes a cache line's words together (with four
+// consecutive words per lane each instruction touched every line of the row
+// with a quarter of its words: a step of 65,536 positives, K = 5, 4e6 x 128,
+// 878 us before and 290 now).
+template <int G, int C>
+__device__ __forceinline__ void load_lanes(float (&x)[4 * C], const float* __restrict__ row,
+                                           int32_t D, int lane) {
+#pragma unroll
+    for (int q = 0; q < 4 * C; ++q) x[q] = lane + q * G < D ? row[lane + q * G] : 0.f;
+}
+
+template <int G, int C>
+__device__ __forceinline__ void add_lanes(float* __restrict__ row, float w,
+                                          const float (&x)[4 * C], int32_t D, int lane) {
+#pragma unroll
+    for (int q = 0; q < 4 * C; ++q)
+        if (lane + q * G < D) unsafeAtomicAdd(row + lane + q * G, w * x[q]);
+}
+
 template <int G, int C>
 __global__ __launch_bounds__(kBlock) void k_atomic_scatter_T(TableArgs t,
                                                              const Control* __restrict__ ctl,
                                                              StepArgs a,
                                                              const int32_t* __restrict__ neg,
                                                              const float* __restrict__ coef) {
-    using IO = RowIO<G, C>;
     if (ctl->step_bad) return;
     constexpr int PPB = kBlock / G;
     const int lane = threadIdx.x % G;
@@ -123,23 +143,13 @@ __global__ __launch_bounds__(kBlock) void k_atomic_scatter_T(TableArgs t,
     if (u < 0 || (int64_t)u >= t.N || v < 0 || (int64_t)v >= t.N) return;
     const int K = t.K;
     const int32_t D = t.D;
-    const int q4 = D >> 2;
-    float4 s[C];
-    IO::load(s, static_cast<const float*>(t.S), u, D, lane);
+    float s[4 * C];
+    load_lanes<G, C>(s, static_cast<const float*>(t.S) + u * (int64_t)D, D, lane);
     for (int j = 0; j <= K; ++j) {
         const int64_t row = j == 0 ? (int64_t)v : (int64_t)neg[i * (int64_t)K + j - 1];
         const float w = -a.lr * coef[i * (int64_t)(1 + K) + j];
         float* p = static_cast<float*>(t.T) + row * (int64_t)D;
-#pragma unroll
-        for (int q = 0; q < C; ++q) {
-            const int jj = lane + q * G;
-            if (jj < q4) {
-                unsafeAtomicAdd(p + 4 * jj + 0, w * s[q].x);
-                unsafeAtomicAdd(p + 4 * jj + 1, w * s[q].y);
-                unsafeAtomicAdd(p + 4 * jj + 2, w * s[q].z);
-                unsafeAtomicAdd(p + 4 * jj + 3, w * s[q].w);
-            }
-        }
+        add_lanes<G, C>(p, w, s, D, lane);
     }
 }
 
@@ -148,7 +158,6 @@ __global__ __launch_bounds__(kBlock) void k_atomic_scatter_S(TableArgs t,
                                                              const Control* __restrict__ ctl,
                                                              StepArgs a,
                                                              const float* __restrict__ gsrc) {
-    using IO = RowIO<G, C>;
     if (ctl->step_bad) return;
     constexpr int PPB = kBlock / G;
     const int lane = threadIdx.x % G;
@@ -157,21 +166,9 @@ __global__ __launch_bounds__(kBlock) void k_atomic_scatter_S(TableArgs t,
     const int32_t u = a.src[i];
     if (u < 0 || (int64_t)u >= t.N) return;
     const int32_t D = t.D;
-    const int q4 = D >> 2;
-    float4 g[C];
-    IO::load(g, gsrc, i, D, lane);
-    float* p = static_cast<float*>(t.S) + (int64_t)u * D;
-    const float w = -a.lr;
-#pragma unroll
-    for (int q = 0; q < C; ++q) {
-        const int jj = lane + q * G;
-        if (jj < q4) {
-            unsafeAtomicAdd(p + 4 * jj + 0, w * g[q].x);
-            unsafeAtomicAdd(p + 4 * jj + 1, w * g[q].y);
-            unsafeAtomicAdd(p + 4 * jj + 2, w * g[q].z);
-            unsafeAtomicAdd(p + 4 * jj + 3, w * g[q].w);
-        }
-    }
+    float g[4 * C];
+    load_lanes<G, C>(g, gsrc + i * (int64_t)D, D, lane);
+    add_lanes<G, C>(static_cast<float*>(t.S) + (int64_t)u * D, -a.lr, g, D, lane);
 }
 
 // Loss of a batch at the current tables; validates ids and counts itself and
