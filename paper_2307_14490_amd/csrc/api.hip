@@ -381,10 +381,11 @@ hipError_t side_end(huge_handle* h, hipStream_t s) {
 
 // The preparation of a batch into the next slot, on stream s: validation,
 // negatives and keys, tile counts and prefixes, radix pass, grouping
-// (launches only; arguments checked).
+// (launches only; arguments checked).  beside: another batch's apply may run
+// at the same time (a preparation of its own).
 huge_status stage_prepare(huge_handle* h, const int32_t* src, const int32_t* dst,
                           const int32_t* cc, const float* w, int64_t n, uint64_t first_pos,
-                          hipStream_t s) {
+                          bool beside, hipStream_t s) {
     const int slot = (int)(h->prepared % kSlots);
     const SlotLayout& SL = h->lay.slot[slot];
     const Layout& L = h->lay;
@@ -436,7 +437,7 @@ huge_status stage_prepare(huge_handle* h, const int32_t* src, const int32_t* dst
                              at<uint4>(h, SL.shorts),
                              at<uint4>(h, SL.pieces), at<uint4>(h, SL.combs),
                              at<uint32_t>(h, SL.ccount), at<uint4>(h, SL.bcount), caps,
-                             at<uint32_t>(h, SL.wstats), 1 << bits, h->key_bits,
+                             at<uint32_t>(h, SL.wstats), 1 << bits, h->key_bits, beside,
                              h->ready[slot], &ready_recorded, s));
         if (!prof_mark(h, b, 5, s)) return HUGE_ERR_HIP;
     } else {
@@ -588,7 +589,7 @@ huge_status train_step(huge_handle* h, const int32_t* d_src, const int32_t* d_ds
     if (!isfinite(lr)) return HUGE_ERR_INVALID_ARG;
     if (h->prepared != h->applied) return HUGE_ERR_INVALID_ARG;  // a prepared batch is pending
     hipStream_t s = static_cast<hipStream_t>(stream);
-    st = stage_prepare(h, d_src, d_dst, d_cc, d_w, n, first_pos_index, s);
+    st = stage_prepare(h, d_src, d_dst, d_cc, d_w, n, first_pos_index, false, s);
     if (st != HUGE_OK) return st;
     return apply_next(h, lr, d_loss_sum, s);
 }
@@ -599,7 +600,7 @@ huge_status prepare_step(huge_handle* h, const int32_t* d_src, const int32_t* d_
     huge_status st = check_batch_args(h, d_src, d_dst, d_cc ? (const void*)d_cc : d_w, n);
     if (st != HUGE_OK) return st;
     if (h->prepared - h->applied >= kMaxPending) return HUGE_ERR_INVALID_ARG;
-    return stage_prepare(h, d_src, d_dst, d_cc, d_w, n, first_pos_index,
+    return stage_prepare(h, d_src, d_dst, d_cc, d_w, n, first_pos_index, true,
                          static_cast<hipStream_t>(stream));
 }
 

@@ -17,33 +17,29 @@ constexpr int kMaxDigitBits = 10;      // the same in every pass of a sort
 constexpr int kMaxBins = 1 << kMaxDigitBits;
 constexpr int kMaxPasses = 4;          // keys < 2^32
 constexpr int kSortTile = 8192;        // keys per radix-pass tile
-// Every kernel of the grouping (tile counts, their prefixes, the radix pass,
-// the per-bucket grouping) runs in workgroups of kBlock threads within the
-// HUGE_BESIDE register budget, so that it runs beside the fused step without
-// evicting any of the step's waves.
+// The kernels of the grouping before the per-bucket one (sampling with the tile
+// counts, their prefixes, the radix pass) run in workgroups of kBlock threads
+// within the HUGE_BESIDE register budget, so that they run beside the fused
+// step without evicting any of the step's waves.
 constexpr int kScanDigits = 4;         // digits per tile-prefix workgroup
 // Register budget of the kernels that run beside the fused step: at most 64
 // VGPRs (the budget of eight waves per SIMD).  With the fused step at five
 // waves of 88 VGPRs per SIMD (440 of 512), one such wave per SIMD fits beside
 // them.
 #define HUGE_BESIDE __attribute__((amdgpu_waves_per_eu(8, 8)))
-// The same at 72 VGPRs (seven waves per SIMD), the most that fits beside the
-// fused step's five waves, for the per-bucket grouping, which needs them.
-#define HUGE_BESIDE_72 __attribute__((amdgpu_waves_per_eu(7, 7)))
-// Per-bucket grouping (k_group): chunks of kGroupChunk keys (kGroupItems
-// consecutive keys per thread); an LDS hash table of kGroupSlots slots counts
-// the repeated keys of a key range; a range with more than 3/4 of the slots
-// in distinct keys is split by further hash bits.  Where a bucket's keys
-// differ in at most kBitmapBits bits, an LDS bitmap of them first marks the
-// keys that occur more than once, and only those enter the table.  The first
-// pass copies up to kGroupCacheKeys keys and kGroupCacheVals occurrence
-// indices of a bucket to LDS; later passes read them there.
-constexpr int kGroupItems = 4;
-constexpr int kGroupChunk = kBlock * kGroupItems;     // 1024 keys per chunk
+// Per-bucket grouping (k_group): chunks of kGroupChunk keys; an LDS hash table of at most
+// 2^kGroupTableBits slots counts the repeated keys of a key range; a range with
+// more than 3/4 of the slots in distinct keys is split by further hash bits.
+// Where a bucket's keys differ in at most kBitmapBits bits, an LDS bitmap of
+// them first marks the keys that occur more than once, and only those enter
+// the table.  The first pass copies the keys and occurrence indices of a bucket
+// to LDS where they fit; later passes read them there.
+constexpr int kLdsBytes = 160 * 1024;                 // LDS of a CU
+constexpr int kGroupChunk = 1024;                     // keys per chunk
 constexpr int kGroupTableBits = 12;
-constexpr int kGroupSlots = 1 << kGroupTableBits;     // 4096 slots, 32 KB
-constexpr int kGroupCacheKeys = 8192;                 // 32 KB
-constexpr int kGroupCacheVals = 4096;                 // 16 KB
+constexpr int kMinTableBits = 11;                     // 7/8 of it holds a chunk of new keys
+static_assert((1 << kMinTableBits) / 8 * 7 >= kGroupChunk, "a chunk fits an empty table");
+constexpr int kGroupCacheMost = 8192;                 // keys cached, at most
 constexpr int kBitmapBits = 18;        // two 32 KB bitmaps (seen, repeated)
 // Embedding evaluation
 constexpr int kEvalMaxQuantiles = 128;  // percentiles per summary
@@ -348,13 +344,14 @@ hipError_t launch_radix_pass(Control* ctl, const uint32_t* keys_in, uint32_t* ke
                              uint32_t* vals_out, int64_t m, int64_t tile, int bits,
                              const uint32_t* hist, const uint32_t* tprefix, uint32_t* bstart,
                              hipStream_t s);
-// stop (if not null) is recorded by the kernel's completion; *launched says
+// beside: the kernel is to run beside another one (fewer threads).  stop (if
+// not null) is recorded by the kernel's completion; *launched says
 // whether a kernel was launched (an empty batch launches none).
 hipError_t launch_group(Control* ctl, const uint32_t* keys, const uint32_t* vals, int64_t m,
                         int64_t N, const uint32_t* hist, const uint32_t* bstart, int32_t* info,
                         uint32_t* occ, uint4* shorts, uint4* pieces, uint4* combs, uint32_t* ccount,
                         uint4* bcount, ListCaps caps, uint32_t* wstats, int bins, int key_bits,
-                        hipEvent_t stop, bool* launched, hipStream_t s);
+                        bool beside, hipEvent_t stop, bool* launched, hipStream_t s);
 // Negative k of positive i: neg[i * neg_stride + k].
 // Occurrences of repeated rows: what the fused step leaves and the finish
 // kernel sums.

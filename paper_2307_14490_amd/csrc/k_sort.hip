@@ -17,17 +17,20 @@
 //      (inside the bucket's own range of positions), writes the slot of each
 //      of its occurrences, in occurrence order, to info[o], and lists the
 //      repeated rows, and by slot their occurrences, for the finish kernel.
-// All of them run beside the previous batch's fused step: 256-thread
+// All of them can run beside the previous batch's fused step: 256-thread
 // workgroups whose waves hold few registers (one item per thread at a time,
 // loads issued in small groups) and work mostly in LDS.
+#include <math.h>
+
 #include "common.hpp"
 #include "device.hpp"
 
 namespace huge {
 
-// Exclusive sum of one value per thread over the workgroup (kBlock threads);
-// *total receives the sum.  Synchronises; s_tmp holds kBlock / 64 words and
+// Exclusive sum of one value per thread over the workgroup (THREADS threads);
+// *total receives the sum.  Synchronises; s_tmp holds THREADS / 64 words and
 // may be reused after the next barrier.
+template <int THREADS = kBlock>
 __device__ __forceinline__ uint32_t block_excl(uint32_t v, uint32_t* s_tmp, uint32_t* total) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     uint32_t incl = v;
@@ -40,7 +43,7 @@ __device__ __forceinline__ uint32_t block_excl(uint32_t v, uint32_t* s_tmp, uint
     __syncthreads();
     uint32_t add = 0, all = 0;
 #pragma unroll
-    for (int w = 0; w < kBlock / 64; ++w) {
+    for (int w = 0; w < THREADS / 64; ++w) {
         const uint32_t x = s_tmp[w];
         if (w < wave) add += x;
         all += x;
@@ -297,15 +300,15 @@ hipError_t launch_radix_pass(Control* ctl, const uint32_t* keys_in, uint32_t* ke
 // ---------------------------------------------------------------------------
 // Grouping of one bucket (its items are in occurrence order).
 //
-// A first pass copies the bucket's keys (up to kGroupCacheKeys) and
-// occurrence indices (up to kGroupCacheVals) to LDS, in one round of loads.
+// A first pass copies the keys and occurrence indices of a bucket of at most
+// `cap` items to LDS, in one round of loads.
 // With BM (the bucket's keys differ in at most kBitmapBits bits above the
 // bucket digit) the same pass sets, per item, the key's bit in an LDS bitmap
 // and, where it was set already, the key's bit in a second bitmap of
 // repeated keys; it also counts the bucket's distinct source and destination
 // rows.  Only keys marked repeated take part in what follows.
 //
-// The (repeated) keys are counted in an LDS hash table of kGroupSlots slots
+// The (repeated) keys are counted in an LDS hash table of 2^most_tbits slots
 // (linear probing).  A bucket with more than 3/4 of the slots in distinct
 // keys is split into key ranges by further hash bits, each range counted and
 // placed in turn (depth first over the binary tree of ranges); at depth 32 a
@@ -343,36 +346,82 @@ __device__ __forceinline__ bool in_range(uint32_t key, int level, uint32_t idx) 
     return level == 0 || ((key * 0xC2B2AE35u) >> (32 - level)) == idx;
 }
 
-// Dynamic LDS words of k_group<BM>.
-template <bool BM>
-constexpr size_t group_lds_words() {
-    return 2 * kGroupSlots + kGroupCacheKeys + kGroupCacheVals + kGroupChunk +
-           (BM ? 2 * ((1 << kBitmapBits) / 32) : 0);
+// LDS of a grouping workgroup, chosen per batch: `cap` keys and occurrence
+// indices of a bucket in LDS, a table of 2^tbits slots, the bitmaps as wide as
+// the keys need.  A bucket's steps are short and full of barriers, so the
+// kernel alone lives on several workgroups per CU: the most (4 .. 1) for which
+// the LDS left holds the batch's average bucket with six standard deviations
+// of an even spread to spare.  (Beside the fused step one workgroup per CU fits
+// by its registers, whatever its LDS.)
+struct GroupShape {
+    int cap;    // keys and indices cached, a multiple of 64
+    int tbits;  // table slots: enough for the repeated keys of an average
+                // bucket (half its items) at a load of 3/4
+    size_t words;  // dynamic LDS
+};
+
+inline GroupShape group_shape(int64_t m, int bins, int sub_bits) {
+    const bool bm = sub_bits <= kBitmapBits;
+    const size_t bits = bm ? 2 * (size_t)(sub_bits > 5 ? 1 << (sub_bits - 5) : 1) : 0;
+    const double avg = (double)m / bins;
+    const double want = avg + 6.0 * sqrt(avg) + 64.0;
+    int tb = kMinTableBits;
+    while (tb < kGroupTableBits && (double)(1 << tb) < 0.75 * want) ++tb;
+    const size_t fixed = 2 * ((size_t)1 << tb) + kGroupChunk + bits;
+    GroupShape g{64, tb, 0};
+    for (int per_cu = 4; per_cu >= 1; --per_cu) {
+        // the statically allocated LDS of the kernel is below 1 KB
+        const size_t budget = (kLdsBytes / per_cu - 1024) / sizeof(uint32_t);
+        if (budget < fixed + 2 * 64) continue;
+        size_t cap = (budget - fixed) / 2 / 64 * 64;
+        if (cap > (size_t)kGroupCacheMost) cap = kGroupCacheMost;
+        g.cap = (int)cap;
+        if ((double)cap >= want) break;
+    }
+    g.words = fixed + 2 * (size_t)g.cap;
+    return g;
 }
 
-template <bool BM>
-__global__ __launch_bounds__(kBlock) HUGE_BESIDE_72 void k_group(
+// THREADS = kBlock runs beside another batch's fused step; a step that waits
+// for its own grouping runs it alone with kGroupAlone threads.  Both keep the
+// registers they need (93 and 109): within 72 a few values were spilled to
+// scratch, which cost more than the waves of the fused step that now make room
+// for it.  With 148 KB of LDS, 256 threads and 72 VGPRs for all, then as now:
+// sequential steps of 1,024 positives 43.5 -> 40.9 us, 65,536 (medium)
+// 192 -> 183, 131,072 with K = 31 1548 -> 1436 (buckets of 4200 keys found no
+// room for their indices), 100,003 of a power-law graph with K = 20
+// 1373 -> 1318; six pipelined steps of 262,144 fp32 3102 -> 3062, bf16
+// 2179 -> 2008.  256 and 1024 threads alone: 42.3, 189, 1481, 1346 and 47.4,
+// 191, 1455, 1358; 512 beside: 3108 and 2073.
+constexpr int kGroupAlone = 512;
+
+template <bool BM, int THREADS>
+__global__ __launch_bounds__(THREADS)
+__attribute__((amdgpu_waves_per_eu(4, 4))) void k_group(
     Control* __restrict__ ctl, const uint32_t* __restrict__ keys,
     const uint32_t* __restrict__ vals, int64_t m, int64_t N, const uint32_t* __restrict__ hist,
     const uint32_t* __restrict__ bstart, int32_t* __restrict__ info,
     uint32_t* __restrict__ occ, uint4* __restrict__ shorts, uint4* __restrict__ pieces, uint4* __restrict__ combs, uint32_t* __restrict__ ccount,
     uint4* __restrict__ bcount, ListCaps caps, uint32_t* __restrict__ wstats, int bins, int shift,
-    int sub_bits) {
-    constexpr int kBitWords = (1 << kBitmapBits) / 32;           // words of one bitmap
-    // The large arrays live in dynamic LDS (group_lds_words<BM>() words): the
-    // compiler then keeps to the HUGE_BESIDE register budget, which a static
-    // size above a fifth of the LDS would let it exceed.
+    int sub_bits, int cap, int most_tbits) {
+    constexpr int ITEMS = kGroupChunk / THREADS;  // consecutive keys of a thread
+    static_assert(ITEMS * THREADS == kGroupChunk, "whole keys per thread");
+    // words of one bitmap
+    const uint32_t bit_words = sub_bits > 5 ? 1u << (sub_bits - 5) : 1u;
+    // The large arrays live in dynamic LDS (group_shape): the compiler then
+    // keeps to the HUGE_BESIDE register budget, which a static size above a
+    // fifth of the LDS would let it exceed.
     extern __shared__ uint32_t s_dyn[];
-    uint32_t* const s_key = s_dyn;                          // [kGroupSlots]
-    uint32_t* const s_cnt = s_key + kGroupSlots;            // count; after emit, kRepFlag | next slot
-    uint32_t* const s_ckey = s_cnt + kGroupSlots;           // [kGroupCacheKeys]
-    uint32_t* const s_cval = s_ckey + kGroupCacheKeys;      // [kGroupCacheVals]
+    uint32_t* const s_key = s_dyn;                          // [2^most_tbits]
+    uint32_t* const s_cnt = s_key + (1 << most_tbits);      // count; after emit, kRepFlag | next slot
+    uint32_t* const s_ckey = s_cnt + (1 << most_tbits);     // [cap]
+    uint32_t* const s_cval = s_ckey + cap;                  // [cap]
     // repeated items of a chunk in order: their table slot, then their
-    // duplicate-buffer slot
-    uint32_t* const s_rep = s_cval + kGroupCacheVals;       // [kGroupChunk]
-    uint32_t* const s_seen = s_rep + kGroupChunk;           // [kBitWords] with BM
-    uint32_t* const s_dup = s_seen + kBitWords;             // [kBitWords] with BM
-    __shared__ uint32_t s_tmp[6][kBlock / 64];
+    // duplicate slot
+    uint32_t* const s_rep = s_cval + cap;                   // [kGroupChunk]
+    uint32_t* const s_seen = s_rep + kGroupChunk;           // [bit_words] with BM
+    uint32_t* const s_dup = s_seen + bit_words;             // [bit_words] with BM
+    __shared__ uint32_t s_tmp[6][THREADS / 64];
     __shared__ uint32_t s_distinct, s_fail, s_nrep;
     __shared__ uint32_t s_stat[3];
     __shared__ uint32_t s_rbase[2];
@@ -394,51 +443,51 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE_72 void k_group(
         if (tid == 0) bcount[b] = make_uint4(0u, 0u, 0u, 0u);
         continue;
     }
-    const bool keys_cached = n <= (uint32_t)kGroupCacheKeys;
-    const bool vals_cached = n <= (uint32_t)kGroupCacheVals;
-    // the kGroupItems keys of this thread in chunk c0
+    const bool cached = n <= (uint32_t)cap;
+    // the ITEMS keys of this thread in chunk c0
     // (after the compaction: of the first nw items)
-    auto load_keys = [&](uint32_t c0, uint32_t nlim, uint32_t (&k)[kGroupItems]) {
-        const uint32_t e0 = c0 + (uint32_t)(tid * kGroupItems);
-        if (keys_cached) {
+    auto load_keys = [&](uint32_t c0, uint32_t nlim, uint32_t (&k)[ITEMS]) {
+        const uint32_t e0 = c0 + (uint32_t)(tid * ITEMS);
+        if (cached) {
 #pragma unroll
-            for (int r = 0; r < kGroupItems; ++r) k[r] = e0 + r < nlim ? s_ckey[e0 + r] : 0u;
+            for (int r = 0; r < ITEMS; ++r) k[r] = e0 + r < nlim ? s_ckey[e0 + r] : 0u;
         } else {
             const uint32_t* kp = keys + s0 + e0;
 #pragma unroll
-            for (int r = 0; r < kGroupItems; ++r) k[r] = e0 + r < nlim ? kp[r] : 0u;
+            for (int r = 0; r < ITEMS; ++r) k[r] = e0 + r < nlim ? kp[r] : 0u;
         }
     };
 
     // ---- copy to LDS; repeated keys (BM) ----
     // the bit of key k is bit (k >> shift) of the bucket's bitmap; a key
     // beyond the bitmap cannot occur (sub_bits <= kBitmapBits)
-    const uint32_t bit_words = sub_bits > 5 ? 1u << (sub_bits - 5) : 1u;
     auto repeated = [&](uint32_t k) -> bool {
         if (!BM) return true;
         const uint32_t sub = k >> shift;
         return sub >> 5 < bit_words && ((s_dup[sub >> 5] >> (sub & 31u)) & 1u);
     };
     if (BM) {
-        for (uint32_t j = tid; j < bit_words; j += kBlock) {
+        for (uint32_t j = tid; j < bit_words; j += THREADS) {
             s_seen[j] = 0u;
             s_dup[j] = 0u;
         }
     }
-    if (keys_cached || vals_cached) {  // coalesced: item j + q kBlock by thread j
-        for (uint32_t e0 = 0; e0 < n; e0 += 4 * kBlock) {
+    if (cached) {  // coalesced: item j + q THREADS by thread j
+        for (uint32_t e0 = 0; e0 < n; e0 += 4 * THREADS) {
             uint32_t kk[4], vv[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const uint32_t e = e0 + (uint32_t)(q * kBlock + tid);
-                kk[q] = e < n && keys_cached ? keys[s0 + e] : 0u;
-                vv[q] = e < n && vals_cached ? vals[s0 + e] : 0u;
+                const uint32_t e = e0 + (uint32_t)(q * THREADS + tid);
+                kk[q] = e < n ? keys[s0 + e] : 0u;
+                vv[q] = e < n ? vals[s0 + e] : 0u;
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const uint32_t e = e0 + (uint32_t)(q * kBlock + tid);
-                if (e < n && keys_cached) s_ckey[e] = kk[q];
-                if (e < n && vals_cached) s_cval[e] = vv[q];
+                const uint32_t e = e0 + (uint32_t)(q * THREADS + tid);
+                if (e < n) {
+                    s_ckey[e] = kk[q];
+                    s_cval[e] = vv[q];
+                }
             }
         }
     }
@@ -446,11 +495,11 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE_72 void k_group(
     if (BM) {
         uint32_t nS = 0, nT = 0, nR = 0;
         for (uint32_t c0 = 0; c0 < n; c0 += kGroupChunk) {
-            uint32_t k[kGroupItems];
+            uint32_t k[ITEMS];
             load_keys(c0, n, k);
 #pragma unroll 1
-            for (int r = 0; r < kGroupItems; ++r) {
-                const uint32_t e = c0 + (uint32_t)(tid * kGroupItems + r);
+            for (int r = 0; r < ITEMS; ++r) {
+                const uint32_t e = c0 + (uint32_t)(tid * ITEMS + r);
                 if (e >= n) continue;
                 const uint32_t sub = k[r] >> shift, w = sub >> 5, bit = 1u << (sub & 31u);
                 if (w >= bit_words) {
@@ -482,29 +531,29 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE_72 void k_group(
     // lower position, so no item is overwritten before it is read), and
     // the hash table is sized to them.
     uint32_t nw = n;  // items the count and the placement go through
-    int tbits = kGroupTableBits;
-    if (BM && any && keys_cached && vals_cached) {
+    int tbits = most_tbits;
+    if (BM && any && cached) {
         uint32_t out = 0;
         for (uint32_t c0 = 0; c0 < n; c0 += kGroupChunk) {
-            uint32_t kk[kGroupItems], vv[kGroupItems];
+            uint32_t kk[ITEMS], vv[ITEMS];
             uint32_t mask = 0u, cnt = 0u;
-            const uint32_t e0 = c0 + (uint32_t)(tid * kGroupItems);
+            const uint32_t e0 = c0 + (uint32_t)(tid * ITEMS);
 #pragma unroll
-            for (int r = 0; r < kGroupItems; ++r) {
+            for (int r = 0; r < ITEMS; ++r) {
                 kk[r] = e0 + r < n ? s_ckey[e0 + r] : 0u;
                 vv[r] = e0 + r < n ? s_cval[e0 + r] : 0u;
             }
 #pragma unroll 1
-            for (int r = 0; r < kGroupItems; ++r) {
+            for (int r = 0; r < ITEMS; ++r) {
                 if (e0 + r < n && repeated(kk[r])) {
                     mask |= 1u << r;
                     ++cnt;
                 }
             }
             uint32_t total;
-            uint32_t p = out + block_excl(cnt, s_tmp[0], &total);  // synchronises
+            uint32_t p = out + block_excl<THREADS>(cnt, s_tmp[0], &total);  // synchronises
 #pragma unroll 1
-            for (int r = 0; r < kGroupItems; ++r) {
+            for (int r = 0; r < ITEMS; ++r) {
                 if (mask & (1u << r)) {
                     s_ckey[p] = kk[r];
                     s_cval[p] = vv[r];
@@ -516,7 +565,7 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE_72 void k_group(
         }
         nw = out;
         tbits = 6;
-        while (tbits < kGroupTableBits && (1u << tbits) < 2u * nw) ++tbits;
+        while (tbits < most_tbits && (1u << tbits) < 2u * nw) ++tbits;
     }
     const uint32_t tsize = 1u << tbits;
     const uint32_t tmask = tsize - 1u;
@@ -545,7 +594,7 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE_72 void k_group(
     while (any) {
         // ---- count ----
 #pragma unroll 1
-        for (uint32_t q = tid; q < tsize; q += kBlock) {
+        for (uint32_t q = tid; q < tsize; q += THREADS) {
             s_key[q] = kEmptyKey;
             s_cnt[q] = 0u;
         }
@@ -562,12 +611,12 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE_72 void k_group(
                 over = true;
                 break;
             }
-            uint32_t k[kGroupItems];
+            uint32_t k[ITEMS];
             load_keys(c0, nw, k);
             uint32_t fresh = 0u;
 #pragma unroll 1
-            for (int r = 0; r < kGroupItems; ++r) {
-                const uint32_t e = c0 + (uint32_t)(tid * kGroupItems + r);
+            for (int r = 0; r < ITEMS; ++r) {
+                const uint32_t e = c0 + (uint32_t)(tid * ITEMS + r);
                 if (e >= nw || !in_range(k[r], level, ridx) || !repeated(k[r])) continue;
                 uint32_t h = slot_hash(k[r], tbits);
                 bool found = false;
@@ -612,12 +661,12 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE_72 void k_group(
 
         {
         // ---- emit ----
-        // this thread's table slots (tid, tid + kBlock, ...; conflict-free
+        // this thread's table slots (tid, tid + THREADS, ...; conflict-free
         // LDS reads): statistics, slot counts, record counts; slots and
         // records are handed out thread by thread
         uint32_t nS = 0, nT = 0, nrep = 0, nshort = 0, npiece = 0, ncomb = 0, npart = 0;
 #pragma unroll 1
-        for (uint32_t q = tid; q < tsize; q += kBlock) {
+        for (uint32_t q = tid; q < tsize; q += THREADS) {
             const uint32_t k = s_key[q];
             if (k == kEmptyKey) continue;
             if (!BM) {  // with BM the first pass counted the rows
@@ -639,11 +688,11 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE_72 void k_group(
             }
         }
         uint32_t t_rep, t_short, t_piece, t_comb, t_part;
-        const uint32_t x_rep = block_excl(nrep, s_tmp[0], &t_rep);
-        const uint32_t x_short = block_excl(nshort, s_tmp[1], &t_short);
-        const uint32_t x_piece = block_excl(npiece, s_tmp[2], &t_piece);
-        const uint32_t x_comb = block_excl(ncomb, s_tmp[3], &t_comb);
-        const uint32_t x_part = block_excl(npart, s_tmp[4], &t_part);
+        const uint32_t x_rep = block_excl<THREADS>(nrep, s_tmp[0], &t_rep);
+        const uint32_t x_short = block_excl<THREADS>(nshort, s_tmp[1], &t_short);
+        const uint32_t x_piece = block_excl<THREADS>(npiece, s_tmp[2], &t_piece);
+        const uint32_t x_comb = block_excl<THREADS>(ncomb, s_tmp[3], &t_comb);
+        const uint32_t x_part = block_excl<THREADS>(npart, s_tmp[4], &t_part);
         if (nS) atomicAdd(&s_stat[0], nS);
         if (nT) atomicAdd(&s_stat[1], nT);
         // the range's short runs and pieces are appended to the batch's lists
@@ -674,7 +723,7 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE_72 void k_group(
             uint32_t is = b_short + x_short, ip = b_piece + x_piece;
             uint32_t ic = r_comb + nb_comb + x_comb, ia = r_part + nb_part + x_part;
 #pragma unroll 1
-            for (uint32_t q = tid; q < tsize; q += kBlock) {
+            for (uint32_t q = tid; q < tsize; q += THREADS) {
                 const uint32_t k = s_key[q];
                 const uint32_t c = s_cnt[q];
                 if (k == kEmptyKey || c <= 1u) continue;
@@ -707,12 +756,12 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE_72 void k_group(
         // ---- place ----
         if (t_rep > 0u) {
             for (uint32_t c0 = 0; c0 < nw; c0 += kGroupChunk) {
-                uint32_t k[kGroupItems];
+                uint32_t k[ITEMS];
                 load_keys(c0, nw, k);
                 uint32_t mask = 0u, cnt = 0u;
 #pragma unroll 1
-                for (int r = 0; r < kGroupItems; ++r) {
-                    const uint32_t e = c0 + (uint32_t)(tid * kGroupItems + r);
+                for (int r = 0; r < ITEMS; ++r) {
+                    const uint32_t e = c0 + (uint32_t)(tid * ITEMS + r);
                     if (e >= nw || !in_range(k[r], level, ridx) || !repeated(k[r])) continue;
                     const uint32_t h = lookup(k[r]);
                     if (h == kEmptyKey) {
@@ -725,11 +774,11 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE_72 void k_group(
                     }
                 }
                 uint32_t chunk_rep;
-                const uint32_t k0 = block_excl(cnt, s_tmp[5], &chunk_rep);  // synchronises
+                const uint32_t k0 = block_excl<THREADS>(cnt, s_tmp[5], &chunk_rep);  // synchronises
                 {
                     uint32_t kk = k0;
 #pragma unroll 1
-                    for (int r = 0; r < kGroupItems; ++r)
+                    for (int r = 0; r < ITEMS; ++r)
                         if (mask & (1u << r)) s_rep[kk++] = lookup(k[r]);
                 }
                 __syncthreads();
@@ -754,11 +803,11 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE_72 void k_group(
                 __syncthreads();
                 uint32_t kk = k0;
 #pragma unroll 1
-                for (int r = 0; r < kGroupItems; ++r) {
+                for (int r = 0; r < ITEMS; ++r) {
                     if (mask & (1u << r)) {
                         const uint32_t pos = s_rep[kk++];
-                        const uint32_t e = c0 + (uint32_t)(tid * kGroupItems + r);
-                        const uint32_t o = vals_cached ? s_cval[e] : vals[s0 + e];
+                        const uint32_t e = c0 + (uint32_t)(tid * ITEMS + r);
+                        const uint32_t o = cached ? s_cval[e] : vals[s0 + e];
                         if ((int64_t)pos >= s0 && (int64_t)pos < s0 + (int64_t)n &&
                             (int64_t)o < m) {
                             info[o] = (int32_t)pos;
@@ -800,35 +849,37 @@ hipError_t launch_group(Control* ctl, const uint32_t* keys, const uint32_t* vals
                         int64_t N, const uint32_t* hist, const uint32_t* bstart, int32_t* info,
                         uint32_t* occ, uint4* shorts, uint4* pieces, uint4* combs, uint32_t* ccount,
                         uint4* bcount, ListCaps caps, uint32_t* wstats, int bins, int key_bits,
-                        hipEvent_t stop, bool* launched, hipStream_t s) {
+                        bool beside, hipEvent_t stop, bool* launched, hipStream_t s) {
     *launched = false;
     if (m == 0) return hipSuccess;
     if (bins < 2 || bins > kMaxBins || (bins & (bins - 1)) != 0) return hipErrorInvalidValue;
     const int shift = __builtin_ctz((unsigned)bins);
     const int sub_bits = key_bits > shift ? key_bits - shift : 0;
-    // LDS beyond 64 KB is asked for explicitly, once per variant
-    static bool lds_set[2] = {false, false};
     const bool bm = sub_bits <= kBitmapBits;
-    if (!lds_set[bm]) {
-        const size_t bytes = (bm ? group_lds_words<true>() : group_lds_words<false>()) * 4;
-        const void* fn = bm ? reinterpret_cast<const void*>(&k_group<true>)
-                            : reinterpret_cast<const void*>(&k_group<false>);
-        const hipError_t e =
-            hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        if (e != hipSuccess) return e;
-        lds_set[bm] = true;
-    }
-    if (bm) {
-        hipExtLaunchKernelGGL(k_group<true>, dim3((unsigned)bins), dim3(kBlock),
-                              group_lds_words<true>() * sizeof(uint32_t), s, nullptr, stop, 0,
-                              ctl, keys, vals, m, N, hist, bstart, info, occ, shorts, pieces, combs,
-                              ccount, bcount, caps, wstats, bins, shift, sub_bits);
+    const GroupShape g = group_shape(m, bins, sub_bits);
+#define HUGE_GROUP_LAUNCH(BM, THREADS)                                                         \
+    do {                                                                                      \
+        /* LDS beyond 64 KB is asked for explicitly, once per variant */                      \
+        static const hipError_t set = hipFuncSetAttribute(                                    \
+            reinterpret_cast<const void*>(&k_group<BM, THREADS>),                             \
+            hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes - 1024);                    \
+        if (set != hipSuccess) return set;                                                    \
+        hipExtLaunchKernelGGL((k_group<BM, THREADS>), dim3((unsigned)bins), dim3(THREADS),    \
+                              g.words * sizeof(uint32_t), s, nullptr, stop, 0, ctl, keys,     \
+                              vals, m, N, hist, bstart, info, occ, shorts, pieces, combs,     \
+                              ccount, bcount, caps, wstats, bins, shift, sub_bits, g.cap,     \
+                              g.tbits);                                                       \
+    } while (0)
+    if (bm && beside) {
+        HUGE_GROUP_LAUNCH(true, kBlock);
+    } else if (bm) {
+        HUGE_GROUP_LAUNCH(true, kGroupAlone);
+    } else if (beside) {
+        HUGE_GROUP_LAUNCH(false, kBlock);
     } else {
-        hipExtLaunchKernelGGL(k_group<false>, dim3((unsigned)bins), dim3(kBlock),
-                              group_lds_words<false>() * sizeof(uint32_t), s, nullptr, stop, 0,
-                              ctl, keys, vals, m, N, hist, bstart, info, occ, shorts, pieces, combs,
-                              ccount, bcount, caps, wstats, bins, shift, sub_bits);
+        HUGE_GROUP_LAUNCH(false, kGroupAlone);
     }
+#undef HUGE_GROUP_LAUNCH
     const hipError_t e = hipGetLastError();
     *launched = e == hipSuccess;
     return e;

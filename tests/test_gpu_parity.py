@@ -649,3 +649,39 @@ def test_eval_loss_over_row_layouts_and_negative_blocks(D, K, n, dtype):
         assert np.isnan(tr.eval_loss(*args, 5).item())
         assert tr.check() == status
         args[at][n - 1] = 0
+
+
+@pytest.mark.parametrize("N,n,K,skew", [
+    (64, 60_000, 5, 1.0),       # few rows: buckets far beyond the LDS copy, every row combined
+    (3000, 40_000, 6, 6.0),     # skewed sources and destinations beside even negatives
+    (1_000_000, 30_011, 31, 1.0),   # 3/4 of the rows once
+    (40_000_000, 20_000, 3, 1.0),   # keys of 27 bits, most bitmaps wide
+])
+def test_grouping_alone_and_beside_give_the_same_steps(N, n, K, skew):
+    """The step's own grouping (512 threads) and a prepared batch's (256) place
+    the same occurrences: tables, losses and row counts bit for bit, and the
+    counts those of the batch."""
+    D = 8
+    rng = np.random.default_rng(n)
+    say(f"grouping alone and beside N={N} n={n} K={K}")
+    src, dst = ((N * rng.random(n) ** skew).astype(np.int32) for _ in range(2))
+    cc = rng.integers(1, 3, n).astype(np.int32)
+    args = [dev(x, torch) for x in (src, dst, cc)]
+    got = []
+    for prepared in (False, True):
+        tr = P.Trainer(N, D, K, n, seed=3)
+        loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+        if prepared:
+            tr.prepare(*args, 77)
+            tr.train_prepared(1e-4, loss_out=loss)
+        else:
+            tr.step(*args, 77, 1e-4, loss_out=loss)
+        assert tr.check() == 0
+        got.append((tr.S, tr.T, loss.item(), tr.stats()))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert got[0][2:] == got[1][2:]
+    ctx = np.concatenate([dst.astype(np.int64),
+                          orc.sample_negatives(3, 77, n, K, N).astype(np.int64).reshape(-1)])
+    counts = [np.unique(x, return_counts=True)[1] for x in (src, ctx)]
+    assert got[0][3] == (counts[0].size, counts[1].size,
+                         int(sum(c[c > 1].sum() for c in counts)))
