@@ -381,8 +381,7 @@ hipError_t side_end(huge_handle* h, hipStream_t s) {
 
 // The preparation of a batch into the next slot, on stream s: validation,
 // negatives and keys, tile counts and prefixes, radix pass, grouping
-// (launches only; arguments checked).  beside: another batch's apply may run
-// at the same time (a preparation of its own).
+// (launches only; arguments checked).
 huge_status stage_prepare(huge_handle* h, const int32_t* src, const int32_t* dst,
                           const int32_t* cc, const float* w, int64_t n, uint64_t first_pos,
                           bool beside, hipStream_t s) {
@@ -428,7 +427,8 @@ huge_status stage_prepare(huge_handle* h, const int32_t* src, const int32_t* dst
         if (!prof_mark(h, b, 1, s) || !prof_mark(h, b, 2, s)) return HUGE_ERR_HIP;
         HIP_TRY(launch_radix_pass(ctl, at<uint32_t>(h, SL.keys0), at<uint32_t>(h, SL.keys1),
                                   at<uint32_t>(h, SL.vals1), m, tile, bits, hist,
-                                  at<uint32_t>(h, SL.tprefix), at<uint32_t>(h, SL.bstart), s));
+                                  at<uint32_t>(h, SL.tprefix), at<uint32_t>(h, SL.bstart), beside,
+                                  s));
         if (!prof_mark(h, b, 3, s) || !prof_mark(h, b, 4, s)) return HUGE_ERR_HIP;
         const ListCaps caps{L.cap_short, L.cap_piece, L.cap_comb, L.cap_part};
         HIP_TRY(launch_group(ctl, at<uint32_t>(h, SL.keys1), at<uint32_t>(h, SL.vals1), m,
@@ -589,7 +589,8 @@ huge_status train_step(huge_handle* h, const int32_t* d_src, const int32_t* d_ds
     if (!isfinite(lr)) return HUGE_ERR_INVALID_ARG;
     if (h->prepared != h->applied) return HUGE_ERR_INVALID_ARG;  // a prepared batch is pending
     hipStream_t s = static_cast<hipStream_t>(stream);
-    st = stage_prepare(h, d_src, d_dst, d_cc, d_w, n, first_pos_index, false, s);
+    st = stage_prepare(h, d_src, d_dst, d_cc, d_w, n, first_pos_index,
+                       false, s);
     if (st != HUGE_OK) return st;
     return apply_next(h, lr, d_loss_sum, s);
 }

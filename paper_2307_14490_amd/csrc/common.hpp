@@ -334,6 +334,8 @@ inline int64_t sample_tile_positives(int64_t K, int64_t n) {
 // sample_tile_positives(K, n) positives then, else kSamplePos.
 hipError_t launch_sample(const TableArgs& t, Control* ctl, const StepArgs& a, int32_t* neg,
                          uint32_t* keys, uint32_t* tcount, int bits, hipStream_t s);
+// beside: another batch's fused step may run at the same time (not in a step
+// that waits for its own grouping).
 // Bucketing of m keys by their lowest `bits` bits in tiles of `tile` keys (at
 // most kSortTile): the tiles' digit counts summed over earlier tiles and the
 // bucket sizes (hist), then the stable scatter into bucket order; bstart
@@ -343,8 +345,8 @@ hipError_t launch_tile_scan(Control* ctl, const uint32_t* tcount, int64_t m, int
 hipError_t launch_radix_pass(Control* ctl, const uint32_t* keys_in, uint32_t* keys_out,
                              uint32_t* vals_out, int64_t m, int64_t tile, int bits,
                              const uint32_t* hist, const uint32_t* tprefix, uint32_t* bstart,
-                             hipStream_t s);
-// beside: the kernel is to run beside another one (fewer threads).  stop (if
+                             bool beside, hipStream_t s);
+// stop (if
 // not null) is recorded by the kernel's completion; *launched says
 // whether a kernel was launched (an empty batch launches none).
 hipError_t launch_group(Control* ctl, const uint32_t* keys, const uint32_t* vals, int64_t m,

@@ -125,7 +125,7 @@ hipError_t launch_tile_scan(Control* ctl, const uint32_t* tcount, int64_t m, int
 
 // ---------------------------------------------------------------------------
 // Stable scatter by the lowest BITS bits over a tile of tile_keys <=
-// kSortTile consecutive items; wave w owns the w-th quarter of the tile's
+// kSortTile consecutive items; wave w owns the w-th share of the tile's
 // items, in rounds of 64.
 //   count: lanes of a round holding the same digit are found with BITS
 //          ballots; the lowest of them adds the round's count to the wave's
@@ -141,17 +141,25 @@ hipError_t launch_tile_scan(Control* ctl, const uint32_t* tcount, int64_t m, int
 // vals_out receives the position of each key in keys_in; bstart the first
 // position of each bucket.
 // ---------------------------------------------------------------------------
-template <int BITS>
-__global__ __launch_bounds__(kBlock) HUGE_BESIDE void k_radix_pass(
+// THREADS = kBlock runs beside another batch's fused step, within the
+// HUGE_BESIDE registers; a step that waits for its own grouping runs
+// kRadixAlone threads (its 134 KB of LDS leave one workgroup per CU either
+// way): K = 31, 4.3M keys,
+// 125 -> 91 us; 2.2M 83 -> 60; medium 13.7 -> 11.3.
+constexpr int kRadixAlone = 512;
+
+template <int BITS, int THREADS>
+__global__ __launch_bounds__(THREADS)
+__attribute__((amdgpu_waves_per_eu(THREADS == kBlock ? 8 : 2, 8))) void k_radix_pass(
     Control* __restrict__ ctl, const uint32_t* __restrict__ keys_in,
     uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out, int64_t m,
     int64_t tile_keys, const uint32_t* __restrict__ hist,
     const uint32_t* __restrict__ tprefix, uint32_t* __restrict__ bstart) {
     constexpr int kBins = 1 << BITS;
-    constexpr int kWaves = kBlock / 64;
-    constexpr int kDpt = kBins / kBlock;  // digits per thread
-    static_assert(kDpt >= 1 && kBins % kBlock == 0, "whole digits per thread");
-    // dynamic LDS (radix_lds_bytes<BITS>()): with a static size this large
+    constexpr int kWaves = THREADS / 64;
+    constexpr int kDpt = kBins > THREADS ? kBins / THREADS : 1;  // digits per thread
+    static_assert(kBins % kDpt == 0, "whole digits per thread");
+    // dynamic LDS (radix_lds_bytes<BITS, THREADS>()): with a static size this large
     // the compiler, seeing one wave per SIMD at most, would not keep to the
     // HUGE_BESIDE register budget
     extern __shared__ uint32_t s_dyn[];
@@ -170,13 +178,13 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE void k_radix_pass(
     const int64_t tile = blockIdx.x;
     const int64_t tile_base = tile * tile_keys;  // tile_keys <= kSortTile
     const int64_t valid_n = (m - tile_base) < tile_keys ? (m - tile_base) : tile_keys;
-    // wave w owns the w-th quarter of the tile (a multiple of 64 items), in
+    // wave w owns the w-th share of the tile (a multiple of 64 items), in
     // order, so the scatter stays stable
     const int rounds = (int)((valid_n + kWaves * 64 - 1) / (kWaves * 64));
     const int wbase = wave * rounds * 64;
 
-    for (int j = tid; j < kWaves * kBins; j += kBlock) (&s_wave[0][0])[j] = 0u;
-    for (int p = tid; p < valid_n; p += kBlock) s_in[p] = keys_in[tile_base + p];
+    for (int j = tid; j < kWaves * kBins; j += THREADS) (&s_wave[0][0])[j] = 0u;
+    for (int p = tid; p < valid_n; p += THREADS) s_in[p] = keys_in[tile_base + p];
     __syncthreads();
 
     // count
@@ -192,19 +200,22 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE void k_radix_pass(
 
     // order
     uint32_t cnt_sum = 0, hist_sum = 0;
+    const bool digits = tid * kDpt < kBins;  // this thread has digits
 #pragma unroll
     for (int j = 0; j < kDpt; ++j) {
         const int d = tid * kDpt + j;
+        if (!digits) break;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) cnt_sum += s_wave[w][d];
         hist_sum += hist[d];
     }
     uint32_t total;
-    uint32_t local = block_excl(cnt_sum, s_tmp[0], &total);
-    uint32_t gstart = block_excl(hist_sum, s_tmp[1], &total);
+    uint32_t local = block_excl<THREADS>(cnt_sum, s_tmp[0], &total);
+    uint32_t gstart = block_excl<THREADS>(hist_sum, s_tmp[1], &total);
 #pragma unroll
     for (int j = 0; j < kDpt; ++j) {
         const int d = tid * kDpt + j;
+        if (!digits) break;
         uint32_t run = local;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
@@ -240,7 +251,7 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE void k_radix_pass(
     __syncthreads();
 
     // write
-    for (int p = tid; p < valid_n; p += kBlock) {
+    for (int p = tid; p < valid_n; p += THREADS) {
         const uint32_t k = s_keys[p];
         const int64_t dest = (int64_t)s_delta[k & (kBins - 1)] + p;
         if (dest >= 0 && dest < m) {
@@ -252,28 +263,29 @@ __global__ __launch_bounds__(kBlock) HUGE_BESIDE void k_radix_pass(
     }
 }
 
-// Dynamic LDS bytes of k_radix_pass<BITS>.
-template <int BITS>
+// Dynamic LDS bytes of k_radix_pass<BITS, THREADS>.
+template <int BITS, int THREADS>
 constexpr size_t radix_lds_bytes() {
-    return sizeof(uint32_t) * ((size_t)(kBlock / 64 + 1) * (1 << BITS) + 3 * (size_t)kSortTile);
+    return sizeof(uint32_t) * ((size_t)(THREADS / 64 + 1) * (1 << BITS) + 3 * (size_t)kSortTile);
 }
 
-template <int BITS>
+template <int BITS, int THREADS>
 hipError_t launch_radix_bits(Control* ctl, const uint32_t* keys_in, uint32_t* keys_out,
                              uint32_t* vals_out, int64_t m, int64_t tile,
                              const uint32_t* hist, const uint32_t* tprefix, uint32_t* bstart,
                              int64_t tiles, hipStream_t s) {
+    constexpr size_t kLds = radix_lds_bytes<BITS, THREADS>();
     // LDS beyond 64 KB is asked for explicitly, once per variant
     static bool lds_set = false;
     if (!lds_set) {
         const hipError_t e = hipFuncSetAttribute(
-            reinterpret_cast<const void*>(&k_radix_pass<BITS>),
-            hipFuncAttributeMaxDynamicSharedMemorySize, (int)radix_lds_bytes<BITS>());
+            reinterpret_cast<const void*>(&k_radix_pass<BITS, THREADS>),
+            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
         if (e != hipSuccess) return e;
         lds_set = true;
     }
-    hipLaunchKernelGGL(k_radix_pass<BITS>, dim3((unsigned)tiles), dim3(kBlock),
-                       radix_lds_bytes<BITS>(), s, ctl, keys_in, keys_out, vals_out, m, tile,
+    hipLaunchKernelGGL((k_radix_pass<BITS, THREADS>), dim3((unsigned)tiles), dim3(THREADS),
+                       kLds, s, ctl, keys_in, keys_out, vals_out, m, tile,
                        hist, tprefix, bstart);
     return hipGetLastError();
 }
@@ -281,13 +293,16 @@ hipError_t launch_radix_bits(Control* ctl, const uint32_t* keys_in, uint32_t* ke
 hipError_t launch_radix_pass(Control* ctl, const uint32_t* keys_in, uint32_t* keys_out,
                              uint32_t* vals_out, int64_t m, int64_t tile, int bits,
                              const uint32_t* hist, const uint32_t* tprefix, uint32_t* bstart,
-                             hipStream_t s) {
+                             bool beside, hipStream_t s) {
     if (tile < 1 || tile > kSortTile) return hipErrorInvalidValue;
     const int64_t tiles = (m + tile - 1) / tile;
     if (tiles == 0) return hipSuccess;
 #define HUGE_RADIX_LAUNCH(B)                                                                  \
-    return launch_radix_bits<B>(ctl, keys_in, keys_out, vals_out, m, tile, hist,       \
-                                tprefix, bstart, tiles, s)
+    return beside                                                                             \
+               ? launch_radix_bits<B, kBlock>(ctl, keys_in, keys_out, vals_out, m, tile,   \
+                                                 hist, tprefix, bstart, tiles, s)             \
+                  : launch_radix_bits<B, kRadixAlone>(ctl, keys_in, keys_out, vals_out, m,    \
+                                                      tile, hist, tprefix, bstart, tiles, s)
     switch (bits) {
         case 8: HUGE_RADIX_LAUNCH(8);
         case 9: HUGE_RADIX_LAUNCH(9);
@@ -351,8 +366,10 @@ __device__ __forceinline__ bool in_range(uint32_t key, int level, uint32_t idx) 
 // the keys need.  A bucket's steps are short and full of barriers, so the
 // kernel alone lives on several workgroups per CU: the most (4 .. 1) for which
 // the LDS left holds the batch's average bucket with six standard deviations
-// of an even spread to spare.  (Beside the fused step one workgroup per CU fits
-// by its registers, whatever its LDS.)
+// of an even spread to spare.  Beside the fused step one workgroup per CU fits
+// by its registers, but what it takes of the LDS the finish kernel's 10 KB
+// workgroups lack, so 48 KB are left to them where the bucket still fits
+// (1e8 rows: finish 25 us beside 148 KB, 17 beside 112).
 struct GroupShape {
     int cap;    // keys and indices cached, a multiple of 64
     int tbits;  // table slots: enough for the repeated keys of an average
@@ -369,9 +386,10 @@ inline GroupShape group_shape(int64_t m, int bins, int sub_bits) {
     while (tb < kGroupTableBits && (double)(1 << tb) < 0.75 * want) ++tb;
     const size_t fixed = 2 * ((size_t)1 << tb) + kGroupChunk + bits;
     GroupShape g{64, tb, 0};
-    for (int per_cu = 4; per_cu >= 1; --per_cu) {
+    // a quarter, a third, half, 112 KB or all of a CU's LDS
+    for (const int share : {kLdsBytes / 4, kLdsBytes / 3, kLdsBytes / 2, 112 * 1024, kLdsBytes}) {
         // the statically allocated LDS of the kernel is below 1 KB
-        const size_t budget = (kLdsBytes / per_cu - 1024) / sizeof(uint32_t);
+        const size_t budget = (size_t)(share - 1024) / sizeof(uint32_t);
         if (budget < fixed + 2 * 64) continue;
         size_t cap = (budget - fixed) / 2 / 64 * 64;
         if (cap > (size_t)kGroupCacheMost) cap = kGroupCacheMost;
@@ -385,14 +403,15 @@ inline GroupShape group_shape(int64_t m, int bins, int sub_bits) {
 // THREADS = kBlock runs beside another batch's fused step; a step that waits
 // for its own grouping runs it alone with kGroupAlone threads.  Both keep the
 // registers they need (93 and 109): within 72 a few values were spilled to
-// scratch, which cost more than the waves of the fused step that now make room
-// for it.  With 148 KB of LDS, 256 threads and 72 VGPRs for all, then as now:
-// sequential steps of 1,024 positives 43.5 -> 40.9 us, 65,536 (medium)
-// 192 -> 183, 131,072 with K = 31 1548 -> 1436 (buckets of 4200 keys found no
-// room for their indices), 100,003 of a power-law graph with K = 20
-// 1373 -> 1318; six pipelined steps of 262,144 fp32 3102 -> 3062, bf16
+// scratch, which cost more than the wave of a float fused step that now makes
+// room for it (1e8 rows, 112 KB of LDS: 462.6 us per step within 72, 458.4 with
+// 93; with 148 KB and 93 466-472).  With 148 KB of LDS, 256 threads and 72 VGPRs
+// for all, then as now: sequential steps of 1,024 positives 43.5 -> 40.9 us,
+// 65,536 (medium) 192 -> 183, 131,072 with K = 31 1548 -> 1436 (buckets of
+// 4200 keys found no room for their indices), 100,003 of a power-law graph with
+// K = 20 1373 -> 1318; six pipelined steps of 262,144 fp32 3102 -> 3064, bf16
 // 2179 -> 2008.  256 and 1024 threads alone: 42.3, 189, 1481, 1346 and 47.4,
-// 191, 1455, 1358; 512 beside: 3108 and 2073.
+// 191, 1455, 1358.
 constexpr int kGroupAlone = 512;
 
 template <bool BM, int THREADS>
@@ -861,14 +880,14 @@ hipError_t launch_group(Control* ctl, const uint32_t* keys, const uint32_t* vals
     do {                                                                                      \
         /* LDS beyond 64 KB is asked for explicitly, once per variant */                      \
         static const hipError_t set = hipFuncSetAttribute(                                    \
-            reinterpret_cast<const void*>(&k_group<BM, THREADS>),                             \
+            reinterpret_cast<const void*>(&k_group<BM, THREADS>),                      \
             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes - 1024);                    \
         if (set != hipSuccess) return set;                                                    \
-        hipExtLaunchKernelGGL((k_group<BM, THREADS>), dim3((unsigned)bins), dim3(THREADS),    \
-                              g.words * sizeof(uint32_t), s, nullptr, stop, 0, ctl, keys,     \
-                              vals, m, N, hist, bstart, info, occ, shorts, pieces, combs,     \
-                              ccount, bcount, caps, wstats, bins, shift, sub_bits, g.cap,     \
-                              g.tbits);                                                       \
+        hipExtLaunchKernelGGL((k_group<BM, THREADS>), dim3((unsigned)bins),            \
+                              dim3(THREADS), g.words * sizeof(uint32_t), s, nullptr, stop, 0, \
+                              ctl, keys, vals, m, N, hist, bstart, info, occ, shorts, pieces, \
+                              combs, ccount, bcount, caps, wstats, bins, shift, sub_bits,     \
+                              g.cap, g.tbits);                                                \
     } while (0)
     if (bm && beside) {
         HUGE_GROUP_LAUNCH(true, kBlock);
