@@ -369,7 +369,8 @@ __device__ __forceinline__ bool in_range(uint32_t key, int level, uint32_t idx) 
 // of an even spread to spare.  Beside the fused step one workgroup per CU fits
 // by its registers, but what it takes of the LDS the finish kernel's 10 KB
 // workgroups lack, so 48 KB are left to them where the bucket still fits
-// (1e8 rows: finish 25 us beside 148 KB, 17 beside 112).
+// (1e8 rows, fp32: finish 27 us beside 148 KB and a loss sum with 8 loads in
+// flight, 17 beside 112 KB and 16 loads; the two were not timed apart).
 struct GroupShape {
     int cap;    // keys and indices cached, a multiple of 64
     int tbits;  // table slots: enough for the repeated keys of an average
@@ -405,13 +406,13 @@ inline GroupShape group_shape(int64_t m, int bins, int sub_bits) {
 // registers they need (93 and 109): within 72 a few values were spilled to
 // scratch, which cost more than the wave of a float fused step that now makes
 // room for it (1e8 rows, 112 KB of LDS: 462.6 us per step within 72, 458.4 with
-// 93; with 148 KB and 93 466-472).  With 148 KB of LDS, 256 threads and 72 VGPRs
+// 93, 455.8 before the grouping and the finish kernel were changed).  With 148 KB of LDS, 256 threads and 72 VGPRs
 // for all, then as now: sequential steps of 1,024 positives 43.5 -> 40.9 us,
 // 65,536 (medium) 192 -> 183, 131,072 with K = 31 1548 -> 1436 (buckets of
 // 4200 keys found no room for their indices), 100,003 of a power-law graph with
 // K = 20 1373 -> 1318; six pipelined steps of 262,144 fp32 3102 -> 3064, bf16
 // 2179 -> 2008.  256 and 1024 threads alone: 42.3, 189, 1481, 1346 and 47.4,
-// 191, 1455, 1358.
+// 191, 1455, 1358; 512 beside: 3108 and 2073.
 constexpr int kGroupAlone = 512;
 
 template <bool BM, int THREADS>
@@ -876,14 +877,14 @@ hipError_t launch_group(Control* ctl, const uint32_t* keys, const uint32_t* vals
     const int sub_bits = key_bits > shift ? key_bits - shift : 0;
     const bool bm = sub_bits <= kBitmapBits;
     const GroupShape g = group_shape(m, bins, sub_bits);
-#define HUGE_GROUP_LAUNCH(BM, THREADS)                                                         \
+#define HUGE_GROUP_LAUNCH(BM, THREADS)                                                        \
     do {                                                                                      \
         /* LDS beyond 64 KB is asked for explicitly, once per variant */                      \
         static const hipError_t set = hipFuncSetAttribute(                                    \
-            reinterpret_cast<const void*>(&k_group<BM, THREADS>),                      \
+            reinterpret_cast<const void*>(&k_group<BM, THREADS>),                             \
             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes - 1024);                    \
         if (set != hipSuccess) return set;                                                    \
-        hipExtLaunchKernelGGL((k_group<BM, THREADS>), dim3((unsigned)bins),            \
+        hipExtLaunchKernelGGL((k_group<BM, THREADS>), dim3((unsigned)bins),                   \
                               dim3(THREADS), g.words * sizeof(uint32_t), s, nullptr, stop, 0, \
                               ctl, keys, vals, m, N, hist, bstart, info, occ, shorts, pieces, \
                               combs, ccount, bcount, caps, wstats, bins, shift, sub_bits,     \

@@ -690,9 +690,10 @@ __global__ __launch_bounds__(kBlock, C > 1 ? 1 : sizeof(E) == 4 ? 6 : 5) void k_
 
     // Workgroup 0 (dispatched first) sums the loss and nothing else: thread t
     // adds partial pairs t, t + kBlock, ... in that order (16-byte loads, 16
-    // in flight: with 8 the loss outlasted the records, 27 against 22 us beside a
-    // preparation at 262,144 positives), then the threads' sums meet in a fixed tree: the same
-    // double on every run.
+    // in flight, so that the sum ends with the records: at 262,144 positives the
+    // kernel beside a preparation took 27 us with 8, and takes 17 with 16 and more
+    // LDS left to it), then the threads' sums meet in a fixed tree: the same double
+    // on every run.
     if (blockIdx.x == 0) {
         if (f.loss_out == nullptr) return;
         const double2* p2 = reinterpret_cast<const double2*>(f.lossp);
