@@ -647,9 +647,15 @@ hipError_t launch_eval_summary(const float* d, int64_t n_edge, int64_t n_non, co
 // Normalised query rows qn[j * D ..] (zero for a zero row or a padding slot)
 // and qn2[j] = |qn_j|^2 in {0, 1}; with the threshold scans, their state: no
 // candidates, the bound +inf (-inf for a padding slot: nothing passes it) and
-// the fallback gate closed.  qh (if not null) receives the queries' fp16
-// parts as matrix operands.
+// the fallback gate closed.  A query row whose squared norm is no normal
+// number (not finite, or so small that its sum has lost bits) is not of
+// length 1 after the scaling, which the screens' bounds take for granted: its
+// bound is -inf too, and k_knn_select opens the gate for it.  qh (if not null)
+// receives the queries' fp16 parts as matrix operands.
 constexpr float kKnnSplitScale = 1024.0f;  // 2^10: the scale of the fp16 parts
+// Squared norms between these have kept their precision: squares below 2^-149
+// are lost, at most dim 2^-150 in all, 2^-40 of the smallest.
+constexpr float kKnnNormMin = 1e-30f, kKnnNormMax = 1e38f;
 
 __global__ __launch_bounds__(kBlock) void k_knn_queries(const float* __restrict__ T, int64_t N,
                                                         int32_t D, const int32_t* __restrict__ q,
@@ -702,7 +708,8 @@ __global__ __launch_bounds__(kBlock) void k_knn_queries(const float* __restrict_
         qid[j] = id;
         if (cnt) {
             cnt[j * kKnnCntStride] = 0u;
-            tau[j] = id >= 0 ? __builtin_inff() : -__builtin_inff();
+            const bool screened = n2 == 0.f || (n2 >= kKnnNormMin && n2 <= kKnnNormMax);
+            tau[j] = id >= 0 && screened ? __builtin_inff() : -__builtin_inff();
         }
         if (gate && j == 0) *gate = 0;
     }
@@ -1357,7 +1364,10 @@ __global__ __launch_bounds__(kKnnWavesR * 64) void k_knn_tiles_h4(KnnArgs A) {
 // most 2^-21, a quarter of a unit of acc), so a screened product below that
 // less kKnnScreenMargin = 1536 clears the pair.  A query block with any pair
 // left, or a tile with a zero or missing row, gets the full products of the
-// list search (bit for bit) and the exact test.
+// list search (bit for bit) and the exact test.  So does a tile with a row
+// whose squared norm lies outside [kKnnNormMin, kKnnNormMax] (its scaled norm
+// may not be 2^10, or its scaled values are no numbers), and a pair whose
+// screened product is no number.
 // ---------------------------------------------------------------------------
 struct KnnScanArgs {
     const float* T;
@@ -1480,6 +1490,9 @@ void k_knn_scan(KnnScanArgs A) {
         const float sc = nr > 0.f ? kKnnSplitScale / sqrtf(nr) : 0.f;
         // bit m (and m + 32): row m of the tile is present and nonzero
         const uint64_t live = __ballot(nr > 0.f && t * 32 + x < A.N);
+        // every row is one that the screen's bound holds for
+        const bool sure =
+            __ballot(nr >= kKnnNormMin && nr <= kKnnNormMax && t * 32 + x < A.N) == ~0ull;
         // the screen: hi.hi products of every query block
         knn_acc16 acc[QB];
 #pragma unroll
@@ -1498,9 +1511,9 @@ void k_knn_scan(KnnScanArgs A) {
         uint32_t need = 0u;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            bool look = live != ~0ull;
+            bool look = !sure;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) look |= acc[qb][r] >= athr[qb];
+            for (int r = 0; r < 16; ++r) look |= !(acc[qb][r] < athr[qb]);
             need |= __ballot(look) != 0ull ? 1u << qb : 0u;
         }
         // the full products of the list search for those blocks, then the exact test
@@ -1539,8 +1552,9 @@ void k_knn_scan(KnnScanArgs A) {
 // list's kept keys (at most cap, a power of two).  After a sample scan the
 // k-th key's d^2 becomes the query's bound (fewer than k keys leave it); after
 // the last scan the k smallest keys are the answer, written as the
-// list-merging search writes it, and a list that overflowed opens the gate for
-// that search.  The count is reset for the next scan.
+// list-merging search writes it, and a list that overflowed, or a query whose
+// bound is -inf (no screen holds for it), opens the gate for that search.  The
+// count is reset for the next scan.
 // The keys' distances are counted in kKnnSelectBins equal ranges of their bit
 // patterns between the smallest and the largest; only the keys up to the range
 // that holds the k-th are sorted (a bitonic network in LDS).  Sorting all of
@@ -1554,6 +1568,7 @@ struct KnnSelectArgs {
     int32_t last;      // 1: the last scan
     int32_t m;         // queries of the pass (slots beyond are padding)
     int32_t q_first;   // the pass's first query
+    const int32_t* qid;
     float* tau;
     int32_t* ids;
     float* dist;
@@ -1661,8 +1676,11 @@ __global__ __launch_bounds__(kKnnSelectThreads) void k_knn_select(KnnSelectArgs 
                                           : sqrtf(__uint_as_float((uint32_t)(key >> 32)));
             }
         }
-        if (tid == 0 && c > (uint32_t)S.cap) *S.gate = 1;
-    } else if (tid == 0 && s_key[S.k - 1] != kNoKey) {
+        // a list that overflowed, or a query that the scans do not answer
+        if (tid == 0 &&
+            (c > (uint32_t)S.cap || (S.qid[q] >= 0 && S.tau[q] == -__builtin_inff())))
+            *S.gate = 1;
+    } else if (tid == 0 && s_key[S.k - 1] != kNoKey && S.tau[q] != -__builtin_inff()) {
         S.tau[q] = __uint_as_float((uint32_t)(s_key[S.k - 1] >> 32));
     }
     if (tid == 0) S.cnt[q * kKnnCntStride] = 0u;
@@ -1856,7 +1874,7 @@ void k_knn_wide_scan(KnnWideArgs A) {
         const int64_t row = i * A.step * 32 + x;
         const float norm = sc * sqrtf(nr);
         const bool zero = nr == 0.f;
-        const bool fits = nr >= 1e-30f && nr <= 1e38f && norm >= 1.f && norm <= 16384.f;
+        const bool fits = nr >= kKnnNormMin && nr <= kKnnNormMax && norm >= 1.f && norm <= 16384.f;
         const bool there = row < A.N;
         const float f = zero ? 1.f : norm * (1.f / 1024.f);
         const float off = zero ? -kKnnAccPerD2 : 0.f;
@@ -1885,7 +1903,8 @@ void k_knn_wide_scan(KnnWideArgs A) {
             for (uint32_t m = mask[qb]; m != 0u; m &= m - 1u) {
                 const int r = __builtin_ctz(m);
                 const int q = qb * 32 + 8 * (r / 4) + 4 * h + (r % 4);
-                if (A.qid[q] < 0) continue;  // a padding slot
+                // a padding slot, or a query that the scans do not answer
+                if (A.tau[q] == -__builtin_inff()) continue;
                 const uint32_t pos = atomicAdd(&A.cnt[q * kKnnCntStride], 1u);
                 if (pos < (uint32_t)A.cap) A.cand[(size_t)q * A.cap + pos] = (uint64_t)row;
             }
@@ -2024,6 +2043,7 @@ hipError_t launch_knn(const float* T, int64_t N, int32_t D, const int32_t* q, in
         SS.k = k;
         SS.m = m;
         SS.q_first = q0;
+        SS.qid = B.qid;
         SS.tau = B.tau;
         SS.ids = ids;
         SS.dist = dist;

@@ -387,6 +387,38 @@ def test_knn_wide_scans_match_the_list_search(N, D, nq, k, note):
         check_knn(T.cpu().numpy(), fine, k, i2.cpu().numpy(), d2.cpu().numpy())
 
 
+@pytest.mark.parametrize("N,D,nq,k", [(40007, 64, 2, 1), (40007, 128, 100, 10), (40007, 128, 3, 2),
+                                      (70001, 36, 1, 1), (40007, 192, 2, 1), (40007, 264, 70, 10)])
+@pytest.mark.parametrize("queries", ["fine", "zero", "inf", "nan", "huge", "tiny"])
+def test_knn_scans_match_the_list_search_on_rows_no_screen_holds_for(N, D, nq, k, queries):
+    """Rows and queries that are not finite, huge, or so small that the sum of
+    their squares has lost bits (the scaled row is then not of length 1): the
+    threshold scans give the list search's answer bit for bit, also for the
+    other queries of the pass.  With few queries most tiles hold no candidate,
+    so that nothing but the row itself takes it to the exact test."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + D)
+    T = torch.randn((N, D), generator=g, device="cuda")
+    T[100, 3] = float("inf")
+    T[4000, D - 1] = float("nan")
+    T[5000] *= 1e18
+    T[5001] *= 1e25
+    # one square of a subnormal step, the others just below half of one
+    T[6000:6004] = 2.6e-23 * torch.sign(T[6000:6004])
+    T[6000:6004, 0] = 3.0e-23
+    T[N - 1] *= 1e-19
+    q = torch.randint(0, N, (nq,), generator=g, device="cuda", dtype=torch.int32)
+    special = {"fine": 17, "zero": 18, "inf": 100, "nan": 4000, "huge": 5001, "tiny": 6001}[queries]
+    T[18] = 0.0
+    q[nq // 2] = special
+    say(f"knn scans and odd rows N={N} D={D} nq={nq} k={k} queries={queries}")
+    ev = P.Evaluator(N, D, 8, k=k)
+    ids, dist = ev.knn(T, q, k)
+    ids_l, dist_l = ev.knn(T, q, k, lists=True)
+    assert torch.equal(ids, ids_l)
+    assert torch.equal(dist.view(torch.int32), dist_l.view(torch.int32))
+
+
 def test_knn_wide_falls_back_to_the_list_search_when_a_candidate_list_overflows():
     N, D, k = 30000, 192, 10
     T = torch.from_numpy(np.random.default_rng(8).normal(size=(N, D)).astype(np.float32)).cuda()
