@@ -253,6 +253,7 @@ constexpr int small_sort() {
 constexpr uint32_t kNoPair = ~0u;
 constexpr uint32_t kNoPlace = 0xFFFFu;
 constexpr int64_t kDirectNodes = (int64_t)1 << 27;  // ids below it fit a key directly
+constexpr int64_t kWalkMostSeeds = (int64_t)1 << 25;  // seeds of a launch
 
 template <int R, bool RANK, bool WRITE>
 __global__ __launch_bounds__(kBlock) void k_walk_group(
@@ -584,8 +585,11 @@ hipError_t launch_walks(const WalkArgs& A, int32_t pairs, const WalkBuffers& B, 
         return hipErrorInvalidValue;
     // seeds whose nodes fit the buffer at a time
     const int64_t per_seed = (int64_t)A.walks * A.steps;
-    const int64_t fit = B.node_cap / per_seed;
+    int64_t fit = B.node_cap / per_seed;
     if (fit < 1) return hipErrorInvalidValue;
+    // a wave per seed and fewer than 2^32 threads in a launch: 2^26 seeds of one
+    // walk of one step, whose nodes fit, are 2^32
+    if (fit > kWalkMostSeeds) fit = kWalkMostSeeds;
     const int64_t chunk = n < fit ? n : fit;
     const bool direct = A.seed_only && A.num_nodes < kDirectNodes;
     for (int pass = 0; pass < 2; ++pass) {

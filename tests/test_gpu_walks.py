@@ -181,3 +181,22 @@ def test_triple_counts_are_scanned_over_many_ranges():
     ring = (np.arange(n)[:, None] + np.arange(1, steps + 1)) % n
     assert np.array_equal(dst.cpu().numpy(), np.sort(ring, axis=1).reshape(-1))
     assert (cc == 2).all() and (hist.sum(1) == 2).all()
+
+
+@pytest.mark.parametrize("seed_only", [True, False])
+def test_more_seeds_than_waves_of_one_launch(seed_only):
+    """2^26 + 5 seeds of one walk of one step: their nodes fit the workspace,
+    but a wave for each in one launch would be more than 2^32 - 1 threads."""
+    n = 2 ** 26 + 5
+    say(f"walks n={n} of one step, seed_only={seed_only}")
+    off = torch.arange(n + 1, dtype=torch.int64, device="cuda")
+    nbr = (off[:-1] + 1).remainder(n).int()
+    src, dst, cc, _ = P.sample_walks(off, nbr, n, 1, 1, 1, seed_only, seed=1, with_hist=False)
+    ids = off[:-1].int()
+    if seed_only:
+        assert torch.equal(src, ids) and torch.equal(dst, nbr)
+    else:  # (s, s + 1) and (s + 1, s), ascending by source
+        a, b = torch.minimum(ids, nbr), torch.maximum(ids, nbr)
+        assert torch.equal(src.view(-1, 2), torch.stack([a, b], 1))
+        assert torch.equal(dst.view(-1, 2), torch.stack([b, a], 1))
+    assert bool((cc == 1).all())
