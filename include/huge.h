@@ -302,8 +302,9 @@ typedef struct huge_walk_config {
    window for seed pairs, walks_per_node x 2 (window (walk_steps + 1) -
    window (window + 1) / 2) for window pairs). */
 
-/* Bytes of device workspace huge_sample_walks needs for num_seeds seeds;
-   0 if the config is invalid. */
+/* Bytes of device workspace for huge_sample_walks over num_seeds seeds: 12 per
+   seed and the nodes of their walks, at most 256 MiB of them; 0 if the config
+   is invalid. */
 size_t huge_walk_workspace_bytes(const huge_walk_config* cfg, int64_t num_seeds);
 
 /* Triples of the seeds first_seed .. first_seed + num_seeds - 1.
@@ -316,8 +317,9 @@ size_t huge_walk_workspace_bytes(const huge_walk_config* cfg, int64_t num_seeds)
      d_status    : device int32, receives 0; -2 if the graph is malformed
                    (an offset or neighbour out of range: nothing is written);
                    -4 if the triples exceed capacity (nothing is written)
-     d_workspace : >= huge_walk_workspace_bytes(cfg, num_seeds) bytes, 256-byte
-                   aligned
+     d_workspace : huge_walk_workspace_bytes(cfg, num_seeds) bytes, 256-byte
+                   aligned.  With room for fewer nodes, down to 2048 bytes
+                   per seed (and 32 KB), the seeds are taken in chunks
    Asynchronous on `stream`; host-detectable argument errors return before
    any launch. */
 huge_status huge_sample_walks(const huge_walk_config* cfg, const int64_t* d_offsets,

@@ -759,14 +759,15 @@ struct WalkLayout {
     size_t offsets, counts, sums, nodes, total;
 };
 
-WalkLayout walk_layout(int64_t num_seeds) {
+// The regions of a workspace with per_seed bytes of nodes per seed.
+WalkLayout walk_layout(int64_t num_seeds, int64_t per_seed) {
     const size_t n = (size_t)(num_seeds > 0 ? num_seeds : 1);
     WalkLayout L;
     L.offsets = 0;
     L.counts = L.offsets + align_up(sizeof(uint64_t) * n);
     L.sums = L.counts + align_up(sizeof(uint32_t) * n);
     L.nodes = L.sums + align_up(sizeof(uint64_t) * (size_t)kWalkRanges);
-    L.total = L.nodes + align_up((size_t)walk_node_bytes((int64_t)n));
+    L.total = L.nodes + align_up((size_t)walk_node_bytes((int64_t)n, per_seed));
     return L;
 }
 
@@ -776,7 +777,9 @@ extern "C" {
 
 size_t huge_walk_workspace_bytes(const huge_walk_config* cfg, int64_t num_seeds) {
     if (!walk_config_ok(cfg) || num_seeds < 0) return 0;
-    return walk_layout(num_seeds).total;
+    const int64_t nodes = (int64_t)sizeof(int32_t) * cfg->walks_per_node * cfg->walk_steps;
+    return walk_layout(num_seeds, nodes > kWalkNodeBytesPerSeed ? nodes : kWalkNodeBytesPerSeed)
+        .total;
 }
 
 huge_status huge_sample_walks(const huge_walk_config* cfg, const int64_t* d_offsets,
@@ -792,15 +795,18 @@ huge_status huge_sample_walks(const huge_walk_config* cfg, const int64_t* d_offs
     if (capacity < 0 || !d_count || !d_status || !d_workspace) return HUGE_ERR_INVALID_ARG;
     if (capacity > 0 && (!d_src || !d_dst || !d_cc)) return HUGE_ERR_INVALID_ARG;
     if ((uintptr_t)d_workspace % kAlign != 0) return HUGE_ERR_INVALID_ARG;
-    if (ws_bytes < huge_walk_workspace_bytes(cfg, num_seeds)) return HUGE_ERR_WORKSPACE;
+    // the nodes come last: what the workspace has for them, is used
+    const WalkLayout L = walk_layout(num_seeds, kWalkNodeBytesPerSeed);
+    if (ws_bytes < L.total) return HUGE_ERR_WORKSPACE;
     uint8_t* ws = static_cast<uint8_t*>(d_workspace);
-    const WalkLayout L = walk_layout(num_seeds);
     WalkBuffers B;
     B.offsets = reinterpret_cast<uint64_t*>(ws + L.offsets);
     B.counts = reinterpret_cast<uint32_t*>(ws + L.counts);
     B.sums = reinterpret_cast<uint64_t*>(ws + L.sums);
     B.nodes = reinterpret_cast<int32_t*>(ws + L.nodes);
-    B.node_cap = walk_node_bytes(num_seeds) / (int64_t)sizeof(int32_t);
+    const size_t room = ws_bytes - L.nodes;
+    B.node_cap = (int64_t)((room < (size_t)kWalkNodeBytesMax ? room : (size_t)kWalkNodeBytesMax) /
+                           sizeof(int32_t));
     const WalkOut O{d_count, capacity, d_src, d_dst, d_cc, d_hist, d_status};
     WalkArgs A;
     A.off = d_offsets;

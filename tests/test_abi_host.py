@@ -154,6 +154,15 @@ def test_workspace_grows_with_batch_and_holds_duplicate_buffer():
     assert 0 < atomic < big
 
 
+@pytest.mark.parametrize("walks,steps,seeds", [(1024, 4, 30), (256, 6, 2000), (126, 64, 8192),
+                                               (1, 1, 1), (128, 3, 65_536)])
+def test_walk_workspace_holds_the_nodes_of_all_seeds(walks, steps, seeds):
+    """Seeds whose nodes do not fit are taken in chunks, one after the other."""
+    cfg = P.walk_config(10**6, walks, steps, 1, True)
+    got = P.load().huge_walk_workspace_bytes(ctypes.byref(cfg), seeds)
+    assert got >= 12 * seeds + 4 * walks * steps * seeds
+
+
 def test_host_alias_table_equals_oracle_bitwise():
     rng = np.random.default_rng(0)
     for w in (rng.pareto(1.2, 50_000) + 1e-3,

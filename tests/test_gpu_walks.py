@@ -200,3 +200,37 @@ def test_more_seeds_than_waves_of_one_launch(seed_only):
         assert torch.equal(src.view(-1, 2), torch.stack([a, b], 1))
         assert torch.equal(dst.view(-1, 2), torch.stack([b, a], 1))
     assert bool((cc == 1).all())
+
+
+@pytest.mark.parametrize("walks,steps,window,seed_only", [(1024, 4, 4, True), (16, 40, 1, False)])
+def test_a_small_workspace_takes_the_seeds_in_chunks(walks, steps, window, seed_only):
+    """2048 bytes of nodes per seed, an eighth (0.8) of what the walks need: the
+    same triples as with room for all."""
+    import ctypes
+    n, seeds = 400, 101
+    off, nbr = _graph("sbm", n)
+    doff, dnbr = dev(off, torch), dev(nbr, torch)
+    say(f"walks in chunks walks={walks} steps={steps}")
+    want = P.sample_walks(doff, dnbr, n, walks, steps, window, seed_only, seed=4, first_seed=7,
+                          num_seeds=seeds)
+    cfg = P.walk_config(n, walks, steps, window, seed_only, 4)
+    few = P.walk_config(n, 1, 1, 1, True, 4)  # 2048 bytes per seed are the least reported
+    need = P.load().huge_walk_workspace_bytes(ctypes.byref(few), seeds)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    assert ws.data_ptr() % 256 == 0
+    total = want[0].numel()
+    out = [torch.empty_like(x) for x in want]
+    count = torch.zeros(1, dtype=torch.int64, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+
+    def run(nbytes):
+        return P.load().huge_sample_walks(
+            ctypes.byref(cfg), doff.data_ptr(), dnbr.data_ptr(), dnbr.numel(), 7, seeds,
+            *(x.data_ptr() for x in out), total, count.data_ptr(), status.data_ptr(),
+            ws.data_ptr(), nbytes, torch.cuda.current_stream().cuda_stream)
+
+    assert run(need - 1) == -4
+    assert run(need) == 0
+    assert int(status.item()) == 0 and int(count.item()) == total
+    for x, y in zip(out, want):
+        assert torch.equal(x, y)
