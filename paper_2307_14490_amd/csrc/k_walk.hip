@@ -611,8 +611,10 @@ hipError_t launch_walks(const WalkArgs& A, int32_t pairs, const WalkBuffers& B, 
             int64_t len = (n + kWalkRanges - 1) / kWalkRanges;
             len = (len + kWalkStep - 1) / kWalkStep * kWalkStep;
             const unsigned ranges = (unsigned)((n + len - 1) / len);
-            hipLaunchKernelGGL(k_walk_sums, dim3(ranges), dim3(kBlock), 0, s, B.counts, n, len,
-                               B.sums);
+            // one range (at most kWalkStep seeds): the scan reads no sums
+            if (ranges > 1)
+                hipLaunchKernelGGL(k_walk_sums, dim3(ranges), dim3(kBlock), 0, s, B.counts, n,
+                                   len, B.sums);
             if ((e = hipGetLastError()) != hipSuccess) return e;
             hipLaunchKernelGGL(k_walk_scan, dim3(ranges), dim3(kBlock), 0, s, B.counts, B.sums,
                                B.offsets, n, len, O.count, O.capacity, O.status);
