@@ -953,12 +953,17 @@ huge_status huge_profile_end(huge_handle* h, void* stream, double* phase_ms, int
 namespace {
 
 struct SummaryLayout {
-    size_t bins, map, mid, map2, low, state, part, total;
+    size_t bins, map, mid, map2, low, state, part;
+    size_t counters;  // what the regions take
+    size_t least;     // the least workspace that is accepted
+    size_t total;     // the size reported
 };
 
-// The summary's regions, and the size reported for it: at least 8 bytes per
-// distance and 8 KB per 8192 of them (huge_eval_summary_static takes as many
-// distances as that size leaves in its array).
+// The summary's regions.  The least workspace, two words per distance and 8 KB
+// per 8192 of them, is what callers' own arrays have been sized by (that of
+// huge_eval_summary_static among them, which takes as many distances as it
+// leaves there); where it does not hold the regions, a smaller workspace than
+// the one reported is taken by a kernel that needs none.
 SummaryLayout summary_layout(int64_t max_pairs) {
     SummaryLayout L;
     size_t off = 0;
@@ -977,8 +982,9 @@ SummaryLayout summary_layout(int64_t max_pairs) {
     L.part = take(sizeof(double) * 2 * kEvalSumBlocks);
     const size_t n = (size_t)(max_pairs > 0 ? max_pairs : 1);
     const size_t tiles = (n + 8191) / 8192;
-    const size_t reported = 2 * align_up(4 * n) + 8192 * tiles + 12544;
-    L.total = off > reported ? off : reported;
+    L.counters = off;
+    L.least = 2 * align_up(4 * n) + 8192 * tiles + 12544;
+    L.total = L.counters > L.least ? L.counters : L.least;
     return L;
 }
 
@@ -1068,7 +1074,7 @@ huge_status eval_summary(const float* d_dist, int64_t n_edge, int64_t n_non,
     if (!d_workspace) return HUGE_ERR_INVALID_ARG;
     if (reinterpret_cast<uintptr_t>(d_workspace) % kAlign != 0) return HUGE_ERR_WORKSPACE;
     const SummaryLayout L = summary_layout(n_edge + n_non);
-    if (ws_bytes < L.total) return HUGE_ERR_WORKSPACE;
+    if (ws_bytes < L.least) return HUGE_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t* ws = static_cast<uint8_t*>(d_workspace);
     SumBuffers B;
@@ -1080,7 +1086,8 @@ huge_status eval_summary(const float* d_dist, int64_t n_edge, int64_t n_non,
     uint32_t* state = reinterpret_cast<uint32_t*>(ws + L.state);
     B.state = SumState{state, state + 4 * kEvalMaxQuantiles, state + 8 * kEvalMaxQuantiles};
     B.part = reinterpret_cast<double*>(ws + L.part);
-    HIP_TRY(launch_eval_summary(d_dist, n_edge, n_non, h_quantiles, n_quantiles, B, d_out, s));
+    HIP_TRY(launch_eval_summary(d_dist, n_edge, n_non, h_quantiles, n_quantiles, B,
+                                ws_bytes >= L.counters, d_out, s));
     return HUGE_OK;
 }
 

@@ -434,8 +434,10 @@ struct SumBuffers {
     SumState state;
     double* part;    // [2 kEvalSumBlocks]
 };
+// have_counters: B's regions exist; else nothing of B is used.
 hipError_t launch_eval_summary(const float* d, int64_t n_edge, int64_t n_non, const double* q,
-                               int nq, const SumBuffers& B, double* out, hipStream_t s);
+                               int nq, const SumBuffers& B, bool have_counters, double* out,
+                               hipStream_t s);
 int knn_pass_queries(int D);
 int64_t knn_lists(int64_t N, int D, int QB);
 // Workspace of a nearest-row search (device memory, one pass of queries).

@@ -365,6 +365,18 @@ __global__ __launch_bounds__(kSumThreads) void k_sum_hist(const float* __restric
     }
 }
 
+// out[0..4] from the sets' sums and counts.
+__device__ __forceinline__ void write_means(double* __restrict__ out, double se, double sn,
+                                            double ce, double cn) {
+    const double nan = __builtin_nan("");
+    const double me = ce > 0.0 ? se / ce : nan, mn = cn > 0.0 ? sn / cn : nan;
+    out[0] = ce;
+    out[1] = cn;
+    out[2] = me;
+    out[3] = mn;
+    out[4] = (ce > 0.0 && cn > 0.0) ? mn / me : nan;
+}
+
 // Workgroup s: set s's totals (workgroup 0 writes out[0..4]), the ranks its
 // percentiles need and the bins that hold them.  Rank r of the set is state
 // entry s 2 nq + r (r even: the lower statistic of percentile r / 2); a bin's
@@ -395,15 +407,7 @@ __global__ __launch_bounds__(kSumThreads) void k_sum_bins(const uint32_t* __rest
         __syncthreads();
     }
     const double se = s_t[0][0], sn = s_t[1][0], ce = s_t[2][0], cn = s_t[3][0];
-    if (set == 0 && tid == 0) {
-        const double nan = __builtin_nan("");
-        const double me = ce > 0.0 ? se / ce : nan, mn = cn > 0.0 ? sn / cn : nan;
-        out[0] = ce;
-        out[1] = cn;
-        out[2] = me;
-        out[3] = mn;
-        out[4] = (ce > 0.0 && cn > 0.0) ? mn / me : nan;
-    }
+    if (set == 0 && tid == 0) write_means(out, se, sn, ce, cn);
     const int64_t count = (int64_t)(set ? cn : ce);
     if (tid < nr) {
         int64_t lo = 0, hi = 0;
@@ -598,8 +602,186 @@ __global__ __launch_bounds__(kSumThreads) void k_sum_pick(const uint32_t* __rest
     }
 }
 
+// The same for a workspace that does not hold the counters (below about 233,000
+// distances the size asked for is less than they take): one workgroup per set,
+// the selection in LDS, eight bits at a time from the top, and no workspace.
+// The values are read once per level and 128 slots, so it takes the longer the
+// more there are (1,000, 10,000, 100,000, 230,000 distances and 11 percentiles: 23,
+// 32, 148, 331 us; with the counters 63 to 64).  The sums are formed in k_sum_hist's and
+// k_sum_bins's order: the same bits.
+//   s_bin    [128][256] counters of a level's slots, 128 slots at a time
+//   s_order  the ranks in ascending order, so that the values found so far
+//            (s_pre, their upper bits) ascend too and a value's slot among the
+//            distinct ones (s_uniq) is found by bisection
+constexpr int kSmallSlots = 128;
+constexpr int kSmallLoads = 8;  // values of a thread in flight
+
+// fn(value) for every value that is a number in d[i0 .. i1), thread by thread
+// in strides of the workgroup.
+template <typename Fn>
+__device__ __forceinline__ void small_values(const float* __restrict__ d, int64_t i0, int64_t i1,
+                                             Fn fn) {
+    for (int64_t c = i0 + threadIdx.x; c < i1; c += kSmallLoads * kSumThreads) {
+        float x[kSmallLoads];
+#pragma unroll
+        for (int j = 0; j < kSmallLoads; ++j) {
+            const int64_t i = c + j * kSumThreads;
+            x[j] = i < i1 ? d[i] : __builtin_nanf("");
+        }
+#pragma unroll
+        for (int j = 0; j < kSmallLoads; ++j)
+            if (x[j] == x[j]) fn(x[j]);
+    }
+}
+
+__global__ __launch_bounds__(kSumThreads) void k_sum_small(const float* __restrict__ d,
+                                                           int64_t n_edge, int64_t n,
+                                                           int edge_blocks, int blocks,
+                                                           Quantiles Q, int nq,
+                                                           double* __restrict__ out) {
+    extern __shared__ uint32_t s_bin[];  // [kSmallSlots][256]
+    __shared__ double s_t[4][kEvalSumBlocks];
+    __shared__ double s_w[2][kSumThreads / 64];
+    constexpr int kRanks = 2 * kEvalMaxQuantiles;
+    __shared__ uint32_t s_rank[kRanks], s_rest[kRanks], s_pre[kRanks], s_uniq[kRanks];
+    __shared__ uint16_t s_order[kRanks], s_slot[kRanks];
+    __shared__ int s_slots;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int set = blockIdx.x, nr = 2 * nq;
+    // the sums of both sets, part by part as k_sum_hist's workgroups form them
+    if (tid < kEvalSumBlocks)
+        for (int c = 0; c < 4; ++c) s_t[c][tid] = 0.0;
+    __syncthreads();
+    for (int p = 0; p < blocks; ++p) {
+        const bool non = p >= edge_blocks;
+        const int b = non ? p - edge_blocks : p, nb = non ? blocks - edge_blocks : edge_blocks;
+        const int64_t first = non ? n_edge : 0, cnt = non ? n - n_edge : n_edge;
+        const int64_t per = (cnt + nb - 1) / nb;
+        const int64_t i0 = first + b * per;
+        const int64_t i1 = b * per + per < cnt ? i0 + per : first + cnt;
+        double sum = 0.0, num = 0.0;
+        small_values(d, i0, i1, [&](float x) {
+            sum += (double)x;
+            num += 1.0;
+        });
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            sum += __shfl_xor(sum, off, 64);
+            num += __shfl_xor(num, off, 64);
+        }
+        if (lane == 0) {
+            s_w[0][wave] = sum;
+            s_w[1][wave] = num;
+        }
+        __syncthreads();
+        if (tid < 2) {
+            double t = 0.0;
+            for (int w = 0; w < kSumThreads / 64; ++w) t += s_w[tid][w];
+            s_t[2 * tid + (non ? 1 : 0)][p] = t;
+        }
+        __syncthreads();
+    }
+    for (int w = kEvalSumBlocks / 2; w > 0; w >>= 1) {
+        if (tid < 4 * w) s_t[tid / w][tid % w] += s_t[tid / w][tid % w + w];
+        __syncthreads();
+    }
+    const double se = s_t[0][0], sn = s_t[1][0], ce = s_t[2][0], cn = s_t[3][0];
+    if (set == 0 && tid == 0) write_means(out, se, sn, ce, cn);
+    const int64_t count = (int64_t)(set ? cn : ce);
+    if (count == 0 || nq == 0) {  // uniform
+        if (tid < nq) out[5 + set * nq + tid] = __builtin_nan("");
+        return;
+    }
+    // the wanted ranks, ascending
+    if (tid < nr) {
+        int64_t lo, hi;
+        double frac;
+        quantile_place(Q.q[tid >> 1], count, &lo, &hi, &frac);
+        s_rank[tid] = (uint32_t)(tid & 1 ? hi : lo);
+    }
+    __syncthreads();
+    if (tid < nr) {
+        const uint32_t mine = s_rank[tid];
+        int at = 0;
+        for (int j = 0; j < nr; ++j)
+            at += s_rank[j] < mine || (s_rank[j] == mine && j < tid) ? 1 : 0;
+        s_order[at] = (uint16_t)tid;
+        s_rest[at] = mine;
+        s_pre[at] = 0u;
+    }
+    __syncthreads();
+    const int64_t i0 = set ? n_edge : 0, i1 = set ? n : n_edge;
+    for (int shift = 24; shift >= 0; shift -= 8) {
+        // the distinct values of the bits above, ascending: the level's slots
+        if (tid < nr) {
+            int slot = 0;
+            for (int j = 1; j <= tid; ++j) slot += s_pre[j] != s_pre[j - 1] ? 1 : 0;
+            s_slot[tid] = (uint16_t)slot;
+            s_uniq[slot] = s_pre[tid];
+            if (tid == nr - 1) s_slots = slot + 1;
+        }
+        __syncthreads();
+        const int slots = s_slots;
+        for (int g0 = 0; g0 < slots; g0 += kSmallSlots) {
+            const int g1 = g0 + kSmallSlots < slots ? g0 + kSmallSlots : slots;
+            for (int j = tid; j < kSmallSlots * 256; j += kSumThreads) s_bin[j] = 0u;
+            __syncthreads();
+            small_values(d, i0, i1, [&](float x) {
+                const uint32_t key = __float_as_uint(x);
+                // (all of the value, shifted out, at the first level)
+                const uint32_t above = shift == 24 ? 0u : key >> (shift + 8);
+                int lo = g0, hi = g1;  // the first slot not below
+                while (lo < hi) {
+                    const int mid = (lo + hi) / 2;
+                    if (s_uniq[mid] < above)
+                        lo = mid + 1;
+                    else
+                        hi = mid;
+                }
+                if (lo < g1 && s_uniq[lo] == above)
+                    atomicAdd(&s_bin[(lo - g0) * 256 + (int)(key >> shift & 255u)], 1u);
+            });
+            __syncthreads();
+            // a wave per rank: its digit among the slot's counters
+            for (int r = wave; r < nr; r += kSumThreads / 64) {
+                const int slot = s_slot[r];
+                if (slot < g0 || slot >= g1) continue;
+                const uint32_t* const bin = s_bin + (slot - g0) * 256 + lane * 4;
+                const uint32_t c[4] = {bin[0], bin[1], bin[2], bin[3]};
+                const uint32_t sum = c[0] + c[1] + c[2] + c[3], rest = s_rest[r];
+                uint32_t incl = sum;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const uint32_t t = __shfl_up(incl, off, 64);
+                    if (lane >= off) incl += t;
+                }
+                const uint32_t base = incl - sum;
+                if (rest >= base && rest - base < sum) {
+                    uint32_t left = rest - base, j = 0;
+                    while (j < 3u && left >= c[j]) left -= c[j++];
+                    s_rest[r] = left;
+                    s_pre[r] = s_pre[r] << 8 | ((uint32_t)lane * 4u + j);
+                }
+            }
+            __syncthreads();
+        }
+    }
+    // s_pre holds the order statistics' bits: back to the percentiles' order
+    if (tid < nr) s_rank[s_order[tid]] = s_pre[tid];
+    __syncthreads();
+    if (tid < nq) {
+        int64_t lo, hi;
+        double frac;
+        quantile_place(Q.q[tid], count, &lo, &hi, &frac);
+        const double a = (double)__uint_as_float(s_rank[2 * tid]);
+        const double b = (double)__uint_as_float(s_rank[2 * tid + 1]);
+        out[5 + set * nq + tid] = a + frac * (b - a);
+    }
+}
+
 hipError_t launch_eval_summary(const float* d, int64_t n_edge, int64_t n_non, const double* q,
-                               int nq, const SumBuffers& B, double* out, hipStream_t s) {
+                               int nq, const SumBuffers& B, bool have_counters, double* out,
+                               hipStream_t s) {
     if (nq < 0 || nq > kEvalMaxQuantiles) return hipErrorInvalidValue;
     const int64_t n = n_edge + n_non;
     Quantiles Q;
@@ -610,6 +792,16 @@ hipError_t launch_eval_summary(const float* d, int64_t n_edge, int64_t n_non, co
         return (int)(b < kEvalSumBlocks / 2 ? b : kEvalSumBlocks / 2);
     };
     const int eb = blocks_of(n_edge), blocks = eb + blocks_of(n_non);
+    if (!have_counters) {
+        constexpr size_t kLds = sizeof(uint32_t) * kSmallSlots * 256;
+        const hipError_t e = hipFuncSetAttribute(
+            reinterpret_cast<const void*>(&k_sum_small),
+            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_sum_small, dim3(2), dim3(kSumThreads), kLds, s, d, n_edge, n, eb,
+                           blocks, Q, nq, out);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_sum_clear, dim3(128), dim3(kBlock), 0, s, B.bins, B.mid, B.low);
     if (blocks > 0) {
         // LDS beyond 64 KB is asked for explicitly, once

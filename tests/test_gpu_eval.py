@@ -207,6 +207,46 @@ def test_summary_selects_the_order_statistics(ne, nn, kind):
         assert np.all(close | np.equal(s[name], want) | (np.isnan(s[name]) & np.isnan(want)))
 
 
+@pytest.mark.parametrize("ne,nn", [(0, 0), (1, 0), (0, 3), (700, 2), (20_001, 9_000),
+                                   (3, 65_537), (100_000, 130_000)])
+@pytest.mark.parametrize("kind", ["spread", "near", "odd"])
+def test_summary_in_the_least_workspace_gives_the_same_bits(ne, nn, kind):
+    """Two words per distance, 8 KB per 8192 and 12,544 bytes: less than the
+    counters of the selection take, and always accepted."""
+    import ctypes
+    n = ne + nn
+    rng = np.random.default_rng(n + len(kind))
+    if kind == "spread":
+        d = np.exp(rng.uniform(-90, 80, n)).astype(np.float32)
+    elif kind == "near":
+        d = (rng.normal(1.4, 0.05, n)).astype(np.float32)
+    else:  # few values, many of them equal, no number or infinite
+        d = rng.choice(np.array([0.0, -0.0, 1.5, np.inf, np.nan, 1e-40, -2.0], np.float32), n)
+    say(f"summary in the least workspace ne={ne} nn={nn} {kind}")
+    q = (ctypes.c_double * 128)(*rng.uniform(0, 100, 126), 0.0, 100.0)
+    align = lambda x: (x + 255) // 256 * 256  # noqa: E731
+    m = max(n, 1)
+    least = 2 * align(4 * m) + 8192 * ((m + 8191) // 8192) + 12544
+    L = P.load()
+    full = L.huge_eval_workspace_bytes(m, 16, 16, 1)
+    dd = dev(d, torch)
+    got = []
+    for nbytes in (full, least):
+        ws = torch.full((nbytes,), 255, dtype=torch.uint8, device="cuda")
+        assert ws.data_ptr() % 256 == 0
+        out = torch.full((5 + 256,), -7.0, dtype=torch.float64, device="cuda")
+        run = lambda b: L.huge_eval_summary(  # noqa: E731
+            ctypes.c_void_p(dd.data_ptr() if n else None), ne, nn, q, 128,
+            ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(ws.data_ptr()), b, None)
+        if nbytes == least:
+            assert run(least - 1) == -4
+        assert run(nbytes) == 0
+        torch.cuda.synchronize()
+        got.append(out.cpu().numpy())
+    same = (got[0].view(np.int64) == got[1].view(np.int64)) | (np.isnan(got[0]) & np.isnan(got[1]))
+    assert same.all(), np.flatnonzero(~same)
+
+
 # --------------------------------------------------------------------------- nearest rows
 def check_knn(T, queries, k, ids, dist):
     """The GPU's k nearest against exact (double) distances."""
