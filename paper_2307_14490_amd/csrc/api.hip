@@ -990,6 +990,7 @@ SummaryLayout summary_layout(int64_t max_pairs) {
 
 struct KnnLayout {
     size_t qn, qn2, qid, partial, tau, cnt, gate, cand, qh, total;
+    int32_t cnt_stride;
 };
 
 KnnLayout knn_layout(int64_t num_rows, int32_t dim, int32_t k) {
@@ -1008,11 +1009,19 @@ KnnLayout knn_layout(int64_t num_rows, int32_t dim, int32_t k) {
         take(sizeof(uint64_t) * (size_t)knn_lists(num_rows, dim, 1) * kKnnPass * (size_t)k);
     // the threshold scans' bounds, counts, gate and candidate lists
     L.tau = take(sizeof(float) * kKnnPass);
-    L.cnt = take(sizeof(uint32_t) * kKnnPass * kKnnCntStride);
+    L.cnt = take(sizeof(uint32_t) * kKnnPass);
     L.gate = take(sizeof(int32_t));
     L.cand = take(sizeof(uint64_t) * kKnnPass * (size_t)kKnnCandCap);
-    L.qh = take(sizeof(uint16_t) * kKnnPass * (size_t)((dim + 15) / 16 * 16));
     L.total = off;
+    // several scans: the counts, a cache line apart, and the queries' fp16 parts
+    // lie where the list search keeps its lists, which runs after the scans
+    // (more than kKnnStageTiles tiles: at least 260 lists, 266,240 bytes)
+    L.qh = L.partial;
+    L.cnt_stride = 1;
+    if (num_rows > 32 * kKnnStageTiles) {
+        L.cnt = L.partial + align_up(sizeof(uint16_t) * kKnnPass * (size_t)((dim + 15) / 16 * 16));
+        L.cnt_stride = kKnnCntStride;
+    }
     return L;
 }
 
@@ -1113,6 +1122,7 @@ huge_status eval_knn(const float* d_table, int64_t num_rows, int32_t dim,
     B.partial = reinterpret_cast<uint64_t*>(ws + L.partial);
     B.tau = reinterpret_cast<float*>(ws + L.tau);
     B.cnt = reinterpret_cast<uint32_t*>(ws + L.cnt);
+    B.cnt_stride = L.cnt_stride;
     B.gate = reinterpret_cast<int32_t*>(ws + L.gate);
     B.cand = reinterpret_cast<uint64_t*>(ws + L.cand);
     B.qh = reinterpret_cast<_Float16*>(ws + L.qh);

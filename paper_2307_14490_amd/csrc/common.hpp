@@ -447,8 +447,9 @@ struct KnnBuffers {
     int32_t* qid;     // [kKnnPass] their rows (-1: padding)
     uint64_t* partial;  // per-wave lists of the list-merging search
     float* tau;       // [kKnnPass] distance bound of the next threshold scan
-    uint32_t* cnt;    // [kKnnPass * kKnnCntStride] candidates of the current scan
-    _Float16* qh;     // wide rows: the queries' fp16 parts, as matrix operands
+    uint32_t* cnt;    // [kKnnPass * cnt_stride] candidates of the current scan
+    int32_t cnt_stride;
+    _Float16* qh;     // wide rows, several scans: the queries' fp16 parts, as matrix operands
     uint64_t* cand;   // [kKnnPass][kKnnCandCap] their keys
     int32_t* gate;    // 1: a final scan overflowed, the list-merging search runs
 };

@@ -857,6 +857,7 @@ __global__ __launch_bounds__(kBlock) void k_knn_queries(const float* __restrict_
                                                         int32_t* __restrict__ qid,
                                                         float* __restrict__ tau,
                                                         uint32_t* __restrict__ cnt,
+                                                        int32_t cnt_stride,
                                                         int32_t* __restrict__ gate,
                                                         _Float16* __restrict__ qh,
                                                         int32_t* __restrict__ status) {
@@ -899,7 +900,7 @@ __global__ __launch_bounds__(kBlock) void k_knn_queries(const float* __restrict_
         qn2[j] = n2 > 0.f ? 1.f : 0.f;
         qid[j] = id;
         if (cnt) {
-            cnt[j * kKnnCntStride] = 0u;
+            cnt[j * cnt_stride] = 0u;
             const bool screened = n2 == 0.f || (n2 >= kKnnNormMin && n2 <= kKnnNormMax);
             tau[j] = id >= 0 && screened ? __builtin_inff() : -__builtin_inff();
         }
@@ -1566,6 +1567,7 @@ struct KnnScanArgs {
     int64_t N;
     int32_t D;
     int32_t cap;    // keys kept per list
+    int32_t cnt_stride;  // words between the counts of two queries
     int64_t step;   // tiles i * step, 0 <= i < count
     int64_t count;
     const float* qn;
@@ -1604,7 +1606,7 @@ __device__ __forceinline__ void knn_scan_append(const KnnScanArgs& A, int qb, in
         if (d2 <= tau && m < rows && t * 32 + m != qid) pass |= 1u << r;
     }
     if (pass == 0u) return;
-    uint32_t pos = atomicAdd(&A.cnt[q * kKnnCntStride], (uint32_t)__popc(pass));
+    uint32_t pos = atomicAdd(&A.cnt[q * A.cnt_stride], (uint32_t)__popc(pass));
     uint64_t* dst = A.cand + (size_t)q * A.cap;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -1756,6 +1758,7 @@ struct KnnSelectArgs {
     uint32_t* cnt;
     const uint64_t* cand;
     int32_t cap;
+    int32_t cnt_stride;  // words between the counts of two queries
     int32_t k;
     int32_t last;      // 1: the last scan
     int32_t m;         // queries of the pass (slots beyond are padding)
@@ -1777,7 +1780,7 @@ __global__ __launch_bounds__(kKnnSelectThreads) void k_knn_select(KnnSelectArgs 
     static_assert(kKnnSelectBins == kKnnSelectThreads, "a bin per thread");
     static_assert(kKnnCandCap % kKnnSelectThreads == 0, "whole keys per thread");
     const int q = blockIdx.x, tid = threadIdx.x;
-    const uint32_t c = S.cnt[q * kKnnCntStride];
+    const uint32_t c = S.cnt[q * S.cnt_stride];
     const uint32_t n = c < (uint32_t)S.cap ? c : (uint32_t)S.cap;
     constexpr int kPer = kKnnCandCap / kKnnSelectThreads;
     s_bin[tid] = 0u;
@@ -1875,7 +1878,7 @@ __global__ __launch_bounds__(kKnnSelectThreads) void k_knn_select(KnnSelectArgs 
     } else if (tid == 0 && s_key[S.k - 1] != kNoKey && S.tau[q] != -__builtin_inff()) {
         S.tau[q] = __uint_as_float((uint32_t)(s_key[S.k - 1] >> 32));
     }
-    if (tid == 0) S.cnt[q * kKnnCntStride] = 0u;
+    if (tid == 0) S.cnt[q * S.cnt_stride] = 0u;
 }
 
 // ---------------------------------------------------------------------------
@@ -1918,6 +1921,7 @@ struct KnnWideArgs {
     int64_t N;
     int32_t D;
     int32_t cap;
+    int32_t cnt_stride;  // words between the counts of two queries
     int64_t step;   // tiles i * step, 0 <= i < count
     int64_t count;
     const float* qn;
@@ -1956,7 +1960,7 @@ __global__ __launch_bounds__(256) void k_knn_wide_dense(KnnWideArgs A) {
         const bool pair = ok && id >= 0 && row != (int64_t)id;
         A.cand[(size_t)q * A.cap + (size_t)i * 32 + x] =
             pair ? ((uint64_t)__float_as_uint(d2) << 32) | (uint64_t)row : kNoKey;
-        if (i == 0 && x == 0) A.cnt[q * kKnnCntStride] = (uint32_t)(A.count * 32);
+        if (i == 0 && x == 0) A.cnt[q * A.cnt_stride] = (uint32_t)(A.count * 32);
     }
 }
 
@@ -1968,7 +1972,7 @@ __global__ __launch_bounds__(256) void k_knn_wide_rescore(KnnWideArgs A) {
     const int lane = threadIdx.x & 63;
     const int x = lane & 31, h = lane >> 5;
     const int q = blockIdx.x;
-    const uint32_t c = A.cnt[q * kKnnCntStride];
+    const uint32_t c = A.cnt[q * A.cnt_stride];
     const uint32_t n = c < (uint32_t)A.cap ? c : (uint32_t)A.cap;
     if (32u * 4u * blockIdx.y >= n) return;  // uniform
     for (int d = threadIdx.x; d < A.D; d += 256) s_query[d] = A.qn[(int64_t)q * A.D + d];
@@ -2097,7 +2101,7 @@ void k_knn_wide_scan(KnnWideArgs A) {
                 const int q = qb * 32 + 8 * (r / 4) + 4 * h + (r % 4);
                 // a padding slot, or a query that the scans do not answer
                 if (A.tau[q] == -__builtin_inff()) continue;
-                const uint32_t pos = atomicAdd(&A.cnt[q * kKnnCntStride], 1u);
+                const uint32_t pos = atomicAdd(&A.cnt[q * A.cnt_stride], 1u);
                 if (pos < (uint32_t)A.cap) A.cand[(size_t)q * A.cap + pos] = (uint64_t)row;
             }
         }
@@ -2226,12 +2230,13 @@ hipError_t launch_knn(const float* T, int64_t N, int32_t D, const int32_t* q, in
         const int32_t nqp = 32 * QB;
         hipLaunchKernelGGL(k_knn_queries, dim3((unsigned)nqp), dim3(kBlock), 0, s, T, N, D,
                            q + q0, m, nqp, B.qn, B.qn2, B.qid, scans ? B.tau : nullptr,
-                           scans ? B.cnt : nullptr, scans ? B.gate : nullptr,
-                           scans && wide ? B.qh : nullptr, status);
+                           scans ? B.cnt : nullptr, B.cnt_stride, scans ? B.gate : nullptr,
+                           scans && wide && tiles > kKnnStageTiles ? B.qh : nullptr, status);
         KnnSelectArgs SS;
         SS.cnt = B.cnt;
         SS.cand = B.cand;
         SS.cap = kKnnCandCap;
+        SS.cnt_stride = B.cnt_stride;
         SS.k = k;
         SS.m = m;
         SS.q_first = q0;
@@ -2247,6 +2252,7 @@ hipError_t launch_knn(const float* T, int64_t N, int32_t D, const int32_t* q, in
             WA.N = N;
             WA.D = D;
             WA.cap = kKnnCandCap;
+            WA.cnt_stride = B.cnt_stride;
             WA.qn = B.qn;
             WA.qn2 = B.qn2;
             WA.qid = B.qid;
@@ -2286,6 +2292,7 @@ hipError_t launch_knn(const float* T, int64_t N, int32_t D, const int32_t* q, in
             SA.N = N;
             SA.D = D;
             SA.cap = kKnnCandCap;
+            SA.cnt_stride = B.cnt_stride;
             SA.qn = B.qn;
             SA.qn2 = B.qn2;
             SA.qid = B.qid;

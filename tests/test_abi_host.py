@@ -154,6 +154,16 @@ def test_workspace_grows_with_batch_and_holds_duplicate_buffer():
     assert 0 < atomic < big
 
 
+@pytest.mark.parametrize("pairs,rows,dim,k,most", [
+    (8, 100, 16, 1, 8407296), (8, 8192, 128, 32, 16845056), (8, 8193, 128, 1, 8726784),
+    (8, 8193, 132, 1, 8724736), (8, 10**6, 256, 10, 19007744), (8, 9000, 524, 1, 8950016),
+    (3_000_000, 1000, 64, 10, 27019008), (8, 10**8, 128, 10, 29427968)])
+def test_evaluation_workspace_does_not_grow(pairs, rows, dim, k, most):
+    """Sizes that callers' own arrays may have been given: an array that held
+    the evaluation's workspace goes on holding it."""
+    assert 0 < P.load().huge_eval_workspace_bytes(pairs, rows, dim, k) <= most
+
+
 @pytest.mark.parametrize("walks,steps,seeds", [(1024, 4, 30), (256, 6, 2000), (126, 64, 8192),
                                                (1, 1, 1), (128, 3, 65_536)])
 def test_walk_workspace_holds_the_nodes_of_all_seeds(walks, steps, seeds):
