@@ -149,7 +149,7 @@ Layout make_layout(const huge_config* c) {
     const int64_t pmax = sample_tile_positives(K, INT64_MAX / 2);
     L.sort_tiles = (nb + pmax - 1) / pmax;
     if (L.sort_tiles < kSampleTiles) L.sort_tiles = kSampleTiles;
-    L.loss_blocks = nb + 1;  // at most one workgroup per positive
+    L.loss_blocks = nb / 4 + 1;  // a workgroup holds at least kBlock / 64 = 4 positives
     L.cap_short = caps.shorts;
     L.cap_piece = caps.pieces;
     L.cap_comb = caps.combs;
@@ -160,6 +160,7 @@ Layout make_layout(const huge_config* c) {
         off = align_up(off + bytes);
         return at;
     };
+    size_t beyond = 0;  // bytes of the slots' occ beyond the regions they share
     for (int s = 0; s < kSlots; ++s) {
         SlotLayout& S = L.slot[s];
         S.ctrl = take(sizeof(Control));
@@ -172,12 +173,19 @@ Layout make_layout(const huge_config* c) {
             S.info = take(sizeof(int32_t) * (size_t)M);
             S.tcount = take(sizeof(uint32_t) * (size_t)(L.sort_tiles * kMaxBins));
             S.tprefix = take(sizeof(uint32_t) * (size_t)(L.sort_tiles * kMaxBins));
+            // the grouping lists the occurrences once the radix pass has read
+            // the tiles' counts
+            S.occ = S.tcount;
+            const size_t end = align_up(S.occ + sizeof(uint32_t) * (size_t)M);
+            if (end > off) {
+                beyond += end - off;
+                off = end;
+            }
             S.bstart = take(sizeof(uint32_t) * kMaxBins);
             S.shorts = take(sizeof(uint4) * (size_t)caps.shorts);
             S.pieces = take(sizeof(uint4) * (size_t)caps.pieces);
             S.combs = take(sizeof(uint4) * (size_t)caps.combs);
             S.ccount = take(sizeof(uint32_t) * (size_t)caps.combs);
-            S.bcount = take(sizeof(uint4) * kMaxBins);
             S.wstats = take(sizeof(uint32_t) * kMaxBins * 3);
         }
     }
@@ -185,15 +193,18 @@ Layout make_layout(const huge_config* c) {
     L.lossp = take(sizeof(double) * (size_t)L.loss_blocks);
     if (sorted) {
         L.part = take(sizeof(double) * (size_t)caps.parts * (size_t)D);
-        // occurrences by slot, kept source rows and source gradients, in a region of at least D floats per occurrence (the size
-        // huge_workspace_bytes reports for a sorted handle holds that much)
+        // kept source rows and source gradients.  The workspace is not made
+        // smaller than D floats per occurrence, nor larger than it was when
+        // each occurrence had them (but for small dim, 8 max_batch dim bytes
+        // are used of 4 max_batch (2 + K) dim): callers size their arrays by it
         const size_t rows = align_up(sizeof(float) * (size_t)(nb * D));
-        const size_t occ = align_up(sizeof(uint32_t) * (size_t)M);
-        const size_t need = kSlots * occ + 2 * rows;
         const size_t slots = sizeof(float) * (size_t)(M * D);
-        size_t at = take(need > slots ? need : slots);
-        for (int s = 0; s < kSlots; ++s, at += occ) L.slot[s].occ = at;
-        L.srow = at;
+        const size_t left = slots > beyond ? slots - beyond : 0;
+        // where both would not fit, the gradients take the place of the applied
+        // batch's sorted keys, which its grouping was the last to read
+        L.sgrad_in_keys = 2 * rows > left && 2 * align_up(sizeof(uint32_t) * (size_t)M) >= rows;
+        const size_t need = L.sgrad_in_keys ? rows : 2 * rows;
+        L.srow = take(need > left ? need : left);
         L.sgrad = L.srow + rows;
     } else {
         L.gsrc = take(sizeof(float) * (size_t)(nb * D));
@@ -436,7 +447,7 @@ huge_status stage_prepare(huge_handle* h, const int32_t* src, const int32_t* dst
                              at<int32_t>(h, SL.info), at<uint32_t>(h, SL.occ),
                              at<uint4>(h, SL.shorts),
                              at<uint4>(h, SL.pieces), at<uint4>(h, SL.combs),
-                             at<uint32_t>(h, SL.ccount), at<uint4>(h, SL.bcount), caps,
+                             at<uint32_t>(h, SL.ccount), caps,
                              at<uint32_t>(h, SL.wstats), 1 << bits, h->key_bits, beside,
                              h->ready[slot], &ready_recorded, s));
         if (!prof_mark(h, b, 5, s)) return HUGE_ERR_HIP;
@@ -493,7 +504,8 @@ huge_status apply_next(huge_handle* h, float lr, double* loss_out, hipStream_t s
             ev_start = h->prof_ev[(size_t)b.prof * kProfEvents + 6];
             ev_stop = h->prof_ev[(size_t)b.prof * kProfEvents + 7];
         }
-        const RepeatArgs rep{h->ws + L.srow, at<float>(h, L.sgrad)};
+        const RepeatArgs rep{h->ws + L.srow,
+                             at<float>(h, L.sgrad_in_keys ? SL.keys1 : L.sgrad)};
         HIP_TRY(launch_fused_step(t, ctl, a, at<int32_t>(h, SL.keys0) + 2, stride,
                                   at<int32_t>(h, SL.info), rep, lossp, &blocks, ev_start,
                                   ev_stop, s));

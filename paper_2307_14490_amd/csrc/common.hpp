@@ -15,7 +15,6 @@ constexpr int kBlock = 256;            // threads per workgroup (4 wave64)
 constexpr int kMinDigitBits = 8;       // digit widths of the LSD radix sort: 8 to 10 bits,
 constexpr int kMaxDigitBits = 10;      // the same in every pass of a sort
 constexpr int kMaxBins = 1 << kMaxDigitBits;
-constexpr int kMaxPasses = 4;          // keys < 2^32
 constexpr int kSortTile = 8192;        // keys per radix-pass tile
 // The kernels of the grouping before the per-bucket one (sampling with the tile
 // counts, their prefixes, the radix pass) run in workgroups of kBlock threads
@@ -141,17 +140,17 @@ struct SlotLayout {
     size_t tcount = 0;   // u32 [sort_tiles * kMaxBins] occurrences per tile and digit
     size_t tprefix = 0;  // u32 [sort_tiles * kMaxBins] the same summed over earlier tiles
     size_t bstart = 0;   // u32 [kMaxBins] first position of each bucket
-    size_t occ = 0;      // u32 [M] by duplicate slot: the occurrence
+    size_t occ = 0;      // u32 [M] by duplicate slot: the occurrence (over tcount, tprefix
+                         // and beyond)
     // repeated-row records: short runs and pieces in one list each (a range
     // of the grouping appends at positions reserved from Control::nshort,
     // ::npiece); bucket b (first position s0, n items) writes its combine
     // records at [s0 / 256, ...) and partial slots from s0 / 128 (ListCaps
-    // says why they fit) and its counts to bcount[b]
+    // says why they fit)
     size_t shorts = 0;   // uint4 [cap_short] {start, len, key, 0}
     size_t pieces = 0;   // uint4 [cap_piece] {start, len, key, 0 or combine record index + 1}
     size_t combs = 0;    // uint4 [cap_comb] {key, first partial, partials, first slot}
     size_t ccount = 0;   // u32 [cap_comb] pieces of the row summed so far
-    size_t bcount = 0;   // uint4 [kMaxBins] {short runs, pieces, combines, 0} per bucket
     size_t wstats = 0;   // u32 [kMaxBins * 3] distinct S, distinct T, repeated occurrences
 };
 
@@ -172,6 +171,7 @@ struct Layout {
                          // with a repeated context row
     size_t sgrad = 0;    // f32 [max_batch * D] source gradients of those with a repeated
                          // source row
+    bool sgrad_in_keys = false;  // ... or in the applied slot's keys1 and vals1
     // atomic scatter
     size_t gsrc = 0;     // f32 [max_batch * D] source-row gradients
     size_t coef = 0;     // f32 [max_batch * (1 + K)]
@@ -354,7 +354,7 @@ hipError_t launch_radix_pass(Control* ctl, const uint32_t* keys_in, uint32_t* ke
 hipError_t launch_group(Control* ctl, const uint32_t* keys, const uint32_t* vals, int64_t m,
                         int64_t N, const uint32_t* hist, const uint32_t* bstart, int32_t* info,
                         uint32_t* occ, uint4* shorts, uint4* pieces, uint4* combs, uint32_t* ccount,
-                        uint4* bcount, ListCaps caps, uint32_t* wstats, int bins, int key_bits,
+                        ListCaps caps, uint32_t* wstats, int bins, int key_bits,
                         bool beside, hipEvent_t stop, bool* launched, hipStream_t s);
 // Negative k of positive i: neg[i * neg_stride + k].
 // Occurrences of repeated rows: what the fused step leaves and the finish

@@ -341,8 +341,7 @@ hipError_t launch_radix_pass(Control* ctl, const uint32_t* keys_in, uint32_t* ke
 //   place:  the repeated items, taken in occurrence order (chunk by chunk,
 //           compacted, then ranked by one wave 64 at a time), receive their
 //           row's next slot: info[o] = slot, occ[slot] = o.
-// At the end the bucket's record counts go to bcount[b].  No step waits for
-// another workgroup; the only device-scope atomics reserve a range's places
+// No step waits for another workgroup; the only device-scope atomics reserve a range's places
 // in the batch's record lists.  Where a row's range lands
 // depends on the order of the hash insertions, the order of its occurrences
 // does not: every sum is taken in occurrence order.  Items that occur once
@@ -422,7 +421,7 @@ __attribute__((amdgpu_waves_per_eu(4, 4))) void k_group(
     const uint32_t* __restrict__ vals, int64_t m, int64_t N, const uint32_t* __restrict__ hist,
     const uint32_t* __restrict__ bstart, int32_t* __restrict__ info,
     uint32_t* __restrict__ occ, uint4* __restrict__ shorts, uint4* __restrict__ pieces, uint4* __restrict__ combs, uint32_t* __restrict__ ccount,
-    uint4* __restrict__ bcount, ListCaps caps, uint32_t* __restrict__ wstats, int bins, int shift,
+    ListCaps caps, uint32_t* __restrict__ wstats, int bins, int shift,
     int sub_bits, int cap, int most_tbits) {
     constexpr int ITEMS = kGroupChunk / THREADS;  // consecutive keys of a thread
     static_assert(ITEMS * THREADS == kGroupChunk, "whole keys per thread");
@@ -460,7 +459,6 @@ __attribute__((amdgpu_waves_per_eu(4, 4))) void k_group(
     if (n == 0u || s0 + (int64_t)n > m) {
         if (n != 0u && tid == 0) HUGE_FAIL(kSiteGroupBucket);
         if (tid < 3) wstats[b * 3 + tid] = 0u;
-        if (tid == 0) bcount[b] = make_uint4(0u, 0u, 0u, 0u);
         continue;
     }
     const bool cached = n <= (uint32_t)cap;
@@ -858,7 +856,6 @@ __attribute__((amdgpu_waves_per_eu(4, 4))) void k_group(
     }
     __syncthreads();
     if (tid < 3) wstats[b * 3 + tid] = s_stat[tid];
-    if (tid == 0) bcount[b] = make_uint4(nb_short, nb_piece, nb_comb, 0u);
     }
 finished:
     if (bad) raise_internal(ctl, bad);
@@ -868,7 +865,7 @@ finished:
 hipError_t launch_group(Control* ctl, const uint32_t* keys, const uint32_t* vals, int64_t m,
                         int64_t N, const uint32_t* hist, const uint32_t* bstart, int32_t* info,
                         uint32_t* occ, uint4* shorts, uint4* pieces, uint4* combs, uint32_t* ccount,
-                        uint4* bcount, ListCaps caps, uint32_t* wstats, int bins, int key_bits,
+                        ListCaps caps, uint32_t* wstats, int bins, int key_bits,
                         bool beside, hipEvent_t stop, bool* launched, hipStream_t s) {
     *launched = false;
     if (m == 0) return hipSuccess;
@@ -887,7 +884,7 @@ hipError_t launch_group(Control* ctl, const uint32_t* keys, const uint32_t* vals
         hipExtLaunchKernelGGL((k_group<BM, THREADS>), dim3((unsigned)bins),                   \
                               dim3(THREADS), g.words * sizeof(uint32_t), s, nullptr, stop, 0, \
                               ctl, keys, vals, m, N, hist, bstart, info, occ, shorts, pieces, \
-                              combs, ccount, bcount, caps, wstats, bins, shift, sub_bits,     \
+                              combs, ccount, caps, wstats, bins, shift, sub_bits,     \
                               g.cap, g.tbits);                                                \
     } while (0)
     if (bm && beside) {

@@ -154,6 +154,16 @@ def test_workspace_grows_with_batch_and_holds_duplicate_buffer():
     assert 0 < atomic < big
 
 
+@pytest.mark.parametrize("dim,K,batch,dtype,most", [
+    (4, 1, 1, 0, 8546304), (4, 1, 1000003, 0, 369869568), (4, 3, 65536, 0, 47261440),
+    (8, 1, 1000003, 0, 418619904), (128, 5, 65536, 0, 293636608), (4, 64, 8000000, 1, 63723245568)])
+def test_workspace_does_not_grow(dim, K, batch, dtype, most):
+    """Sizes that callers' own arrays may have been given, from when every
+    occurrence had a row of its own in the workspace."""
+    cfg = P.make_config(10**6, dim, K, batch, table_dtype=dtype)
+    assert 0 < P.workspace_bytes(cfg) <= most
+
+
 @pytest.mark.parametrize("pairs,rows,dim,k,most", [
     (8, 100, 16, 1, 8407296), (8, 8192, 128, 32, 16845056), (8, 8193, 128, 1, 8726784),
     (8, 8193, 132, 1, 8724736), (8, 10**6, 256, 10, 19007744), (8, 9000, 524, 1, 8950016),

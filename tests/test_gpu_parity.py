@@ -685,3 +685,29 @@ def test_grouping_alone_and_beside_give_the_same_steps(N, n, K, skew):
     counts = [np.unique(x, return_counts=True)[1] for x in (src, ctx)]
     assert got[0][3] == (counts[0].size, counts[1].size,
                          int(sum(c[c > 1].sum() for c in counts)))
+
+
+def test_large_batches_of_short_rows_in_a_pipeline():
+    """D = 4, K = 1 and batches whose workspace has no room of its own for the
+    source gradients: they lie over the applied batch's sorted keys, while the
+    next batch is grouped."""
+    N, D, K, n, lr = 200_000, 4, 1, 600_011, 0.02
+    rng = np.random.default_rng(4)
+    say(f"pipeline D={D} K={K} n={n}")
+    tr = P.Trainer(N, D, K, n, seed=8, init_half_width=0.5)
+    ref = [t.cpu().numpy().copy() for t in (tr.S, tr.T)]
+    side = torch.cuda.Stream()
+    batches = [[rng.integers(0, N, n).astype(np.int32) for _ in range(2)] +
+               [rng.integers(1, 4, n).astype(np.int32)] for _ in range(3)]
+    args = [[dev(x, torch) for x in b] for b in batches]
+    torch.cuda.synchronize()
+    tr.prepare(*args[0], 0, stream=side)
+    for k in range(3):
+        if k + 1 < 3:
+            tr.prepare(*args[k + 1], (k + 1) * n, stream=side)
+        tr.train_prepared(lr)
+    assert tr.check() == 0
+    for k, (src, dst, cc) in enumerate(batches):
+        orc.step_dense(*ref, src, dst, cc, orc.sample_negatives(8, k * n, n, K, N), lr)
+    for got, want in zip((tr.S, tr.T), ref):
+        assert_close(got.cpu().numpy(), want, "row")
