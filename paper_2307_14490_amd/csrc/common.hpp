@@ -6,7 +6,26 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 namespace huge {
+
+// Dynamic LDS beyond 64 KB has to be asked for, per kernel and device: `bytes` is
+// the most that kernel is launched with.  Asked once on a device; a call that
+// fails is made again by the next launch.
+template <auto* KERNEL>
+inline hipError_t allow_lds(size_t bytes) {
+    static std::atomic<uint64_t> done{0};  // a bit per device
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = dev >= 0 && dev < 64 ? (uint64_t)1 << dev : 0u;
+    if (done.load(std::memory_order_relaxed) & bit) return hipSuccess;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e == hipSuccess) done.fetch_or(bit, std::memory_order_relaxed);
+    return e;
+}
 
 // ---------------------------------------------------------------------------
 // Compile-time constants

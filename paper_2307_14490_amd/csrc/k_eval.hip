@@ -794,9 +794,7 @@ hipError_t launch_eval_summary(const float* d, int64_t n_edge, int64_t n_non, co
     const int eb = blocks_of(n_edge), blocks = eb + blocks_of(n_non);
     if (!have_counters) {
         constexpr size_t kLds = sizeof(uint32_t) * kSmallSlots * 256;
-        const hipError_t e = hipFuncSetAttribute(
-            reinterpret_cast<const void*>(&k_sum_small),
-            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
+        const hipError_t e = allow_lds<&k_sum_small>(kLds);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_sum_small, dim3(2), dim3(kSumThreads), kLds, s, d, n_edge, n, eb,
                            blocks, Q, nq, out);
@@ -804,12 +802,9 @@ hipError_t launch_eval_summary(const float* d, int64_t n_edge, int64_t n_non, co
     }
     hipLaunchKernelGGL(k_sum_clear, dim3(128), dim3(kBlock), 0, s, B.bins, B.mid, B.low);
     if (blocks > 0) {
-        // LDS beyond 64 KB is asked for explicitly, once
         constexpr size_t kLds = sizeof(uint32_t) * 32768;
-        static const hipError_t set = hipFuncSetAttribute(
-            reinterpret_cast<const void*>(&k_sum_hist),
-            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
-        if (set != hipSuccess) return set;
+        const hipError_t e = allow_lds<&k_sum_hist>(kLds);
+        if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_sum_hist, dim3((unsigned)blocks), dim3(kSumThreads), kLds, s, d,
                            n_edge, n, eb, B.bins, B.part);
     }
@@ -2139,11 +2134,12 @@ void k_knn_wide_scan(KnnWideArgs A) {
 
 template <int QB>
 static hipError_t launch_knn_wide_scan(const KnnWideArgs& A, hipStream_t s) {
-    const size_t lds = sizeof(knn_h8) * 64 * QB * (size_t)((A.D + 15) / 16) +
-                       sizeof(float) * 32 * QB;
-    const hipError_t e = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&k_knn_wide_scan<QB>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    auto lds_bytes = [](int D) {
+        return sizeof(knn_h8) * 64 * QB * (size_t)((D + 15) / 16) + sizeof(float) * 32 * QB;
+    };
+    const size_t lds = lds_bytes(A.D);
+    // the widest rows taken: 32 queries of them fill kKnnQueryFloats
+    const hipError_t e = allow_lds<&k_knn_wide_scan<QB>>(lds_bytes(kKnnQueryFloats / 32));
     if (e != hipSuccess) return e;
     int64_t grid = (A.count + kKnnWideWaves - 1) / kKnnWideWaves;
     grid = grid < kKnnGrid ? grid : kKnnGrid;

@@ -275,15 +275,8 @@ hipError_t launch_radix_bits(Control* ctl, const uint32_t* keys_in, uint32_t* ke
                              const uint32_t* hist, const uint32_t* tprefix, uint32_t* bstart,
                              int64_t tiles, hipStream_t s) {
     constexpr size_t kLds = radix_lds_bytes<BITS, THREADS>();
-    // LDS beyond 64 KB is asked for explicitly, once per variant
-    static bool lds_set = false;
-    if (!lds_set) {
-        const hipError_t e = hipFuncSetAttribute(
-            reinterpret_cast<const void*>(&k_radix_pass<BITS, THREADS>),
-            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
-        if (e != hipSuccess) return e;
-        lds_set = true;
-    }
+    const hipError_t e = allow_lds<&k_radix_pass<BITS, THREADS>>(kLds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_radix_pass<BITS, THREADS>), dim3((unsigned)tiles), dim3(THREADS),
                        kLds, s, ctl, keys_in, keys_out, vals_out, m, tile,
                        hist, tprefix, bstart);
@@ -876,10 +869,7 @@ hipError_t launch_group(Control* ctl, const uint32_t* keys, const uint32_t* vals
     const GroupShape g = group_shape(m, bins, sub_bits);
 #define HUGE_GROUP_LAUNCH(BM, THREADS)                                                        \
     do {                                                                                      \
-        /* LDS beyond 64 KB is asked for explicitly, once per variant */                      \
-        static const hipError_t set = hipFuncSetAttribute(                                    \
-            reinterpret_cast<const void*>(&k_group<BM, THREADS>),                             \
-            hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes - 1024);                    \
+        const hipError_t set = allow_lds<&k_group<BM, THREADS>>(kLdsBytes - 1024);            \
         if (set != hipSuccess) return set;                                                    \
         hipExtLaunchKernelGGL((k_group<BM, THREADS>), dim3((unsigned)bins),                   \
                               dim3(THREADS), g.words * sizeof(uint32_t), s, nullptr, stop, 0, \
