@@ -156,22 +156,13 @@ __device__ __forceinline__ void store_chunk(bf16_t* __restrict__ row, int j, flo
     reinterpret_cast<uint2*>(row)[j] = float4_to_bf16x4(v);
 }
 
-// The same with a streaming hint: for rows that no later access of the same
-// kernel meets in its XCD's L2.
 typedef uint32_t stream_u4 __attribute__((ext_vector_type(4)));
 typedef uint32_t stream_u2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void store_chunk_stream(float* __restrict__ row, int j, float4 v) {
-    __builtin_nontemporal_store(stream_u4{__float_as_uint(v.x), __float_as_uint(v.y),
-                                          __float_as_uint(v.z), __float_as_uint(v.w)},
-                                reinterpret_cast<stream_u4*>(row) + j);
-}
-__device__ __forceinline__ void store_chunk_stream(bf16_t* __restrict__ row, int j, float4 v) {
-    const uint2 w = float4_to_bf16x4(v);
-    __builtin_nontemporal_store(stream_u2{w.x, w.y}, reinterpret_cast<stream_u2*>(row) + j);
-}
 
 // Four consecutive elements as a kernel keeps them in registers: a float4
 // for float tables, the packed uint2 for bf16 tables (widened when used).
+// store_stream: with a streaming hint, for rows that no later access of the
+// same kernel meets in its XCD's L2.
 template <typename E>
 struct Packed4;
 template <>
@@ -179,6 +170,11 @@ struct Packed4<float> {
     using T = float4;
     __device__ __forceinline__ static T load(const float* __restrict__ row, int j) {
         return reinterpret_cast<const float4*>(row)[j];
+    }
+    __device__ __forceinline__ static void store_stream(float* __restrict__ row, int j, T r) {
+        __builtin_nontemporal_store(stream_u4{__float_as_uint(r.x), __float_as_uint(r.y),
+                                              __float_as_uint(r.z), __float_as_uint(r.w)},
+                                    reinterpret_cast<stream_u4*>(row) + j);
     }
     __device__ __forceinline__ static float4 widen(T r) { return r; }
     __device__ __forceinline__ static T zero() { return zero4(); }
@@ -189,6 +185,9 @@ struct Packed4<bf16_t> {
     using T = uint2;
     __device__ __forceinline__ static T load(const bf16_t* __restrict__ row, int j) {
         return reinterpret_cast<const uint2*>(row)[j];
+    }
+    __device__ __forceinline__ static void store_stream(bf16_t* __restrict__ row, int j, T r) {
+        __builtin_nontemporal_store(stream_u2{r.x, r.y}, reinterpret_cast<stream_u2*>(row) + j);
     }
     __device__ __forceinline__ static float4 widen(T r) { return bf16x4_to_float4(r); }
     __device__ __forceinline__ static T zero() { return make_uint2(0u, 0u); }
@@ -250,15 +249,15 @@ struct RowIO {
             if (j < q) store_chunk(p, j, x[c]);
         }
     }
-    __device__ __forceinline__ static void store_stream(E* __restrict__ base, int64_t row,
-                                                        int32_t D, int lane,
-                                                        const float4 (&x)[C]) {
+    __device__ __forceinline__ static void store_packed_stream(E* __restrict__ base, int64_t row,
+                                                               int32_t D, int lane,
+                                                               const Reg (&r)[R]) {
         E* p = base + row * (int64_t)D;
         const int q = D >> 2;
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const int j = lane + c * G;
-            if (j < q) store_chunk_stream(p, j, x[c]);
+            if (j < q) P::store_stream(p, j, r[c]);
         }
     }
     __device__ __forceinline__ static float dot(const float4 (&a)[C], const float4 (&b)[C]) {
@@ -330,18 +329,16 @@ struct PairIO<G, U, bf16_t> {
             }
         }
     }
-    __device__ __forceinline__ static void store_stream(bf16_t* __restrict__ base, int64_t row,
-                                                        int32_t D, int lane,
-                                                        const float4 (&x)[C]) {
+    __device__ __forceinline__ static void store_packed_stream(bf16_t* __restrict__ base,
+                                                               int64_t row, int32_t D, int lane,
+                                                               const Reg (&r)[R]) {
         stream_u4* p = reinterpret_cast<stream_u4*>(base + row * (int64_t)D);
         const int nu = D >> 3;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int k = lane + u * G;
-            if (k < nu) {
-                const uint2 a = float4_to_bf16x4(x[2 * u]), b = float4_to_bf16x4(x[2 * u + 1]);
-                __builtin_nontemporal_store(stream_u4{a.x, a.y, b.x, b.y}, p + k);
-            }
+            if (k < nu)
+                __builtin_nontemporal_store(stream_u4{r[u].x, r[u].y, r[u].z, r[u].w}, p + k);
         }
     }
     __device__ __forceinline__ static float dot(const float4 (&a)[C], const float4 (&b)[C]) {

@@ -52,6 +52,11 @@ __device__ __forceinline__ void block_loss(float loss, double* __restrict__ out)
 // through HBM twice.  131,072 positives, K = 31, 1e7 nodes (1.4M repeated
 // occurrences): fused 900 -> 780 us, finish 356 -> 305; 100,003 positives of a
 // power-law graph, K = 20, D = 256: 800 -> 490 and 565 -> 468.
+// The row is stored as packed words before anything is computed, and a
+// coefficient where its row would be updated: no variant holds more registers
+// for it than the waves it had before allow (with both stored after a block,
+// 18 reached variants lost a wave per SIMD; 32,768 positives, bf16, D = 640,
+// K = 6: 336 us before the rows were kept, 377 then, 310 now).
 template <int G, int NB, bool FULL, typename IO, typename DIO>
 __global__ __launch_bounds__(kBlock) void k_fused_step(TableArgs t, Control* __restrict__ ctl,
                                                        StepArgs a, const int32_t* __restrict__ neg,
@@ -67,10 +72,10 @@ __global__ __launch_bounds__(kBlock) void k_fused_step(TableArgs t, Control* __r
     // Registers: at least 88 VGPRs for float tables -- five waves per SIMD
     // (440 of 512 registers), not six -- and at least 104 for bf16 tables,
     // whose variants need more than 88: four waves, not five -- so that one
-    // wave of the next batch's preparation (at most 64 VGPRs; the per-bucket
-    // grouping's 93 beside bf16 tables) fits beside them on every SIMD.  The
-    // empty statement marks the register as
-    // used; it generates no instruction.
+    // wave of the next batch's preparation (at most 64 VGPRs, the grouping's 93
+    // beside bf16 tables) fits beside them
+    // on every SIMD.  The empty statement marks the register as used; it
+    // generates no instruction.
     if constexpr (sizeof(E) == 2)
         asm volatile("" ::: "v103");
     else
@@ -140,13 +145,24 @@ __global__ __launch_bounds__(kBlock) void k_fused_step(TableArgs t, Control* __r
     if (active) {
         const float c = c_i;
         float4 s[C], dS[C];
-        Reg t0[R];
+        Reg sp[R], t0[R];
         Reg tk[NB][R];
-        IO::load(s, S, u, D, lane);
+        IO::load_packed(sp, S, u, D, lane);
         IO::load_packed(t0, T, v, D, lane);
 #pragma unroll
         for (int j = 0; j < NB; ++j)
             if (j < cnt) IO::load_packed(tk[j], T, mk[j], D, lane);
+        // a repeated context row in the block: the source row is kept as it was
+        // read; streamed: a plain store cost the pipelined step 1.2% (the finish
+        // kernel is the next to read it)
+        int32_t slot = info_d;
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+            if (j < cnt) slot = slot > ik[j] ? slot : ik[j];
+        bool kept = slot >= 0;
+        if (kept) IO::store_packed_stream(srow, i32, D, lane, sp);
+#pragma unroll
+        for (int q = 0; q < C; ++q) s[q] = IO::chunk(sp, q);
 
         // positive pair
         const float x = group_sum<G>(IO::dotp(s, t0));
@@ -162,6 +178,8 @@ __global__ __launch_bounds__(kBlock) void k_fused_step(TableArgs t, Control* __r
 #pragma unroll
                 for (int q = 0; q < C; ++q) nv[q] = axpy4(-(lr * g), s[q], IO::chunk(t0, q));
                 IO::store(T, v, D, lane, nv);
+            } else if (lane == 0) {
+                info[o + 1] = __float_as_int(g);
             }
         };
         if constexpr (!kLanePos) {
@@ -173,11 +191,6 @@ __global__ __launch_bounds__(kBlock) void k_fused_step(TableArgs t, Control* __r
         }
 
         // negatives, NB rows in flight at a time
-        int32_t slot = info_d;  // >= 0: a context row so far is repeated
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-            if (j < cnt) slot = slot > ik[j] ? slot : ik[j];
-        bool kept = false;  // the source row is in srow
         int kb = 0;
         while (true) {
             float y[NB];
@@ -234,34 +247,9 @@ __global__ __launch_bounds__(kBlock) void k_fused_step(TableArgs t, Control* __r
                         for (int q = 0; q < C; ++q)
                             nv[q] = axpy4(-(lr * h[j]), s[q], IO::chunk(tk[j], q));
                         IO::store(T, mk[j], D, lane, nv);
+                    } else if (lane == 0) {
+                        info[o + 2 + (uint32_t)(kb + j)] = __float_as_int(h[j]);
                     }
-                }
-            }
-            if (slot >= 0) {
-                // exact: the row as it was read; streamed: a plain store cost the
-                // pipelined step 1.2% (the finish kernel is the next to read it)
-                if (!kept) IO::store_stream(srow, i32, D, lane, s);
-                kept = true;
-                // the coefficients of the block's repeated rows (and the
-                // destination's): lane q stores that of context row kb + q
-                if constexpr (G > NB) {
-                    float w = g;
-                    int32_t own = kb == 0 ? info_d : -1;
-#pragma unroll
-                    for (int j = 0; j < NB; ++j) {
-                        if (lane == j + 1) {
-                            w = h[j];
-                            own = j < cnt ? ik[j] : -1;
-                        }
-                    }
-                    if (lane <= NB && own >= 0)
-                        info[o + 1 + (uint32_t)(kb + lane)] = __float_as_int(w);
-                } else if (lane == 0) {
-                    if (kb == 0 && info_d >= 0) info[o + 1] = __float_as_int(g);
-#pragma unroll
-                    for (int j = 0; j < NB; ++j)
-                        if (j < cnt && ik[j] >= 0)
-                            info[o + 2 + (uint32_t)(kb + j)] = __float_as_int(h[j]);
                 }
             }
             kb += NB;
@@ -281,6 +269,12 @@ __global__ __launch_bounds__(kBlock) void k_fused_step(TableArgs t, Control* __r
                     slot = slot > ik[j] ? slot : ik[j];
                     IO::load_packed(tk[j], T, mk[j], D, lane);
                 }
+            }
+            if (slot >= 0 && !kept) {  // the row still stands in the table
+                kept = true;
+                Reg again[R];
+                IO::load_packed(again, S, u, D, lane);
+                IO::store_packed_stream(srow, i32, D, lane, again);
             }
         }
 
