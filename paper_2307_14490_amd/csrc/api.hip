@@ -6,9 +6,11 @@
 // groups its rows: k_begin, k_sample (keys, negatives and the digit counts
 // of each radix tile, a tile being one sampler workgroup's keys), k_tile_scan
 // (the counts' prefixes over tiles), k_radix_pass (occurrences grouped by the
-// lowest digits of their key) and k_group (repeated rows and their slots).  These read only the batch, and every one
-// of them runs in 256-thread workgroups of few registers, so that they run
-// beside the previous batch's apply without evicting its waves.  Applying
+// lowest digits of their key) and k_group (repeated rows and their slots).
+// These read only the batch; prepared ahead, they run in 256-thread workgroups
+// of few registers, so that they run beside the previous batch's apply without
+// evicting its waves (a step that prepares its own batch runs the last two
+// with 512 threads).  Applying
 // (huge_train_prepared, on the apply stream) runs the fused step and the
 // finish kernel (repeated rows, loss).  kSlots grouping slots let two batches
 // be prepared ahead; events order the halves: an apply waits for its batch's

@@ -35,15 +35,15 @@ constexpr int kMinDigitBits = 8;       // digit widths of the LSD radix sort: 8 
 constexpr int kMaxDigitBits = 10;      // the same in every pass of a sort
 constexpr int kMaxBins = 1 << kMaxDigitBits;
 constexpr int kSortTile = 8192;        // keys per radix-pass tile
-// The kernels of the grouping before the per-bucket one (sampling with the tile
-// counts, their prefixes, the radix pass) run in workgroups of kBlock threads
-// within the HUGE_BESIDE register budget, so that they run beside the fused
-// step without evicting any of the step's waves.
+// The preparation of a batch beside the previous one's update runs in workgroups
+// of kBlock threads whose waves fit beside the fused step's: sampling with the
+// tile counts, their prefixes and the radix pass within the HUGE_BESIDE budget,
+// the per-bucket grouping within 72 VGPRs.  A step that waits for its own
+// preparation runs the radix pass and the grouping with 512 threads.
 constexpr int kScanDigits = 4;         // digits per tile-prefix workgroup
-// Register budget of the kernels that run beside the fused step: at most 64
-// VGPRs (the budget of eight waves per SIMD).  With the fused step at five
-// waves of 88 VGPRs per SIMD (440 of 512), one such wave per SIMD fits beside
-// them.
+// At most 64 VGPRs (the budget of eight waves per SIMD).  With the fused step at
+// five waves of 88 VGPRs per SIMD (440 of 512), or four of 104 (bf16 tables,
+// 416), one wave of at most 72 fits beside them.
 #define HUGE_BESIDE __attribute__((amdgpu_waves_per_eu(8, 8)))
 // Per-bucket grouping (k_group): chunks of kGroupChunk keys; an LDS hash table of at most
 // 2^kGroupTableBits slots counts the repeated keys of a key range; a range with

@@ -17,15 +17,27 @@
 //      (inside the bucket's own range of positions), writes the slot of each
 //      of its occurrences, in occurrence order, to info[o], and lists the
 //      repeated rows, and by slot their occurrences, for the finish kernel.
-// All of them can run beside the previous batch's fused step: 256-thread
-// workgroups whose waves hold few registers (one item per thread at a time,
-// loads issued in small groups) and work mostly in LDS.
+// Beside the previous batch's fused step they run in 256-thread workgroups
+// whose waves hold few registers (one item per thread at a time, loads issued in
+// small groups, uniform values as scalars) and work mostly in LDS; a step that
+// waits for its own grouping runs 2 and 3 with 512 threads.
 #include <math.h>
 
 #include "common.hpp"
 #include "device.hpp"
 
 namespace huge {
+
+// A value that every lane of the wave holds alike: beside a fused step
+// (workgroups of kBlock threads) as a scalar, so that what follows from it
+// (counts, table sizes, levels) takes no vector registers; alone, where
+// registers are free, as it is (a scalar has to be waited for: the step of 1024
+// positives took 41.3 us with vector values and 42.0 with scalars).
+template <int THREADS>
+__device__ __forceinline__ uint32_t uniform(uint32_t v) {
+    if constexpr (THREADS == kBlock) return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+    return v;
+}
 
 // Exclusive sum of one value per thread over the workgroup (THREADS threads);
 // *total receives the sum.  Synchronises; s_tmp holds THREADS / 64 words and
@@ -42,10 +54,11 @@ __device__ __forceinline__ uint32_t block_excl(uint32_t v, uint32_t* s_tmp, uint
     if (lane == 63) s_tmp[wave] = incl;
     __syncthreads();
     uint32_t add = 0, all = 0;
+    const int me = (int)uniform<THREADS>((uint32_t)wave);
 #pragma unroll
     for (int w = 0; w < THREADS / 64; ++w) {
-        const uint32_t x = s_tmp[w];
-        if (w < wave) add += x;
+        const uint32_t x = uniform<THREADS>(s_tmp[w]);
+        if (w < me) add += x;
         all += x;
     }
     *total = all;
@@ -358,11 +371,15 @@ __device__ __forceinline__ bool in_range(uint32_t key, int level, uint32_t idx) 
 // the keys need.  A bucket's steps are short and full of barriers, so the
 // kernel alone lives on several workgroups per CU: the most (4 .. 1) for which
 // the LDS left holds the batch's average bucket with six standard deviations
-// of an even spread to spare.  Beside the fused step one workgroup per CU fits
-// by its registers, but what it takes of the LDS the finish kernel's 10 KB
-// workgroups lack, so 48 KB are left to them where the bucket still fits
-// (1e8 rows, fp32: finish 27 us beside 148 KB and a loss sum with 8 loads in
-// flight, 17 beside 112 KB and 16 loads; the two were not timed apart).
+// of an even spread to spare.  Beside a fused step whose waves stay resident one
+// workgroup per CU fits by its registers (more settle as those waves end), but
+// what it takes of the LDS the finish kernel's 10 KB workgroups lack, so 48 KB
+// are left to them where the bucket still fits (1e8 rows, fp32: finish 27 us
+// beside 148 KB and a loss sum with 8 loads in flight, 17 beside 112 KB and 16
+// loads; the two were not timed apart).  A skewed batch's largest buckets are
+// read from memory: steps of 3,000, 8,000, 20,000 and 40,000 positives of a
+// power-law graph (5e4 to 1e6 nodes) took 57.0, 74.1, 113.9 and 215 us when
+// every bucket of 4096 keys was copied, 54.5, 74.2, 105.8 and 202 now.
 struct GroupShape {
     int cap;    // keys and indices cached, a multiple of 64
     int tbits;  // table slots: enough for the repeated keys of an average
@@ -394,35 +411,39 @@ inline GroupShape group_shape(int64_t m, int bins, int sub_bits) {
 }
 
 // THREADS = kBlock runs beside another batch's fused step; a step that waits
-// for its own grouping runs it alone with kGroupAlone threads.  Both keep the
-// registers they need (93 and 109): within 72 a few values were spilled to
-// scratch, which cost more than the wave of a float fused step that now makes
-// room for it (1e8 rows, 112 KB of LDS: 462.6 us per step within 72, 458.4 with
-// 93, 455.8 before the grouping and the finish kernel were changed).  With 148 KB of LDS, 256 threads and 72 VGPRs
-// for all, then as now: sequential steps of 1,024 positives 43.5 -> 40.9 us,
-// 65,536 (medium) 192 -> 183, 131,072 with K = 31 1548 -> 1436 (buckets of
-// 4200 keys found no room for their indices), 100,003 of a power-law graph with
-// K = 20 1373 -> 1318; six pipelined steps of 262,144 fp32 3102 -> 3064, bf16
-// 2179 -> 2008.  256 and 1024 threads alone: 42.3, 189, 1481, 1346 and 47.4,
-// 191, 1455, 1358; 512 beside: 3108 and 2073.
+// for its own grouping runs it alone with kGroupAlone threads.  Beside, the
+// kernel is held to 72 VGPRs (it takes 66 to 69, with every value that is the
+// same for a workgroup in scalar registers), the most that fits beside five
+// waves of a float step; with vector values it took 93, so that a wave of the
+// step had to end first, and the preparation became longer than the update (1e8
+// rows, 200 pipelined steps: 470 us a step, 459 now; the grouping beside a
+// fused kernel 267 and 175).  Alone it takes the registers it needs, 109.  With
+// 148 KB of LDS, 256 threads and 72 VGPRs (a few of them spilled) for all, then
+// with this split: sequential steps of 1,024 positives 43.5 -> 40.9 us, 65,536
+// (medium) 192 -> 183, 131,072 with K = 31 1548 -> 1436 (buckets of 4200 keys
+// found no room for their indices), 100,003 of a power-law graph with K = 20
+// 1373 -> 1318; six pipelined steps of 262,144 fp32 3102 -> 3055, bf16 2179 ->
+// 1985.  256 and 1024 threads alone: 42.3, 189, 1481, 1346 and 47.4, 191, 1455,
+// 1358; 512 beside: 3108 and 2073.
 constexpr int kGroupAlone = 512;
 
 template <bool BM, int THREADS>
 __global__ __launch_bounds__(THREADS)
-__attribute__((amdgpu_waves_per_eu(4, 4))) void k_group(
+__attribute__((amdgpu_waves_per_eu(THREADS == kBlock ? 7 : 4, THREADS == kBlock ? 7 : 4)))
+void k_group(
     Control* __restrict__ ctl, const uint32_t* __restrict__ keys,
     const uint32_t* __restrict__ vals, int64_t m, int64_t N, const uint32_t* __restrict__ hist,
     const uint32_t* __restrict__ bstart, int32_t* __restrict__ info,
-    uint32_t* __restrict__ occ, uint4* __restrict__ shorts, uint4* __restrict__ pieces, uint4* __restrict__ combs, uint32_t* __restrict__ ccount,
-    ListCaps caps, uint32_t* __restrict__ wstats, int bins, int shift,
-    int sub_bits, int cap, int most_tbits) {
+    uint32_t* __restrict__ occ, uint4* __restrict__ shorts, uint4* __restrict__ pieces,
+    uint4* __restrict__ combs, uint32_t* __restrict__ ccount, ListCaps caps,
+    uint32_t* __restrict__ wstats, int bins, int shift, int sub_bits, int cap, int most_tbits) {
     constexpr int ITEMS = kGroupChunk / THREADS;  // consecutive keys of a thread
     static_assert(ITEMS * THREADS == kGroupChunk, "whole keys per thread");
     // words of one bitmap
     const uint32_t bit_words = sub_bits > 5 ? 1u << (sub_bits - 5) : 1u;
     // The large arrays live in dynamic LDS (group_shape): the compiler then
-    // keeps to the HUGE_BESIDE register budget, which a static size above a
-    // fifth of the LDS would let it exceed.
+    // keeps to the register budget, which a static size above a fifth of the
+    // LDS would let it exceed.
     extern __shared__ uint32_t s_dyn[];
     uint32_t* const s_key = s_dyn;                          // [2^most_tbits]
     uint32_t* const s_cnt = s_key + (1 << most_tbits);      // count; after emit, kRepFlag | next slot
@@ -534,7 +555,7 @@ __attribute__((amdgpu_waves_per_eu(4, 4))) void k_group(
         __syncthreads();
     }
     // with the bitmap: nothing repeated, nothing to group
-    const bool any = !BM || s_nrep != 0u;
+    const bool any = !BM || uniform<THREADS>(s_nrep) != 0u;
 
     // With the bitmap and the whole bucket in LDS, only the items of
     // repeated keys are grouped: they are compacted to the front of the LDS
@@ -618,7 +639,7 @@ __attribute__((amdgpu_waves_per_eu(4, 4))) void k_group(
         bool over = false;
         for (uint32_t c0 = 0; c0 < nw; c0 += kGroupChunk) {
             const uint32_t len = nw - c0 < (uint32_t)kGroupChunk ? nw - c0 : (uint32_t)kGroupChunk;
-            if (s_distinct + len > tload) {  // uniform: the table could fill up
+            if (uniform<THREADS>(s_distinct) + len > tload) {  // uniform: the table could fill up
                 over = true;
                 break;
             }
@@ -646,7 +667,7 @@ __attribute__((amdgpu_waves_per_eu(4, 4))) void k_group(
             if (fresh) atomicAdd(&s_distinct, fresh);
             __syncthreads();
             seen = c0 + len;
-            if (s_fail || s_distinct > tmax) {  // uniform
+            if (uniform<THREADS>(s_fail) || uniform<THREADS>(s_distinct) > tmax) {  // uniform
                 over = true;
                 break;
             }
@@ -654,8 +675,8 @@ __attribute__((amdgpu_waves_per_eu(4, 4))) void k_group(
         if (over) {
             // split the range; its first part next (uniform)
             int add = 1;
-            if (!s_fail && seen > 0u) {
-                const uint64_t est = (uint64_t)s_distinct * nw / seen;
+            if (!uniform<THREADS>(s_fail) && seen > 0u) {
+                const uint64_t est = (uint64_t)uniform<THREADS>(s_distinct) * nw / seen;
                 while (add < 8 && est > ((uint64_t)tmax << add) / 4u * 3u) ++add;
             }
             __syncthreads();
@@ -714,7 +735,7 @@ __attribute__((amdgpu_waves_per_eu(4, 4))) void k_group(
             s_rbase[1] = t_piece ? atomicAdd(&ctl->npiece, t_piece) : 0u;
         }
         __syncthreads();
-        const uint32_t b_short = s_rbase[0], b_piece = s_rbase[1];
+        const uint32_t b_short = uniform<THREADS>(s_rbase[0]), b_piece = uniform<THREADS>(s_rbase[1]);
         // uniform: every thread has the same totals and bases
         const bool fits = (uint64_t)nb_short + t_short <= c_short &&
                           (uint64_t)nb_piece + t_piece <= c_piece &&

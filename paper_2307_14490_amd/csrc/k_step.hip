@@ -72,8 +72,7 @@ __global__ __launch_bounds__(kBlock) void k_fused_step(TableArgs t, Control* __r
     // Registers: at least 88 VGPRs for float tables -- five waves per SIMD
     // (440 of 512 registers), not six -- and at least 104 for bf16 tables,
     // whose variants need more than 88: four waves, not five -- so that one
-    // wave of the next batch's preparation (at most 64 VGPRs, the grouping's 93
-    // beside bf16 tables) fits beside them
+    // wave of the next batch's preparation (at most 72 VGPRs) fits beside them
     // on every SIMD.  The empty statement marks the register as used; it
     // generates no instruction.
     if constexpr (sizeof(E) == 2)

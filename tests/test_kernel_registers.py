@@ -104,3 +104,15 @@ def test_fused_step_leaves_room_for_the_preparation(kernels):
         m = re.search(r"k_fused_step<(\d+), 5, true, (\w+)<\d+, 1, (unsigned short|float)>", name)
         if m is not None:
             assert vgprs <= (88 if m[3] == "float" else 104), name[:90]
+
+
+def test_preparation_fits_beside_the_fused_step(kernels):
+    """Nothing that runs beside it takes more than the 72 registers left, or keeps
+    any in memory."""
+    seen = 0
+    for name, (vgprs, scratch) in kernels.items():
+        m = re.search(r"k_(group|radix_pass)<(?:true|false|\d+), 256>|k_(sample|tile_scan)\(", name)
+        if m is not None:
+            seen += 1
+            assert vgprs <= (72 if m[1] == "group" else 64) and scratch == 0, name[:90]
+    assert seen == 7
