@@ -1894,7 +1894,9 @@ __global__ __launch_bounds__(kKnnSelectThreads) void k_knn_select(KnnSelectArgs 
 // The screen.  A tile's rows are taken in slabs of 128 dimensions, the next
 // slab's loads in flight during the current one's products.  A row is scaled
 // by sc = 64 / |its first slab| before its fp16 rounding, since its own norm
-// is known only after the last slab; with f = sc |row| / 2^10, the product of
+// is known only after the last slab (where a slab takes the scaled norm past
+// 2^14, by 64 / |the slabs so far|, and the products so far with it, one more
+// rounding each); with f = sc |row| / 2^10, the product of
 // the fp16 parts is f times that of the normalised parts scaled by 2^20, up to
 //   the roundings: 2^-11 of each operand's norm, 2^10 (1 + 2^-11) units in all
 //     (a unit is f times one of a product of size 2^20); parts below 2^-14
@@ -1905,11 +1907,14 @@ __global__ __launch_bounds__(kKnnSelectThreads) void k_knn_select(KnnSelectArgs 
 // product is at least f ((|q|^2 + 1 - tau) 2^19) less those (a zero row:
 // |q|^2 - tau); kKnnScreenMargin = 1536 units are left.  A row whose scaled
 // norm leaves [1, 2^14], or whose norm is tiny or not finite, is no subject of
-// the screen: it is appended to every list.  Should a list overflow, the pass
-// is computed by the list search.
+// the screen: it is appended to every list that has not overflowed.  Should a
+// list overflow, the pass is computed by the list search.
 // 500,000 x 256 rows, 100 queries, k = 10: the list search alone, in two passes
 // over the table, took 1349 us, the scans take 274 us (dense 19, scan
 // 123, rescore 49, selections 14 each; the table once at the copy rate: 106).
+// With the first 128 dimensions zero, or 1e-4 of the others: 1322 us in the list
+// search, 11,980 while such rows went to every list, 241 now; a table of rows
+// that are no numbers: 1052, 11,840 and 1071.
 // ---------------------------------------------------------------------------
 struct KnnWideArgs {
     const float* T;
@@ -2047,6 +2052,18 @@ void k_knn_wide_scan(KnnWideArgs A) {
                 for (int r = 0; r < 16; ++r) acc[qb][r] = 0.f;
         } else {
             nr += p;
+            // this slab would take the scaled norm past 2^14 (or is the first
+            // that is not zero): the row is scaled anew, and its products with it
+            const bool anew = sc * sc * nr > 268435456.f || (sc == 0.f && p > 0.f);
+            if (__ballot(anew) != 0ull) {
+                const float to = anew ? 64.f / sqrtf(nr) : sc;
+                const float by = anew ? (sc > 0.f ? to / sc : 0.f) : 1.f;
+                sc = to;
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[qb][r] *= by;
+            }
         }
 #pragma unroll
         for (int c = 0; c < kCh; ++c) {
@@ -2096,6 +2113,10 @@ void k_knn_wide_scan(KnnWideArgs A) {
                 const int q = qb * 32 + 8 * (r / 4) + 4 * h + (r % 4);
                 // a padding slot, or a query that the scans do not answer
                 if (A.tau[q] == -__builtin_inff()) continue;
+                // (an append is an atomic: not for rows in their thousands)
+                if (force && __hip_atomic_load(&A.cnt[q * A.cnt_stride], __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT) > (uint32_t)A.cap)
+                    continue;
                 const uint32_t pos = atomicAdd(&A.cnt[q * A.cnt_stride], 1u);
                 if (pos < (uint32_t)A.cap) A.cand[(size_t)q * A.cap + pos] = (uint64_t)row;
             }

@@ -459,6 +459,29 @@ def test_knn_scans_match_the_list_search_on_rows_no_screen_holds_for(N, D, nq, k
     assert torch.equal(dist.view(torch.int32), dist_l.view(torch.int32))
 
 
+@pytest.mark.parametrize("N,D,slabs", [(40007, 256, (0.0, 1.0)), (40007, 260, (1e-4, 1.0, 1.0)),
+                                       (40007, 388, (1e-6, 1e-3, 1.0, 1.0)),
+                                       (20011, 520, (0.0, 1e-5, 1.0, 1e3, 1e5)),
+                                       (20011, 384, (1e4, 1.0, 1e-4)), (20011, 192, (0.0, 0.0))])
+def test_knn_wide_scans_of_rows_whose_slabs_differ_in_size(N, D, slabs):
+    """Rows that are zero or small in their first 128 dimensions are scaled anew
+    where a larger slab follows: the list search's answer bit for bit."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + D)
+    T = torch.randn((N, D), generator=g, device="cuda")
+    for j, scale in enumerate(slabs):
+        T[:, 128 * j:128 * (j + 1)] *= scale
+    T[::7, :128] = torch.randn((T[::7].shape[0], 128), generator=g, device="cuda")
+    T[5] = float("nan")
+    q = torch.randint(0, N, (40,), generator=g, device="cuda", dtype=torch.int32)
+    say(f"knn wide slabs N={N} D={D} {slabs}")
+    ev = P.Evaluator(N, D, 8, k=10)
+    ids, dist = ev.knn(T, q, 10)
+    ids_l, dist_l = ev.knn(T, q, 10, lists=True)
+    assert torch.equal(ids, ids_l)
+    assert torch.equal(dist.view(torch.int32), dist_l.view(torch.int32))
+
+
 def test_knn_wide_falls_back_to_the_list_search_when_a_candidate_list_overflows():
     N, D, k = 30000, 192, 10
     T = torch.from_numpy(np.random.default_rng(8).normal(size=(N, D)).astype(np.float32)).cuda()
