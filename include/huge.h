@@ -393,9 +393,10 @@ huge_status huge_eval_summary(const float* d_dist, int64_t n_edge, int64_t n_non
    harnesses that forbid hipMalloc): the same kernels on a fixed 32 MiB array
    of device memory that the library holds on every device it runs on until
    the process ends.  It allocates nothing and calls no allocating routine.
-   n_edge + n_non may be up to 3,726,784 (the largest count whose summary
-   workspace fits in the array); more returns HUGE_ERR_WORKSPACE before any
-   launch.  Every call on a device uses that
+   n_edge + n_non may be up to 3,726,784 (the largest count for which two words
+   per distance and 8 KB per 8192 of them fit in the array: the workspace that
+   the summary has always been given, of which it uses 2.1 MB now); more returns
+   HUGE_ERR_WORKSPACE before any launch.  Every call on a device uses that
    device's one array and finds the previous call's contents there (nothing
    is carried over: each call writes what it reads); calls that overlap on
    one device -- on different streams or from different threads without

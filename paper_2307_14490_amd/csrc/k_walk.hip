@@ -21,10 +21,12 @@
 //                 seed's triples;
 //   k_walk_sums,  the triples' places: sums of ranges of the counts, then
 //   k_walk_scan   their exclusive scan;
-//   k_walk_group  a second pass repeats the sort (cheaper than keeping the
-//                 sorted keys: as many bytes as the nodes) and writes them.
-// The nodes of at most kWalkNodeBytes are held at a time: more seeds are
-// taken in chunks, whose walks are taken once for each pass.
+//   k_walk_group  a second pass repeats the sort and writes them.  (Keeping the
+//                 sorted keys was not tried: a walk of 20 steps in windows of 3
+//                 has 456 bytes of them, written and read, for 80 of nodes.)
+// The nodes of the walks fill kWalkNodeBytesMax at most (or what the workspace
+// holds): more seeds are taken in chunks, whose walks are taken once for each
+// pass.
 #include "common.hpp"
 #include "device.hpp"
 
@@ -42,8 +44,7 @@ __device__ __forceinline__ void wave_lds_order() {
 // nodes[w steps .. + steps): its nodes w_1 ..; -1 past its end, and for the
 // whole of a walk on a malformed graph (reported).  The kernel waits for the
 // dependent reads of the CSR arrays (two offsets, one neighbour per hop): one
-// thread per walk keeps up to 2048 walks per CU in flight, and the draws of
-// four hops are formed while the first one's reads are under way.
+// thread per walk keeps up to 2048 walks per CU in flight.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void k_walk_nodes(WalkArgs A, int64_t g0, uint32_t nw,
                                                        const int64_t* __restrict__ total,

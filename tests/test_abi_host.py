@@ -147,7 +147,8 @@ def test_workspace_grows_with_batch_and_holds_duplicate_buffer():
     small = P.workspace_bytes(P.make_config(10**6, 128, 5, 1000))
     big = P.workspace_bytes(P.make_config(10**6, 128, 5, 100_000))
     assert big > small > 0
-    # sorted scatter keeps one D-float slot per occurrence
+    # the size reported for the sorted scatter stays at D floats per occurrence,
+    # of which kept source rows, source gradients and occurrence lists use a part
     M = 100_000 * 7
     assert big >= M * 128 * 4
     atomic = P.workspace_bytes(P.make_config(10**6, 128, 5, 100_000, scatter_kind=1))
