@@ -380,6 +380,13 @@ __device__ __forceinline__ bool in_range(uint32_t key, int level, uint32_t idx) 
 // read from memory: steps of 3,000, 8,000, 20,000 and 40,000 positives of a
 // power-law graph (5e4 to 1e6 nodes) took 57.0, 74.1, 113.9 and 215 us when
 // every bucket of 4096 keys was copied, 54.5, 74.2, 105.8 and 202 now.
+
+// And never all of it: a fused step's workgroup needs some LDS too, so a CU whose
+// LDS a grouping workgroup has filled takes none of them (1e8 rows, K = 31,
+// 262,144 positives, buckets of 8448 keys that no share holds: grouping 1873 us
+// with 159 KB, 1023 with 147; the pipelined step 2618 and 2344).
+constexpr int kGroupBesideLds = kLdsBytes - 12 * 1024;
+
 struct GroupShape {
     int cap;    // keys and indices cached, a multiple of 64
     int tbits;  // table slots: enough for the repeated keys of an average
@@ -387,7 +394,7 @@ struct GroupShape {
     size_t words;  // dynamic LDS
 };
 
-inline GroupShape group_shape(int64_t m, int bins, int sub_bits) {
+inline GroupShape group_shape(int64_t m, int bins, int sub_bits, bool beside) {
     const bool bm = sub_bits <= kBitmapBits;
     const size_t bits = bm ? 2 * (size_t)(sub_bits > 5 ? 1 << (sub_bits - 5) : 1) : 0;
     const double avg = (double)m / bins;
@@ -396,8 +403,9 @@ inline GroupShape group_shape(int64_t m, int bins, int sub_bits) {
     while (tb < kGroupTableBits && (double)(1 << tb) < 0.75 * want) ++tb;
     const size_t fixed = 2 * ((size_t)1 << tb) + kGroupChunk + bits;
     GroupShape g{64, tb, 0};
-    // a quarter, a third, half, 112 KB or all of a CU's LDS
-    for (const int share : {kLdsBytes / 4, kLdsBytes / 3, kLdsBytes / 2, 112 * 1024, kLdsBytes}) {
+    // a quarter, a third, half, 112 KB or all of a CU's LDS (beside: all but 12 KB)
+    const int most = beside ? kGroupBesideLds : kLdsBytes;
+    for (const int share : {kLdsBytes / 4, kLdsBytes / 3, kLdsBytes / 2, 112 * 1024, most}) {
         // the statically allocated LDS of the kernel is below 1 KB
         const size_t budget = (size_t)(share - 1024) / sizeof(uint32_t);
         if (budget < fixed + 2 * 64) continue;
@@ -887,7 +895,7 @@ hipError_t launch_group(Control* ctl, const uint32_t* keys, const uint32_t* vals
     const int shift = __builtin_ctz((unsigned)bins);
     const int sub_bits = key_bits > shift ? key_bits - shift : 0;
     const bool bm = sub_bits <= kBitmapBits;
-    const GroupShape g = group_shape(m, bins, sub_bits);
+    const GroupShape g = group_shape(m, bins, sub_bits, beside);
 #define HUGE_GROUP_LAUNCH(BM, THREADS)                                                        \
     do {                                                                                      \
         const hipError_t set = allow_lds<&k_group<BM, THREADS>>(kLdsBytes - 1024);            \
